@@ -17,6 +17,7 @@
 #include "common.hpp"
 #include "ffn_mfma.hpp"
 #include "ffn_wide.hpp"
+#include "ffn_stream.hpp"
 #include "kernels.hpp"
 
 namespace dicemoe {
@@ -340,8 +341,12 @@ static hipError_t launch_gemm_f32(const void* A, const void* W, const float* bia
     return hipGetLastError();
 }
 
-// Tile shape for one bf16 grouped GEMM.  The wide kernel fetches fewer bytes per flop and keeps the
-// matrix pipe fed from hand-scheduled wavefronts, and wins as soon as its tiles fill most of the chip:
+// Tile shape for one bf16 grouped GEMM.  With at most 64 segments and enough tiles the persistent kernel of
+// ffn_stream.hpp, 192 or 256 columns, whichever its cost model expects to be faster.  The line: 96 tiles of 256 x 192 for the
+// first GEMM, 120 for the second (DiT-MoE-XL widths: at 2000 rows, 288 and 72 tiles, first GEMM 37 us against 39 on the
+// kernels below, second 45 against 43; at 4096 rows, 480 and 120 tiles, 58 against 66 and 57 against 58; at 512 rows, 192 tiles
+// that are mostly padding, first GEMM 28 us against 25).
+// Otherwise the wide kernel, a workgroup per tile, hand-scheduled wavefronts:
 //   256 x 192, one workgroup of eight wavefronts (4 x 2, each a 64 x 96 block; two per SIMD cover each
 //     other's waits, +1 % over four wavefronts of 128 x 96) per compute unit, two stages of activations
 //     and four of weights (all 160 KB of LDS; three with short reductions): the GEMM with the plain
@@ -374,6 +379,12 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
         return m_tiles * ((N + bn - 1) / bn);
     };
     const bool fits_192 = (N + 191) / 192 * 192 * 8 <= N * 9;          // at most 1/8 of the columns computed in vain
+    const bool full_rows = max_rows >= 128 * n_seg;                    // (row tiles half full on average)
+    if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (GELU ? 96 : 116)) {
+        const bool wide = !fits_192 || stream_cost(256, N, K, GELU, max_rows, n_seg) < stream_cost(192, N, K, GELU, max_rows, n_seg);
+        if (wide) return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+        return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+    }
     // Few rows and a long reduction (the second GEMM after a small refresh fraction or for a small batch):
     // the 128 x 192 tiles do not fill the chip and each walks all of K.  With two or three workgroups per
     // tile, each on a share of K (float partial sums in the workspace, added by a second pass in a fixed
@@ -424,6 +435,8 @@ static hipError_t configure_gemm_bf16_auto()
     if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 4, GELU, 4, 2>();
     if (err == hipSuccess) err = configure_gemm_bf16_wide<4, 3, 2, 2, 2, GELU>();
     if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 2, GELU>();
+    if (err == hipSuccess) err = configure_gemm_bf16_stream<3, GELU>();
+    if (err == hipSuccess) err = configure_gemm_bf16_stream<4, GELU>();
     return err;
 }
 
