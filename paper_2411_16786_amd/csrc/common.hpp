@@ -71,6 +71,26 @@ template <> struct Store<bf16_t> {
     }
 };
 
+// One k-step of a 16 x 16 block of sums on the matrix cores, operands as they lie in memory: lane l holds row l % 16 of
+// either operand and 16 bytes of it, the l / 16-th of the step's 64.  Register v of lane l of the result is the sum of
+// row 4 (l / 16) + v of the first operand and row l % 16 of the second.  Float storage takes four instructions, instruction t the
+// t-th component of every lane's 16 bytes (k index 4 (l / 16) + t for both operands); products and sums are float.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+template <typename T> struct RowMfma;
+template <> struct RowMfma<bf16_t> {
+    typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+    static constexpr int kUnit = 32, kMfma = 1;          // k values per step, instructions per step
+    __device__ static __forceinline__ f32x4_t step(const u32x4_t& a, const u32x4_t& b, const f32x4_t& c, int) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(&a), *reinterpret_cast<const bf16x8_t*>(&b), c, 0, 0, 0);
+    }
+};
+template <> struct RowMfma<float> {
+    static constexpr int kUnit = 16, kMfma = 4;
+    __device__ static __forceinline__ f32x4_t step(const u32x4_t& a, const u32x4_t& b, const f32x4_t& c, int t) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[t]), __uint_as_float(b[t]), c, 0, 0, 0);
+    }
+};
+
 __device__ __forceinline__ int lane_id() { return static_cast<int>(threadIdx.x) & (kWave - 1); }
 
 // butterfly sum over the 64 lanes: every lane ends with the same total, and the order of the

@@ -18,6 +18,7 @@
 #include "ffn_mfma.hpp"
 #include "ffn_wide.hpp"
 #include "ffn_stream.hpp"
+#include "ffn_f32.hpp"
 #include "kernels.hpp"
 
 namespace dicemoe {
@@ -172,81 +173,6 @@ __global__ __launch_bounds__(256, OCC) void ffn_gemm_bf16_kernel(const bf16_t* _
                              out_index);
 }
 
-// float path (small workloads): 64x64 tile, depth 16, each thread a 4x4 block, plain FMAs in a
-// fixed order.
-template <bool GELU>
-__global__ __launch_bounds__(256) void ffn_gemm_f32_kernel(const float* __restrict__ A, const float* __restrict__ W,
-                                                           const float* __restrict__ bias, float* __restrict__ C,
-                                                           int N, int K, const int32_t* __restrict__ seg_offsets,
-                                                           const int32_t* __restrict__ seg_expert, int n_seg,
-                                                           int n_tiles_n, const int32_t* __restrict__ row_index,
-                                                           int row_div, const int32_t* __restrict__ out_index,
-                                                           int32_t* __restrict__ status, int max_rows)
-{
-    constexpr int BM = 64, BN = 64, BK = 16;
-    report_row_overflow(status, seg_offsets, n_seg, max_rows);
-    __shared__ float As[BK][BM + 4];
-    __shared__ float Bs[BK][BN + 4];
-    const int tile_m = blockIdx.x / n_tiles_n;
-    const int tile_n = blockIdx.x % n_tiles_n;
-    int seg, row0, row_end;
-    if (!find_row_tile(seg_offsets, n_seg, BM, tile_m, seg, row0, row_end)) return;
-    const int e = seg_expert[seg];
-    const int n0 = tile_n * BN;
-    const float* We = W + static_cast<size_t>(e) * N * K;
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;       // 16 x 16 threads, 4 columns x 4 rows each
-    const int ld_r = tid >> 2, ld_c = (tid & 3) * 4;  // 64 rows x 4 float4 per tile
-
-    int ar = row0 + ld_r; if (ar >= row_end) ar = row_end - 1;
-    if (row_index) ar = row_index[ar] / row_div;
-    int bn = n0 + ld_r;   if (bn >= N) bn = N - 1;
-    const float* a_src = A + static_cast<size_t>(ar) * K + ld_c;
-    const float* b_src = We + static_cast<size_t>(bn) * K + ld_c;
-
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        const float4 av = *reinterpret_cast<const float4*>(a_src + k0);
-        const float4 bv = *reinterpret_cast<const float4*>(b_src + k0);
-        As[ld_c + 0][ld_r] = av.x; As[ld_c + 1][ld_r] = av.y; As[ld_c + 2][ld_r] = av.z; As[ld_c + 3][ld_r] = av.w;
-        Bs[ld_c + 0][ld_r] = bv.x; Bs[ld_c + 1][ld_r] = bv.y; Bs[ld_c + 2][ld_r] = bv.z; Bs[ld_c + 3][ld_r] = bv.w;
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < BK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty * 4 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tx * 4 + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + ty * 4 + i;
-        if (r >= row_end) continue;
-        const int r_out = out_index ? out_index[r] : r;      // scatter: the row out_index names
-        if (r_out < 0) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = n0 + tx * 4 + j;
-            if (n >= N) continue;
-            float val = acc[i][j] + (bias ? bias[static_cast<size_t>(e) * N + n] : 0.f);
-            if (GELU) val = gelu_erf(val);
-            C[static_cast<size_t>(r_out) * N + n] = val;
-        }
-    }
-}
-
 // Second pass of a split reduction: C[r] = bf16(bias + partial[0][r] + partial[1][r] + ...), shares added in
 // index order (no atomics: the same bits in every run).  One workgroup per 4 rows of a segment.
 constexpr int kReduceRows = 4;
@@ -297,6 +223,16 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     }
 }
 
+static hipError_t launch_splitk_reduce(const float* partial, int k_splits, const float* bias, void* C, int N,
+                                       const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
+                                       const int32_t* out_index, hipStream_t stream)
+{
+    const int blocks = (max_rows + kReduceRows - 1) / kReduceRows + n_seg;
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream, partial, k_splits, max_rows, bias,
+                       static_cast<bf16_t*>(C), N, seg_offsets, seg_expert, n_seg, out_index);
+    return hipGetLastError();
+}
+
 // max_rows == 0: no GEMM is launched, but the caller's bound is still checked against the table
 __global__ void row_overflow_check_kernel(int32_t* __restrict__ status, const int32_t* __restrict__ seg_offsets, int n_seg)
 {
@@ -323,21 +259,6 @@ static hipError_t launch_gemm_bf16(const void* A, const void* W, const float* bi
                        dim3(256), 0, stream, static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(W), bias,
                        static_cast<bf16_t*>(C), N, K, seg_offsets, seg_expert, n_seg, n_tiles_n, m_tiles, row_index,
                        row_div, out_index, status, max_rows);
-    return hipGetLastError();
-}
-
-template <bool GELU>
-static hipError_t launch_gemm_f32(const void* A, const void* W, const float* bias, void* C, int N, int K,
-                                  const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
-                                  hipStream_t stream, const int32_t* row_index = nullptr, int row_div = 1,
-                                  const int32_t* out_index = nullptr, int32_t* status = nullptr)
-{
-    const int n_tiles_n = (N + 63) / 64;
-    const int m_tiles = (max_rows + 63) / 64 + n_seg;
-    hipLaunchKernelGGL((ffn_gemm_f32_kernel<GELU>), dim3(static_cast<unsigned>(m_tiles) * n_tiles_n), dim3(256), 0,
-                       stream, static_cast<const float*>(A), static_cast<const float*>(W), bias,
-                       static_cast<float*>(C), N, K, seg_offsets, seg_expert, n_seg, n_tiles_n, row_index, row_div,
-                       out_index, status, max_rows);
     return hipGetLastError();
 }
 
@@ -403,11 +324,7 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
             hipError_t err = launch_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg,
                                                                        max_rows, stream, row_index, row_div, nullptr,
                                                                        by_expert, partial, splits, status);
-            if (err != hipSuccess) return err;
-            const int blocks = (max_rows + kReduceRows - 1) / kReduceRows + n_seg;
-            hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks), dim3(256), 0, stream, partial, splits, max_rows, bias,
-                               static_cast<bf16_t*>(C), N, seg_offsets, seg_expert, n_seg, out_index);
-            return hipGetLastError();
+            return err != hipSuccess ? err : launch_splitk_reduce(partial, splits, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
         }
     }
     if (!GELU && fits_192 && tiles(256, 192) * 10 >= kComputeUnits * 6) {
