@@ -300,11 +300,36 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
         return m_tiles * ((N + bn - 1) / bn);
     };
     const bool fits_192 = (N + 191) / 192 * 192 * 8 <= N * 9;          // at most 1/8 of the columns computed in vain
-    const bool full_rows = max_rows >= 128 * n_seg;                    // (row tiles half full on average)
+    const bool fits_128 = (N + 127) / 128 * 128 * 8 <= N * 9;
+    const bool full_rows = max_rows >= (GELU ? 192 : 128) * n_seg;     // (row tiles at least half full on average)
     if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (GELU ? 96 : 116)) {
         const bool wide = !fits_192 || stream_cost(256, N, K, GELU, max_rows, n_seg) < stream_cost(192, N, K, GELU, max_rows, n_seg);
         if (wide) return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
         return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+    }
+    // Few rows per expert, or few tiles altogether: 64 x 128 tiles, three stages in 72 KB of LDS, so that two workgroups share
+    // a compute unit and cover each other's waits, and a 64-row tile of a small expert is not half padding.  The second GEMM
+    // takes them while they are at most one per compute unit, then 128 x 128 tiles up to the same line; both have 1.5 to 3
+    // times as many workgroups streaming as the 128 x 192 tiles below, which the long reduction would need two or three shares
+    // of K for.  Second GEMM, change of the time of both GEMMs (64 x 128 / 128 x 128): DiT-MoE-XL widths, 1000 rows, 76 us:
+    // -20 / -14; 1400 rows, 66 us: -6 / 0; 1800 rows, 71 us: +5 / -4; 2000 rows, 77 us: +4 / -5; DiT-MoE-S widths, 2000 rows, 39 us:
+    // -12 / -9; 8192 rows, 45 us: -1 / -3; DiT-MoE-G widths, 256 rows, 207 us: -27 / -27; 1024 rows, 214 us: +10 / -11.
+    // First GEMM: up to 192 rows per expert (per cent of the two GEMMs: DiT-MoE-G widths, 256 rows, 11; expert-parallel widths, 1024 rows,
+    // 10; DiT-MoE-XL, 1400 rows, 4; DiT-MoE-S, 2000 rows, 6; -3 at 225 rows per expert of DiT-MoE-XL).
+    if (by_expert && fits_128 && K >= 256) {
+        const long long t64 = tiles(64, 128), t128 = tiles(128, 128);
+        if (GELU && (!full_rows || t64 <= 2 * kComputeUnits))
+            return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
+        // two shares of K while both together are one workgroup per compute unit and sixteen steps long (DiT-MoE-XL
+        // widths: 128 rows 45 us unsplit, 42 split; 512 rows 48.0, 47.3; with twelve steps, DiT-MoE-S, the second pass costs more)
+        if (!GELU && partial && 2 * t64 <= kComputeUnits && K / 64 / 2 >= 16 && static_cast<size_t>(2) * max_rows * N * sizeof(float) <= partial_bytes) {
+            hipError_t err = launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, nullptr, by_expert, partial, 2, status);
+            return err != hipSuccess ? err : launch_splitk_reduce(partial, 2, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
+        }
+        if (!GELU && t64 <= kComputeUnits)
+            return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
+        if (!GELU && t128 <= kComputeUnits)
+            return launch_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
     }
     // Few rows and a long reduction (the second GEMM after a small refresh fraction or for a small batch):
     // the 128 x 192 tiles do not fill the chip and each walks all of K.  With two or three workgroups per
@@ -351,6 +376,8 @@ static hipError_t configure_gemm_bf16_auto()
     if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 3, GELU, 4, 2>();
     if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 4, GELU, 4, 2>();
     if (err == hipSuccess) err = configure_gemm_bf16_wide<4, 3, 2, 2, 2, GELU>();
+    if (err == hipSuccess) err = configure_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>();
+    if (err == hipSuccess && !GELU) err = configure_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>();
     if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 2, GELU>();
     if (err == hipSuccess) err = configure_gemm_bf16_stream<3, GELU>();
     if (err == hipSuccess) err = configure_gemm_bf16_stream<4, GELU>();

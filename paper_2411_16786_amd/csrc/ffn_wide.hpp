@@ -61,7 +61,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
     static_assert(NW * REGION <= AST * ABYTES + WST * WBYTES, "epilogue slabs must fit in the stage buffers");
     static_assert((AST == 2 && (WST == 2 || WST == 3 || WST == 4)) || (AST == 3 && WST == 3) || (AST == 4 && WST == 4),
                   "ring depths (A, W): (2,2), (2,3), (2,4), (3,3), (4,4)");
-    static_assert(NMFMA >= NFRAG, "one fragment read per MFMA slot");
+    constexpr int FPER = (NFRAG + NMFMA - 1) / NMFMA;    // fragment reads per MFMA slot
     static_assert(SPREAD >= 1 && SPREAD <= 4, "a refill is issued within the four slices before it is needed");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     char* const a_lds = smem;
@@ -268,7 +268,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
             for (int m = 0; m < NMFMA; ++m) {
                 if (LIVE) mfma(set, m);
                 DICEMOE_SCHED_FENCE();
-                if (LIVE && m < NFRAG) { read_frag(set ^ 1, m, cur_a, cur_w, kk + 1); DICEMOE_SCHED_FENCE(); }
+#pragma unroll
+                for (int q = 0; q < FPER; ++q)
+                    if (LIVE && m * FPER + q < NFRAG) { read_frag(set ^ 1, m * FPER + q, cur_a, cur_w, kk + 1); DICEMOE_SCHED_FENCE(); }
                 if ((CARA || CARW) && kk + 1 < SPREAD) {
 #pragma unroll
                     for (int j = 0; j < PER; ++j) {
@@ -293,7 +295,9 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
         for (int m = 0; m < NMFMA; ++m) {
             if (LIVE) mfma(1, m);
             DICEMOE_SCHED_FENCE();
-            if (LIVE && NEXT && m < NFRAG) { read_frag(0, m, nxt_a, nxt_w, 0); DICEMOE_SCHED_FENCE(); }
+#pragma unroll
+            for (int q = 0; q < FPER; ++q)
+                if (LIVE && NEXT && m * FPER + q < NFRAG) { read_frag(0, m * FPER + q, nxt_a, nxt_w, 0); DICEMOE_SCHED_FENCE(); }
             if (REFA || REFW) {
 #pragma unroll
                 for (int j = 0; j < PER; ++j) {
