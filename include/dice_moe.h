@@ -290,6 +290,30 @@ int moe_combine(moe_ctx* ctx, const void* h_packed, const int32_t* inv, const fl
                 const uint8_t* mask, int32_t T, void* H_cache, float* S_cache,
                 int32_t use_fresh_scores, void* y, void* stream);
 
+/* One whole layer: moe_gate, then (policy not NULL) moe_conditional_refresh, moe_dispatch, the expert FFN and
+ * moe_combine, with the arguments those calls take, enqueued by one call (a caller in an interpreted language pays its call
+ * overhead once).  Stops at the first part that fails and returns its status.
+ *   fuse_gather   : dispatch writes indices only and the FFN reads the token rows through perm
+ *                   (moe_expert_ffn_rows); 0: x_packed is materialised (moe_expert_ffn)
+ *   rows_to_cache : with a policy, fuse_gather and no shared experts: the FFN scatters the refreshed rows into H_cache
+ *                   (moe_expert_ffn_commit without scores) and the combine reads every row from there
+ *   max_rows      : bound on the refreshed pairs; with imply_rows it is not read and the bound is the count that the policy
+ *                   implies (T*slots without one)
+ * Without a policy mask, n_refresh, H_cache and S_cache are not used. */
+typedef struct moe_layer_args {
+    const void* x; const void* Wg; const float* bg;
+    const void* W1; const float* b1; const void* W2; const float* b2;
+    float* scores; int32_t* expert_idx; float* probs_all; float* logits;
+    uint8_t* mask; int32_t* n_refresh;
+    void* x_packed; void* h_packed;
+    int32_t* counts; int32_t* offsets; int32_t* perm; int32_t* inv;
+    const int32_t* seg_expert;
+    void* H_cache; float* S_cache; void* y; void* workspace;
+    int32_t T, n_segments, max_rows, imply_rows, fuse_gather, rows_to_cache;
+} moe_layer_args;
+
+int moe_layer_forward(moe_ctx* ctx, const moe_layer_args* args, const moe_policy* policy, void* stream);
+
 /* Segment table of an expert-parallel receive buffer (expert-parallelism figure: each device
  * holds a subset of the experts and receives the rows routed to them from every rank).
  * The buffer is ordered [source rank][local expert]; segment g = src*E_loc + e_loc has

@@ -28,7 +28,7 @@ MOE_ERR_WORKSPACE, MOE_ERR_CACHE_COLD, MOE_ERR_HIP = -5, -6, -7
 EXPORTS = ["moe_create", "moe_destroy", "moe_workspace_bytes", "moe_last_error", "moe_status_string",
            "moe_gate", "moe_policy_refreshed_pairs", "moe_conditional_refresh", "moe_dispatch", "moe_dispatch_noalloc", "moe_expert_ffn", "moe_expert_ffn_rows",
            "moe_expert_ffn_commit", "moe_expert_ffn_status", "moe_expert_ffn_between_event", "moe_calibrate_copy",
-           "moe_calibrate_mfma", "moe_combine", "moe_ep_segments"]
+           "moe_calibrate_mfma", "moe_combine", "moe_layer_forward", "moe_ep_segments"]
 
 
 class MoeShape(ctypes.Structure):
@@ -40,6 +40,13 @@ class MoeShape(ctypes.Structure):
 class MoePolicy(ctypes.Structure):
     _fields_ = [("kind", ctypes.c_int32), ("step_t", ctypes.c_int32), ("stride_n", ctypes.c_int32),
                 ("n_units", ctypes.c_int32), ("use_fresh_scores", ctypes.c_int32)]
+
+
+class MoeLayerArgs(ctypes.Structure):
+    _fields_ = [(name, ctypes.c_void_p) for name in (
+        "x", "Wg", "bg", "W1", "b1", "W2", "b2", "scores", "expert_idx", "probs_all", "logits", "mask", "n_refresh",
+        "x_packed", "h_packed", "counts", "offsets", "perm", "inv", "seg_expert", "H_cache", "S_cache", "y",
+        "workspace")] + [(name, ctypes.c_int32) for name in ("T", "n_segments", "max_rows", "imply_rows", "fuse_gather", "rows_to_cache")]
 
 
 class MoeError(RuntimeError):
@@ -81,6 +88,7 @@ def lib() -> ctypes.CDLL:
         L.moe_calibrate_copy.argtypes = [vp, vp, ctypes.c_size_t, i32, vp]
         L.moe_calibrate_mfma.argtypes = [vp, vp, i32, i32, vp]
         L.moe_combine.argtypes = [vp, vp, vp, vp, vp, i32, vp, vp, i32, vp, vp]
+        L.moe_layer_forward.argtypes = [vp, ctypes.POINTER(MoeLayerArgs), ctypes.POINTER(MoePolicy), vp]
         L.moe_ep_segments.argtypes = [vp, vp, i32, i32, vp, vp, vp]
         for name in EXPORTS:
             getattr(L, name)          # AttributeError if the library lacks a declared entry point
@@ -284,42 +292,24 @@ def moe_layer_forward(ctx: Context, buf: LayerBuffers, x, Wg, bg, W1, b1, W2, b2
     shared experts) the expert call scatters the refreshed rows straight into ``buf.H_cache`` and the
     combine reads every row from there: same results bit for bit, ``buf.h_packed`` stays unwritten."""
     T = x.shape[0]
-    N = T * ctx.slots
-    if max_rows is None and policy is not None:
-        max_rows = ctx.moe_policy_refreshed_pairs(policy, T)[0]
-    ctx.moe_gate(x, Wg, bg, buf.scores[:T], buf.expert_idx[:T], buf.probs, buf.logits)
-    mask = None
-    if policy is not None:
-        ctx.moe_conditional_refresh(buf.scores[:T], buf.expert_idx[:T], policy, buf.mask[:T], buf.n_refresh,
-                                    buf.workspace)
-        mask = buf.mask[:T]
-    rows = N if max_rows is None else max_rows
+    cached = policy is not None
     if rows_to_cache is None:
-        rows_to_cache = policy is not None and fuse_gather and ctx.n_shared == 0
-    if rows_to_cache:
-        if policy is None or not fuse_gather or ctx.n_shared != 0:
-            raise ValueError("rows_to_cache needs a policy (caches), the fused gather and no shared experts")
-        ctx.moe_dispatch(x, buf.expert_idx[:T], mask, None, buf.counts, buf.offsets, buf.perm, buf.inv,
-                         buf.workspace)
-        ctx.moe_expert_ffn_commit(x, buf.perm, buf.perm, buf.offsets, buf.seg_expert, rows, W1, b1, W2, b2,
-                                  None, mask, buf.H_cache, None, buf.workspace, T=T)
-        ctx.moe_combine(None, buf.inv, buf.scores[:T], mask, buf.H_cache, buf.S_cache,
-                        bool(policy.use_fresh_scores), buf.y[:T])
-        return buf.y[:T]
-    if fuse_gather:
-        ctx.moe_dispatch(x, buf.expert_idx[:T], mask, None, buf.counts, buf.offsets, buf.perm, buf.inv,
-                         buf.workspace)
-        ctx.moe_expert_ffn_rows(x, buf.perm, buf.offsets, buf.seg_expert, rows, W1, b1, W2, b2, buf.h_packed,
-                                buf.workspace)
-    else:
-        ctx.moe_dispatch(x, buf.expert_idx[:T], mask, buf.x_packed, buf.counts, buf.offsets, buf.perm, buf.inv,
-                         buf.workspace)
-        ctx.moe_expert_ffn(buf.x_packed, buf.offsets, buf.seg_expert, rows, W1, b1, W2, b2, buf.h_packed,
-                           buf.workspace)
-    use_fresh = bool(policy.use_fresh_scores) if policy is not None else False
-    ctx.moe_combine(buf.h_packed, buf.inv, buf.scores[:T], mask,
-                    buf.H_cache if policy is not None else None,
-                    buf.S_cache if policy is not None else None, use_fresh, buf.y[:T])
+        rows_to_cache = cached and fuse_gather and ctx.n_shared == 0
+    if rows_to_cache and (not cached or not fuse_gather or ctx.n_shared != 0):
+        raise ValueError("rows_to_cache needs a policy (caches), the fused gather and no shared experts")
+    # One native call for the whole layer: through the five separate ones the host took 43 us for a layer whose kernels
+    # take 25 (64 x 256, 64 tokens).  Rows T.. of the buffers stay untouched, so a pointer to their start is enough.
+    st, f32, i32 = ctx.torch_dtype, torch.float32, torch.int32
+    args = MoeLayerArgs(
+        _ptr(x, st), _ptr(Wg, st), _ptr(bg, f32), _ptr(W1, st), _ptr(b1, f32), _ptr(W2, st), _ptr(b2, f32),
+        _ptr(buf.scores, f32), _ptr(buf.expert_idx, i32), _ptr(buf.probs, f32), _ptr(buf.logits, f32),
+        _ptr(buf.mask, torch.uint8) if cached else None, _ptr(buf.n_refresh, i32) if cached else None,
+        None if fuse_gather else _ptr(buf.x_packed, st), None if rows_to_cache else _ptr(buf.h_packed, st),
+        _ptr(buf.counts, i32), _ptr(buf.offsets, i32), _ptr(buf.perm, i32), _ptr(buf.inv, i32), _ptr(buf.seg_expert, i32),
+        _ptr(buf.H_cache, st) if cached else None, _ptr(buf.S_cache, f32) if cached else None, _ptr(buf.y, st),
+        _ptr(buf.workspace), T, buf.seg_expert.shape[0], 0 if max_rows is None else max_rows, int(max_rows is None),
+        int(fuse_gather), int(rows_to_cache))
+    ctx._check(lib().moe_layer_forward(ctx._h, ctypes.byref(args), ctypes.byref(policy.c()) if cached else None, _stream()))
     return buf.y[:T]
 
 

@@ -405,6 +405,43 @@ int moe_combine(moe_ctx* ctx, const void* h_packed, const int32_t* inv, const fl
                       "moe_combine");
 }
 
+int moe_layer_forward(moe_ctx* ctx, const moe_layer_args* a, const moe_policy* policy, void* stream)
+{
+    if (!ctx) return MOE_ERR_NULL;
+    if (!a) return fail(ctx, MOE_ERR_NULL, "moe_layer_forward: args is null");
+    int32_t rows = a->max_rows;
+    if (a->imply_rows) {
+        if (int rc = check_T(ctx, a->T)) return rc;
+        rows = a->T * slots(ctx);
+        if (policy)
+            if (int rc = moe_policy_refreshed_pairs(ctx, policy, a->T, &rows, nullptr)) return rc;
+    }
+    if (int rc = moe_gate(ctx, a->x, a->Wg, a->bg, a->T, a->scores, a->expert_idx, a->probs_all, a->logits, stream)) return rc;
+    const uint8_t* mask = nullptr;
+    if (policy) {
+        if (int rc = moe_conditional_refresh(ctx, a->scores, a->expert_idx, a->T, policy, a->mask, a->n_refresh, a->workspace, stream))
+            return rc;
+        mask = a->mask;
+    }
+    const bool to_cache = a->rows_to_cache != 0, fuse = a->fuse_gather != 0;
+    if (int rc = moe_dispatch(ctx, a->x, a->expert_idx, mask, a->T, fuse ? nullptr : a->x_packed, a->counts, a->offsets, a->perm,
+                              a->inv, a->workspace, stream))
+        return rc;
+    int rc;
+    if (to_cache)
+        rc = moe_expert_ffn_commit(ctx, a->x, a->perm, a->perm, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2,
+                                   a->b2, nullptr, mask, a->T, a->H_cache, nullptr, a->workspace, stream);
+    else if (fuse)
+        rc = moe_expert_ffn_rows(ctx, a->x, a->perm, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2, a->b2,
+                                 a->h_packed, a->workspace, stream);
+    else
+        rc = moe_expert_ffn(ctx, a->x_packed, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2, a->b2,
+                            a->h_packed, a->workspace, stream);
+    if (rc) return rc;
+    return moe_combine(ctx, to_cache ? nullptr : a->h_packed, a->inv, a->scores, mask, a->T, policy ? a->H_cache : nullptr,
+                       policy ? a->S_cache : nullptr, policy ? policy->use_fresh_scores : 0, a->y, stream);
+}
+
 int moe_ep_segments(moe_ctx* ctx, const int32_t* recv_counts, int32_t W, int32_t E_loc, int32_t* seg_offsets,
                     int32_t* seg_expert, void* stream)
 {
