@@ -12,7 +12,7 @@
 //     has done that once for all of them), scans the totals into the experts' offsets,
 //     ranks its own pairs (lanes that hold the same expert find each other with one ballot per bit
 //     of the expert id; per-wave, per-expert running counts in LDS), and writes perm / inv.
-//     With a single workgroup the table is not needed and the count kernel is not launched.
+//     Up to 8192 pairs one workgroup of 1024 threads places them all: no table and no count launch.
 // All integer work; the only atomics are integer adds in LDS: the result is unique.
 //
 // dispatch_gather_kernel: one wavefront per token reads the row once (16 bytes per lane per
@@ -27,6 +27,10 @@ namespace dicemoe {
 
 constexpr int kIdxThreads = 256;
 constexpr int kIdxWaves = kIdxThreads / kWave;
+// Pairs that one workgroup sorts alone.  At 8192 its eight steps take 9.3 us, the two launches 5.0 + 6.1 and the gap between
+// them; at 4096 four steps take 5.1 against 4.6 + 4.7; twice as many steps would no longer gain.  (Up to 256 pairs four
+// wavefronts do it: fewer to wait for at the barriers, 2.3 us.)
+constexpr int kAlonePairs = 8192;
 
 // order this wavefront's LDS accesses: reads before the point complete before writes after it
 // are issued, and the compiler keeps them on their side
@@ -137,8 +141,8 @@ __global__ __launch_bounds__(1024) void dispatch_scan_kernel(int32_t* __restrict
     }
 }
 
-template <int S>
-__global__ __launch_bounds__(kIdxThreads) void dispatch_place_kernel(const int32_t* __restrict__ expert_idx,
+template <int S, int THREADS>
+__global__ __launch_bounds__(THREADS) void dispatch_place_kernel(const int32_t* __restrict__ expert_idx,
                                                                     const uint8_t* __restrict__ mask, int N, int E,
                                                                     const int32_t* __restrict__ block_counts,
                                                                     int prefix_ready, int32_t* __restrict__ counts,
@@ -146,7 +150,8 @@ __global__ __launch_bounds__(kIdxThreads) void dispatch_place_kernel(const int32
                                                                     int32_t* __restrict__ perm,
                                                                     int32_t* __restrict__ inv)
 {
-    __shared__ int wave_run[kIdxWaves][kMaxExperts];   // running count of a wave's pairs per expert; at the end its total
+    constexpr int WAVES = THREADS / kWave;
+    __shared__ int wave_run[WAVES][kMaxExperts];       // running count of a wave's pairs per expert; then the pairs of the waves before it
     __shared__ int s_tot[kMaxExperts];                 // pairs per expert over all workgroups
     __shared__ int s_pre[kMaxExperts];                 // pairs per expert in the workgroups before this one
     __shared__ int s_off[kMaxExperts + 1];
@@ -156,7 +161,7 @@ __global__ __launch_bounds__(kIdxThreads) void dispatch_place_kernel(const int32
     const int b = blockIdx.x;
     const int n_blocks = gridDim.x;
     const int nbits = E > 1 ? 32 - __builtin_clz(static_cast<unsigned>(E - 1)) : 0;
-    wave_run[tid / kMaxExperts][tid % kMaxExperts] = 0;   // 256 threads cover the 4 x 64 table
+    wave_run[tid / kMaxExperts][tid % kMaxExperts] = 0;   // the threads cover the WAVES x 64 table
     if (tid < kMaxExperts) { s_tot[tid] = 0; s_pre[tid] = 0; }
     __syncthreads();
 
@@ -169,7 +174,7 @@ __global__ __launch_bounds__(kIdxThreads) void dispatch_place_kernel(const int32
             s_tot[tid] = block_counts[static_cast<size_t>(n_blocks) * E + tid];
         }
     } else if (n_blocks > 1) {
-        for (int i = tid; i < n_blocks * E; i += kIdxThreads) {
+        for (int i = tid; i < n_blocks * E; i += THREADS) {
             const int c = block_counts[i];
             const int bb = i / E, e = i - bb * E;
             if (c != 0) {
@@ -180,7 +185,7 @@ __global__ __launch_bounds__(kIdxThreads) void dispatch_place_kernel(const int32
     }
 
     // rank of each of this wave's pairs among the wave's pairs of the same expert
-    const int p0 = (b * kIdxWaves + wave) * kWave * S;
+    const int p0 = (b * WAVES + wave) * kWave * S;
     int ev[S], rank[S];
     if (p0 < N) {                                           // wave-uniform
         load_steps<S>(expert_idx, mask, p0, lane, N, E, ev);
@@ -201,11 +206,13 @@ __global__ __launch_bounds__(kIdxThreads) void dispatch_place_kernel(const int32
         for (int u = 0; u < S; ++u) { ev[u] = -1; rank[u] = 0; }
     }
     __syncthreads();
-    if (n_blocks == 1 && tid < E) {
-        int t = 0;
+    if (tid < E) {
+        int cnt[WAVES], t = 0;
 #pragma unroll
-        for (int w = 0; w < kIdxWaves; ++w) t += wave_run[w][tid];
-        s_tot[tid] = t;
+        for (int w = 0; w < WAVES; ++w) cnt[w] = wave_run[w][tid];
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) { wave_run[w][tid] = t; t += cnt[w]; }
+        if (n_blocks == 1) s_tot[tid] = t;
     }
     __syncthreads();
     // exclusive scan over the experts: lane e of the first wave holds expert e's total
@@ -236,9 +243,7 @@ __global__ __launch_bounds__(kIdxThreads) void dispatch_place_kernel(const int32
             const int e = ev[u];
             int r = -1;
             if (e >= 0) {
-                int base = s_off[e] + s_pre[e];
-                for (int w = 0; w < wave; ++w) base += wave_run[w][e];
-                r = base + rank[u];
+                r = s_off[e] + s_pre[e] + wave_run[wave][e] + rank[u];
                 perm[r] = p;
             }
             if (p < N) {
@@ -315,9 +320,9 @@ __global__ __launch_bounds__(256) void dispatch_gather_kernel(const T* __restric
     }
 }
 
-// Steps per wave and workgroups of the index kernels for N pairs.  Up to 2048 pairs one workgroup
-// sorts alone (one launch); beyond, the fewest steps (1, 2, 4, 8) that keep the grid at 256 workgroups
-// or fewer; beyond 2^19 pairs the grid grows instead.
+// Steps per wave and workgroups of the index kernels for N pairs, and with them the scratch that moe_dispatch asks for (nothing
+// up to 2048 pairs).  The fewest steps (1, 2, 4, 8) that keep the grid at 256 workgroups or fewer; beyond 2^19 pairs the grid
+// grows instead.
 static void dispatch_plan(long long N, int& steps, int& blocks)
 {
     steps = 1;
@@ -347,8 +352,17 @@ static void launch_dispatch_index(const int32_t* idx, const uint8_t* mask, int N
         hipLaunchKernelGGL(dispatch_count_kernel<S>, dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch);
     if (scan)
         hipLaunchKernelGGL(dispatch_scan_kernel, dim3(1), dim3(1024), 0, stream, scratch, blocks, E);
-    hipLaunchKernelGGL(dispatch_place_kernel<S>, dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch,
+    hipLaunchKernelGGL((dispatch_place_kernel<S, kIdxThreads>), dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch,
                        scan, counts, offsets, perm, inv);
+}
+
+// One workgroup for all pairs, no counting launch and no table
+template <int S, int THREADS>
+static void launch_dispatch_alone(const int32_t* idx, const uint8_t* mask, int N, int E, int32_t* counts, int32_t* offsets,
+                                  int32_t* perm, int32_t* inv, hipStream_t stream)
+{
+    hipLaunchKernelGGL((dispatch_place_kernel<S, THREADS>), dim3(1), dim3(THREADS), 0, stream, idx, mask, N, E,
+                       static_cast<const int32_t*>(nullptr), 0, counts, offsets, perm, inv);
 }
 
 hipError_t launch_dispatch(bool bf16, const void* x, const int32_t* idx, const uint8_t* mask, int T_tok, int d,
@@ -359,7 +373,12 @@ hipError_t launch_dispatch(bool bf16, const void* x, const int32_t* idx, const u
     int steps, blocks;
     dispatch_plan(N, steps, blocks);
     if (blocks > 1 && scratch == nullptr) return hipErrorInvalidValue;
-    switch (steps) {
+    if (N <= kIdxThreads) launch_dispatch_alone<1, kIdxThreads>(idx, mask, N, E, counts, offsets, perm, inv, stream);
+    else if (N <= 1024) launch_dispatch_alone<1, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
+    else if (N <= 2048) launch_dispatch_alone<2, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
+    else if (N <= 4096) launch_dispatch_alone<4, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
+    else if (N <= kAlonePairs) launch_dispatch_alone<8, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
+    else switch (steps) {
     case 1: launch_dispatch_index<1>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
     case 2: launch_dispatch_index<2>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
     case 4: launch_dispatch_index<4>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
@@ -421,16 +440,26 @@ hipError_t dispatch_static_scratch(int32_t** out)
 __global__ void ep_segments_kernel(const int32_t* __restrict__ recv_counts, int n_seg, int E_loc,
                                    int32_t* __restrict__ seg_offsets, int32_t* __restrict__ seg_expert)
 {
-    // tiny table (at most 1024 entries): one thread walks it
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        int run = 0;
-        for (int g = 0; g < n_seg; ++g) {
-            seg_offsets[g] = run;
-            seg_expert[g] = g % E_loc;
-            run += recv_counts[g];
+    // tiny table (at most 1024 entries): one wavefront scans it 64 entries at a time.  (One thread walking it waited for
+    // memory entry by entry: 5.7 us for 16 segments.)
+    const int lane = lane_id();
+    int run = 0;
+    for (int g0 = 0; g0 < n_seg; g0 += kWave) {
+        const int g = g0 + lane;
+        const int mine = g < n_seg ? recv_counts[g] : 0;
+        int incl = mine;
+#pragma unroll
+        for (int sh = 1; sh < kWave; sh <<= 1) {
+            const int v = __shfl_up(incl, sh, kWave);
+            if (lane >= sh) incl += v;
         }
-        seg_offsets[n_seg] = run;
+        if (g < n_seg) {
+            seg_offsets[g] = run + incl - mine;
+            seg_expert[g] = g % E_loc;
+        }
+        run += __shfl(incl, kWave - 1, kWave);
     }
+    if (lane == 0) seg_offsets[n_seg] = run;
 }
 
 hipError_t launch_ep_segments(const int32_t* recv_counts, int n_seg, int E_loc, int32_t* seg_offsets,
