@@ -263,10 +263,11 @@ static hipError_t launch_gemm_bf16(const void* A, const void* W, const float* bi
 }
 
 // Tile shape for one bf16 grouped GEMM.  With at most 64 segments and enough tiles the persistent kernel of
-// ffn_stream.hpp, 192 or 256 columns, whichever its cost model expects to be faster.  The line: 96 tiles of 256 x 192 for the
-// first GEMM, 120 for the second (DiT-MoE-XL widths: at 2000 rows, 288 and 72 tiles, first GEMM 37 us against 39 on the
-// kernels below, second 45 against 43; at 4096 rows, 480 and 120 tiles, 58 against 66 and 57 against 58; at 512 rows, 192 tiles
-// that are mostly padding, first GEMM 28 us against 25).
+// ffn_stream.hpp, 192 or 256 columns, whichever its cost model expects to be faster.  The line for the first GEMM: 96 tiles
+// of 256 x 192 and 192 rows per expert.  For the second, more tiles of 256 x 192 than compute units: with one tile per
+// workgroup there is nothing to run on into, and the wide kernel starts sooner (kernel trace, DiT-MoE-XL widths: 8192 rows,
+// 240 tiles, 90 us against 94 - 98; 4096 rows, 120 tiles, 61 against 66; 16384 rows with two shared experts, 384
+// tiles, 160 against 145 on the persistent kernel).
 // Otherwise the wide kernel, a workgroup per tile, hand-scheduled wavefronts:
 //   256 x 192, one workgroup of eight wavefronts (4 x 2, each a 64 x 96 block; two per SIMD cover each
 //     other's waits, +1 % over four wavefronts of 128 x 96) per compute unit, two stages of activations
@@ -302,7 +303,7 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
     const bool fits_192 = (N + 191) / 192 * 192 * 8 <= N * 9;          // at most 1/8 of the columns computed in vain
     const bool fits_128 = (N + 127) / 128 * 128 * 8 <= N * 9;
     const bool full_rows = max_rows >= (GELU ? 192 : 128) * n_seg;     // (row tiles at least half full on average)
-    if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (GELU ? 96 : 116)) {
+    if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (GELU ? 96 : kComputeUnits + 1)) {
         const bool wide = !fits_192 || stream_cost(256, N, K, GELU, max_rows, n_seg) < stream_cost(192, N, K, GELU, max_rows, n_seg);
         if (wide) return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
         return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
