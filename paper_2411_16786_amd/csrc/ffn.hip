@@ -264,7 +264,7 @@ static hipError_t launch_gemm_bf16(const void* A, const void* W, const float* bi
 
 // Tile shape for one bf16 grouped GEMM.  With at most 64 segments and enough tiles the persistent kernel of
 // ffn_stream.hpp, 192 or 256 columns, whichever its cost model expects to be faster.  The line for the first GEMM: 96 tiles
-// of 256 x 192 and 192 rows per expert.  For the second, more tiles of 256 x 192 than compute units: with one tile per
+// of 256 x 192 and 128 rows per expert.  For the second, more tiles of 256 x 192 than compute units: with one tile per
 // workgroup there is nothing to run on into, and the wide kernel starts sooner (kernel trace, DiT-MoE-XL widths: 8192 rows,
 // 240 tiles, 90 us against 94 - 98; 4096 rows, 120 tiles, 61 against 66; 16384 rows with two shared experts, 384
 // tiles, 160 against 145 on the persistent kernel).
@@ -302,34 +302,38 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
     };
     const bool fits_192 = (N + 191) / 192 * 192 * 8 <= N * 9;          // at most 1/8 of the columns computed in vain
     const bool fits_128 = (N + 127) / 128 * 128 * 8 <= N * 9;
-    const bool full_rows = max_rows >= (GELU ? 192 : 128) * n_seg;     // (row tiles at least half full on average)
+    const bool full_rows = max_rows >= 128 * n_seg;                    // (row tiles half full on average)
     if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (GELU ? 96 : kComputeUnits + 1)) {
         const bool wide = !fits_192 || stream_cost(256, N, K, GELU, max_rows, n_seg) < stream_cost(192, N, K, GELU, max_rows, n_seg);
         if (wide) return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
         return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
     }
     // Few rows per expert, or few tiles altogether: 64 x 128 tiles, three stages in 72 KB of LDS, so that two workgroups share
-    // a compute unit and cover each other's waits, and a 64-row tile of a small expert is not half padding.  The second GEMM
-    // takes them while they are at most one per compute unit, then 128 x 128 tiles up to the same line; both have 1.5 to 3
-    // times as many workgroups streaming as the 128 x 192 tiles below, which the long reduction would need two or three shares
-    // of K for.  Second GEMM, change of the time of both GEMMs (64 x 128 / 128 x 128): DiT-MoE-XL widths, 1000 rows, 76 us:
-    // -20 / -14; 1400 rows, 66 us: -6 / 0; 1800 rows, 71 us: +5 / -4; 2000 rows, 77 us: +4 / -5; DiT-MoE-S widths, 2000 rows, 39 us:
-    // -12 / -9; 8192 rows, 45 us: -1 / -3; DiT-MoE-G widths, 256 rows, 207 us: -27 / -27; 1024 rows, 214 us: +10 / -11.
-    // First GEMM: up to 192 rows per expert (per cent of the two GEMMs: DiT-MoE-G widths, 256 rows, 11; expert-parallel widths, 1024 rows,
-    // 10; DiT-MoE-XL, 1400 rows, 4; DiT-MoE-S, 2000 rows, 6; -3 at 225 rows per expert of DiT-MoE-XL).
+    // a compute unit and cover each other's waits, and a 64-row tile of a small expert is not half padding.
+    // First GEMM (us, 128-row tiles / 64-row tiles, cold caches): up to 72 rows per expert, above that a second row tile
+    // reads the weights again: DiT-MoE-XL, 58 rows an expert 24 / 22.5, 68: 24.5 / 22.5, 75: 26 / 29.5, 88: 25.5 / 30;
+    // DiT-MoE-G, 16: 116 / 90, 64: 122 / 105; and up to 96 rows where the 128 x 192 tiles would take more than one round: DiT-MoE-G, 88:
+    // 121 / 116, 112: 123 / 129; expert-parallel widths, 88: 170 / 145.
+    // Second GEMM: while there is at most one tile per compute unit (128 x 192 tiles, K in two or three shares / 64-row tiles: DiT-MoE-XL,
+    // 900 rows 48 / 29.5, 1400 rows 42 / 34; DiT-MoE-S, 2000 rows 27 / 16; DiT-MoE-G, 256 rows 109 / 84); then 128 x 128 tiles
+    // up to seven eighths of that (a count beyond 256 is a second round: DiT-MoE-G, 1024 rows, 224 tiles 110 / 99; 1200 rows, 252 tiles
+    // 110 / 138), unless two shares of K on 128 x 192 tiles fill the chip (DiT-MoE-XL, 2000 rows: 45 split, 49 on 128 x 128).
     if (by_expert && fits_128 && K >= 256) {
-        const long long t64 = tiles(64, 128), t128 = tiles(128, 128);
-        if (GELU && (!full_rows || t64 <= 2 * kComputeUnits))
+        const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t192 = tiles(128, 192);
+        const bool small_experts = max_rows <= 72 * n_seg || (max_rows <= 96 * n_seg && t192 > kComputeUnits);
+        if (GELU && (small_experts || (full_rows && t64 <= 2 * kComputeUnits)))
             return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-        // two shares of K while both together are one workgroup per compute unit and sixteen steps long (DiT-MoE-XL
-        // widths: 128 rows 45 us unsplit, 42 split; 512 rows 48.0, 47.3; with twelve steps, DiT-MoE-S, the second pass costs more)
-        if (!GELU && partial && 2 * t64 <= kComputeUnits && K / 64 / 2 >= 16 && static_cast<size_t>(2) * max_rows * N * sizeof(float) <= partial_bytes) {
+        // two shares of K while both together leave an eighth of the compute units free and are sixteen steps long (DiT-MoE-XL
+        // widths, against 128 x 192 tiles in three shares: 128 rows 27.6 -> 24.0 us, 512 rows, 216 workgroups, 31.7 -> 28.7; 600 rows, 252, 33.4 -> 38.4
+        // in two shares; with twelve steps, DiT-MoE-S, the second pass costs more than it gains)
+        if (!GELU && partial && 16 * t64 <= 7 * kComputeUnits && K / 64 / 2 >= 16 && static_cast<size_t>(2) * max_rows * N * sizeof(float) <= partial_bytes) {
             hipError_t err = launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, nullptr, by_expert, partial, 2, status);
             return err != hipSuccess ? err : launch_splitk_reduce(partial, 2, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
         }
         if (!GELU && t64 <= kComputeUnits)
             return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-        if (!GELU && t128 <= kComputeUnits)
+        const bool splits = partial && fits_192 && t192 * 2 * 20 <= kComputeUnits * 21 && K / 64 / 2 >= 16;
+        if (!GELU && !splits && 8 * t128 <= 7 * kComputeUnits)
             return launch_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
     }
     // Few rows and a long reduction (the second GEMM after a small refresh fraction or for a small batch):

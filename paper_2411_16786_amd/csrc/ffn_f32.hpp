@@ -11,8 +11,9 @@
 //     lane, and three units are in flight per wavefront, sixteen wavefronts per compute unit.
 // Both GEMMs, graph of ten calls: DiT-MoE-S widths, 500 tokens top-2: 137 us on the vector units, 56 here; 100 tokens 127 ->
 // 28; 600 tokens top-3 144 -> 80; 2000 tokens 186 -> 162; 64 x 256, 4 experts, 64 tokens 28 -> 10.  Larger tiles (32 x 64, 64 x 64),
-// more wavefronts per tile and deeper rings were within 5 us of it at 500 tokens, slower at 100.  What is left is mostly the
-// vector caches: 32 x 32 tiles read 8 bytes per multiply-add row pair, 370 MB at 500 tokens.
+// more wavefronts per tile and deeper rings were within 5 us of it at 500 tokens, slower at 100.  What bounds it now was
+// not separated: 33 us and 28 us at 500 tokens (kernel trace) move 185 MB each into the compute units, 38 MB of them cold
+// weights; the matrix pipes need 8 us each.
 #pragma once
 #include "ffn_mfma.hpp"
 #include "ffn_stream.hpp"
