@@ -39,7 +39,7 @@ def kernel_sources_hash():
     """sha256 over the FFN kernel sources: ties a stored counter summary to the code it was taken on."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2411_16786_amd", "csrc")
-    for name in ("ffn.hip", "ffn_wide.hpp", "ffn_mfma.hpp"):
+    for name in ("ffn.hip", "ffn_stream.hpp", "ffn_wide.hpp", "ffn_mfma.hpp"):
         h.update(open(os.path.join(csrc, name), "rb").read())
     return h.hexdigest()[:16]
 
@@ -308,7 +308,7 @@ def main():
         elif stored is not None:
             traffic_note = (f"profiles/bench_xl28_hbm_traffic.txt was taken on kernel sources {stored_hash}, "
                             f"these are {kernel_sources_hash()}: not reported")
-    roofline = {"kernel": "ffn_gemm_bf16_wide_kernel (GEMM1 + GEMM2 of one moe_expert_ffn_rows call)", "bound": "mfma",
+    roofline = {"kernel": "ffn_gemm_bf16_stream_kernel + ffn_gemm_bf16_wide_kernel (GEMM1 + GEMM2 of one moe_expert_ffn_rows call)", "bound": "mfma",
                 "achieved": round(ffn_tflops, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(ffn_tflops / PEAK_BF16_TFLOPS, 4), "traffic": traffic, "traffic_note": traffic_note,
                 "timing": f"mean over {n_layers} calls (one per layer, cold weights) replayed as one HIP graph, HIP events",
