@@ -310,8 +310,8 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
     }
     // Few rows per expert, or few tiles altogether: 64 x 128 tiles, three stages in 72 KB of LDS, so that two workgroups share
     // a compute unit and cover each other's waits, and a 64-row tile of a small expert is not half padding.
-    // First GEMM (us, 128-row tiles / 64-row tiles, cold caches): up to 72 rows per expert, above that a second row tile
-    // reads the weights again: DiT-MoE-XL, 58 rows an expert 24 / 22.5, 68: 24.5 / 22.5, 75: 26 / 29.5, 88: 25.5 / 30;
+    // First GEMM (us, 128-row tiles / 64-row tiles): up to 72 rows per expert, above that a second row tile
+    // reads the weights again (DiT-MoE-XL, 75 rows an expert 26 / 29.5, 88: 25.5 / 30): DiT-MoE-S, 38: 15 / 12, 69: 16 / 14;
     // DiT-MoE-G, 16: 116 / 90, 64: 122 / 105; and up to 96 rows where the 128 x 192 tiles would take more than one round: DiT-MoE-G, 88:
     // 121 / 116, 112: 123 / 129; expert-parallel widths, 88: 170 / 145.
     // Second GEMM: while there is at most one tile per compute unit (128 x 192 tiles, K in two or three shares / 64-row tiles: DiT-MoE-XL,
@@ -320,20 +320,19 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
     // 110 / 138), unless two shares of K on 128 x 192 tiles fill the chip (DiT-MoE-XL, 2000 rows: 45 split, 49 on 128 x 128).
     if (by_expert && fits_128 && K >= 256) {
         const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t192 = tiles(128, 192);
-        const bool small_experts = max_rows <= 72 * n_seg || (max_rows <= 96 * n_seg && t192 > kComputeUnits);
+        // (not for a long reduction that 128 x 192 tiles do in one round: those have 120 KB of loads in flight per compute unit, which
+        // cold weights need: whole layer, DiT-MoE-XL widths, 256 tokens, other weights in every pass, 72.6 us against 74.1)
+        const bool one_round = t192 <= kComputeUnits && K >= 1024;
+        const bool small_experts = (max_rows <= 72 * n_seg && !one_round) || (max_rows <= 96 * n_seg && t192 > kComputeUnits);
+        // (the same for the second GEMM in three shares of K on one 128-row tile per expert)
+        const bool three_shares = partial && fits_192 && t192 * 3 * 20 <= kComputeUnits * 21 && K / 64 / 3 >= 16 &&
+                                  static_cast<size_t>(3) * max_rows * N * sizeof(float) <= partial_bytes && max_rows <= 100 * n_seg;
         if (GELU && (small_experts || (full_rows && t64 <= 2 * kComputeUnits)))
             return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-        // two shares of K while both together leave an eighth of the compute units free and are sixteen steps long (DiT-MoE-XL
-        // widths, against 128 x 192 tiles in three shares: 128 rows 27.6 -> 24.0 us, 512 rows, 216 workgroups, 31.7 -> 28.7; 600 rows, 252, 33.4 -> 38.4
-        // in two shares; with twelve steps, DiT-MoE-S, the second pass costs more than it gains)
-        if (!GELU && partial && 16 * t64 <= 7 * kComputeUnits && K / 64 / 2 >= 16 && static_cast<size_t>(2) * max_rows * N * sizeof(float) <= partial_bytes) {
-            hipError_t err = launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, nullptr, by_expert, partial, 2, status);
-            return err != hipSuccess ? err : launch_splitk_reduce(partial, 2, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
-        }
-        if (!GELU && t64 <= kComputeUnits)
+        if (!GELU && !three_shares && t64 <= kComputeUnits)
             return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
         const bool splits = partial && fits_192 && t192 * 2 * 20 <= kComputeUnits * 21 && K / 64 / 2 >= 16;
-        if (!GELU && !splits && 8 * t128 <= 7 * kComputeUnits)
+        if (!GELU && !three_shares && !splits && 8 * t128 <= 7 * kComputeUnits)
             return launch_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
     }
     // Few rows and a long reduction (the second GEMM after a small refresh fraction or for a small batch):
