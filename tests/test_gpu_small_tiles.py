@@ -1,5 +1,5 @@
 """The kernels for few rows, narrow outputs and float storage where their tiles and shares can go wrong: the 64- and 128-row
-tiles of the expert FFN at their edges (whole, split reduction, the shortest reduction their rings take, columns that do not
+tiles of the expert FFN at their edges (the shortest reduction their rings take, a split one, columns that do not
 fill the last tile), the float GEMM's shared reduction with fewer units than wavefronts and with more segments than a wavefront
 has lanes, the float router over remainders of its k-steps and experts, and the one-workgroup dispatch at each size where it
 takes another number of steps.
@@ -23,9 +23,10 @@ FFN_CASES = [
     ("64-row-tiles", [63, 0, 64, 65, 1, 128, 129, 40], 320, 384, "bf16"),          # both GEMMs on 64 x 128 tiles
     ("four-steps", [10, 64, 70, 3], 256, 256, "bf16"),                             # the shortest ring of three stages
     ("half-last-column-tile", [100, 31, 65, 0], 576, 1088, "bf16"),                # N % 128 == 64 in both GEMMs
-    ("two-shares-of-k", [64, 127, 1, 30], 256, 2048, "bf16"),                      # second GEMM: 16 steps a share
-    ("two-ragged-shares", [64, 65, 0, 17], 256, 2112, "bf16"),                     # ... 16 and 17 steps
-    ("128-row-tiles", [127, 128, 129, 700, 1, 0, 516, 900], 256, 2048 * 3, "bf16"),
+    ("long-reduction", [64, 127, 1, 30], 256, 2048, "bf16"),
+    ("odd-steps", [64, 65, 0, 17], 256, 2112, "bf16"),                             # 33 steps of a three-stage ring
+    ("128-row-tiles", [127, 128, 129, 700, 1, 0, 416, 400], 1088, 1536, "bf16"),   # second GEMM on 128 x 128, ragged columns
+    ("three-shares-of-k", [64, 100, 0, 70], 1152, 4608, "bf16"),                   # second GEMM: 24 steps a share on 128 x 192
     ("first-gemm-many-rows", [500, 400], 256, 384, "bf16"),                        # full row tiles, few of them
     ("f32-one-unit", [5, 33, 0, 32], 16, 16, "f32"),                               # K = 16: three of four shares are empty
     ("f32-five-units", [31, 32, 33, 64], 80, 48, "f32"),
