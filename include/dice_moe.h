@@ -292,11 +292,12 @@ int moe_combine(moe_ctx* ctx, const void* h_packed, const int32_t* inv, const fl
 
 /* One whole layer: moe_gate, then (policy not NULL) moe_conditional_refresh, moe_dispatch, the expert FFN and
  * moe_combine, with the arguments those calls take, enqueued by one call (a caller in an interpreted language pays its call
- * overhead once).  Stops at the first part that fails and returns its status.
+ * overhead once).  The arguments of all parts are checked before the first launch, with the statuses of the parts: a refused
+ * call writes nothing.
  *   fuse_gather   : dispatch writes indices only and the FFN reads the token rows through perm
  *                   (moe_expert_ffn_rows); 0: x_packed is materialised (moe_expert_ffn)
  *   rows_to_cache : with a policy, fuse_gather and no shared experts: the FFN scatters the refreshed rows into H_cache
- *                   (moe_expert_ffn_commit without scores) and the combine reads every row from there
+ *                   (moe_expert_ffn_commit without scores) and the combine reads every row from there.  MOE_ERR_NULL otherwise
  *   max_rows      : bound on the refreshed pairs; with imply_rows it is not read and the bound is the count that the policy
  *                   implies (T*slots without one)
  * Without a policy mask, n_refresh, H_cache and S_cache are not used. */

@@ -93,6 +93,72 @@ int policy_routed_pairs(moe_ctx* ctx, const moe_policy* policy, int32_t T, int32
     }
 }
 
+// Argument checks of the entry points, one function each, so that the call of a whole layer runs all of them before its first launch.
+
+int check_gate(moe_ctx* ctx, const void* x, const void* Wg, int32_t T, const float* scores, const int32_t* expert_idx)
+{
+    if (int rc = check_T(ctx, T)) return rc;
+    if (!x || !Wg || !scores || !expert_idx) return fail(ctx, MOE_ERR_NULL, "moe_gate: null pointer");
+    return MOE_OK;
+}
+
+// routed: what policy_routed_pairs counts
+int check_refresh(moe_ctx* ctx, const float* scores, int32_t T, const moe_policy* policy, const uint8_t* mask,
+                  const int32_t* n_refresh, int32_t* routed)
+{
+    if (int rc = check_T(ctx, T)) return rc;
+    if (!policy || !mask || !n_refresh) return fail(ctx, MOE_ERR_NULL, "moe_conditional_refresh: null pointer");
+    if (int rc = policy_routed_pairs(ctx, policy, T, routed)) return rc;
+    if (!scores && (policy->kind == MOE_REFRESH_FRACTION_TOKEN || policy->kind == MOE_REFRESH_FRACTION_PAIR))
+        return fail(ctx, MOE_ERR_NULL, "moe_conditional_refresh: scores is null");
+    return MOE_OK;
+}
+
+int check_dispatch(moe_ctx* ctx, const void* x, const int32_t* expert_idx, int32_t T, const void* x_packed, const int32_t* counts,
+                   const int32_t* offsets, const int32_t* perm, const int32_t* inv, const void* workspace)
+{
+    if (int rc = check_T(ctx, T)) return rc;
+    if (!expert_idx || !counts || !offsets || !perm || !inv || (x_packed && !x))
+        return fail(ctx, MOE_ERR_NULL, "moe_dispatch: null pointer");
+    // the per-workgroup counts travel from the counting launch to the placing launch at the start of the workspace
+    if (!workspace && dicemoe::dispatch_scratch_bytes(static_cast<long long>(T) * slots(ctx), experts(ctx)) > 0)
+        return fail(ctx, MOE_ERR_WORKSPACE, "moe_dispatch: workspace is null");
+    return MOE_OK;
+}
+
+int check_ffn(moe_ctx* ctx, const char* who, const void* x_rows, const int32_t* seg_offsets, const int32_t* seg_expert,
+              int32_t n_segments, int32_t max_rows, const void* W1, const void* W2, const void* out, const void* workspace)
+{
+    const long long bound = static_cast<long long>(ctx->shape.T_max) * slots(ctx);
+    if (n_segments < 1 || n_segments > 1024)
+        return fail(ctx, MOE_ERR_SHAPE, "n_segments=%ld outside 1..1024", n_segments);
+    if (max_rows < 0 || max_rows > bound)
+        return fail(ctx, MOE_ERR_SHAPE, "max_rows=%ld outside 0..T_max*slots=%ld", max_rows, static_cast<long>(bound));
+    if (!x_rows || !seg_offsets || !seg_expert || !W1 || !W2 || !out) {
+        std::snprintf(ctx->err, sizeof(ctx->err), "%s: null pointer", who);
+        return MOE_ERR_NULL;
+    }
+    if (!workspace) {
+        std::snprintf(ctx->err, sizeof(ctx->err), "%s: workspace is null", who);
+        return MOE_ERR_WORKSPACE;
+    }
+    return MOE_OK;
+}
+
+int check_combine(moe_ctx* ctx, const void* h_packed, const int32_t* inv, const float* scores, const uint8_t* mask, int32_t T,
+                  const void* H_cache, const float* S_cache, const void* y)
+{
+    if (int rc = check_T(ctx, T)) return rc;
+    if (!inv || !scores || !y) return fail(ctx, MOE_ERR_NULL, "moe_combine: null pointer");
+    if (!h_packed && (!H_cache || ctx->shape.n_shared != 0))
+        return fail(ctx, MOE_ERR_NULL, "moe_combine: h_packed may be null only with a cache and without shared experts");
+    if (mask && (!H_cache || !S_cache))
+        return fail(ctx, MOE_ERR_CACHE_COLD, "moe_combine: a refresh mask was given without a cache");
+    if ((H_cache == nullptr) != (S_cache == nullptr))
+        return fail(ctx, MOE_ERR_NULL, "moe_combine: H_cache and S_cache must be given together");
+    return MOE_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -156,8 +222,7 @@ int moe_gate(moe_ctx* ctx, const void* x, const void* Wg, const float* bg, int32
              int32_t* expert_idx, float* probs_all, float* logits, void* stream)
 {
     if (!ctx) return MOE_ERR_NULL;
-    if (int rc = check_T(ctx, T)) return rc;
-    if (!x || !Wg || !scores || !expert_idx) return fail(ctx, MOE_ERR_NULL, "moe_gate: null pointer");
+    if (int rc = check_gate(ctx, x, Wg, T, scores, expert_idx)) return rc;
     if (T == 0) return MOE_OK;
     const moe_shape& s = ctx->shape;
     return hip_result(ctx,
@@ -186,10 +251,8 @@ int moe_conditional_refresh(moe_ctx* ctx, const float* scores, const int32_t* ex
     (void)expert_idx;      // no current policy reads the expert ids or needs scratch (see the header)
     (void)workspace;
     if (!ctx) return MOE_ERR_NULL;
-    if (int rc = check_T(ctx, T)) return rc;
-    if (!policy || !mask || !n_refresh) return fail(ctx, MOE_ERR_NULL, "moe_conditional_refresh: null pointer");
     int32_t routed = 0;
-    if (int rc = policy_routed_pairs(ctx, policy, T, &routed)) return rc;
+    if (int rc = check_refresh(ctx, scores, T, policy, mask, n_refresh, &routed)) return rc;
     const moe_shape& s = ctx->shape;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int n_value = routed + T * s.n_shared;       // what the device-side n_refresh receives
@@ -208,13 +271,11 @@ int moe_conditional_refresh(moe_ctx* ctx, const float* scores, const int32_t* ex
                                                 static_cast<uint32_t>(policy->n_units), n_value, mask, n_refresh, st),
                           "moe_conditional_refresh");
     case MOE_REFRESH_FRACTION_TOKEN:
-        if (!scores) return fail(ctx, MOE_ERR_NULL, "moe_conditional_refresh: scores is null");
         return hip_result(ctx,
                           launch_refresh_select(scores, T, s.k, s.n_shared, 0, policy->n_units, true, n_value, mask,
                                                 n_refresh, st),
                           "moe_conditional_refresh");
     default: {      // MOE_REFRESH_FRACTION_PAIR (policy_routed_pairs has rejected every other kind)
-        if (!scores) return fail(ctx, MOE_ERR_NULL, "moe_conditional_refresh: scores is null");
         if (policy->n_units == N)
             return hip_result(ctx, launch_refresh_simple(MOE_REFRESH_ALL, T, s.k, s.n_shared, 0, 0u, n_value, mask, n_refresh, st),
                               "moe_conditional_refresh");
@@ -233,13 +294,8 @@ int moe_dispatch(moe_ctx* ctx, const void* x, const int32_t* expert_idx, const u
                  void* stream)
 {
     if (!ctx) return MOE_ERR_NULL;
-    if (int rc = check_T(ctx, T)) return rc;
-    if (!expert_idx || !counts || !offsets || !perm || !inv || (x_packed && !x))
-        return fail(ctx, MOE_ERR_NULL, "moe_dispatch: null pointer");
+    if (int rc = check_dispatch(ctx, x, expert_idx, T, x_packed, counts, offsets, perm, inv, workspace)) return rc;
     const moe_shape& s = ctx->shape;
-    // the per-workgroup counts travel from the counting launch to the placing launch at the start of the workspace
-    if (!workspace && dicemoe::dispatch_scratch_bytes(static_cast<long long>(T) * slots(ctx), experts(ctx)) > 0)
-        return fail(ctx, MOE_ERR_WORKSPACE, "moe_dispatch: workspace is null");
     return hip_result(ctx,
                       launch_dispatch(is_bf16(ctx), x, expert_idx, mask, T, s.d, experts(ctx), slots(ctx), x_packed, counts, offsets,
                                       perm, inv, static_cast<int32_t*>(workspace), static_cast<hipStream_t>(stream)),
@@ -275,18 +331,7 @@ static int expert_ffn_common(moe_ctx* ctx, const char* who, const void* x_rows, 
                              void* h_packed, const int32_t* out_pairs, void* workspace, void* stream)
 {
     const moe_shape& s = ctx->shape;
-    if (n_segments < 1 || n_segments > 1024)
-        return fail(ctx, MOE_ERR_SHAPE, "n_segments=%ld outside 1..1024", n_segments);
-    if (max_rows < 0 || static_cast<long long>(max_rows) > static_cast<long long>(s.T_max) * slots(ctx))
-        return fail(ctx, MOE_ERR_SHAPE, "max_rows=%ld outside 0..T_max*slots=%ld", max_rows, static_cast<long>(s.T_max) * slots(ctx));
-    if (!x_rows || !seg_offsets || !seg_expert || !W1 || !W2 || !h_packed) {
-        std::snprintf(ctx->err, sizeof(ctx->err), "%s: null pointer", who);
-        return MOE_ERR_NULL;
-    }
-    if (!workspace) {
-        std::snprintf(ctx->err, sizeof(ctx->err), "%s: workspace is null", who);
-        return MOE_ERR_WORKSPACE;
-    }
+    if (int rc = check_ffn(ctx, who, x_rows, seg_offsets, seg_expert, n_segments, max_rows, W1, W2, h_packed, workspace)) return rc;
     // per-device kernel attributes, once per context and device (a context serves one host thread at a time)
     int device = 0;
     if (hipError_t err = hipGetDevice(&device); err != hipSuccess) return hip_result(ctx, err, who);
@@ -389,14 +434,7 @@ int moe_combine(moe_ctx* ctx, const void* h_packed, const int32_t* inv, const fl
                 int32_t T, void* H_cache, float* S_cache, int32_t use_fresh_scores, void* y, void* stream)
 {
     if (!ctx) return MOE_ERR_NULL;
-    if (int rc = check_T(ctx, T)) return rc;
-    if (!inv || !scores || !y) return fail(ctx, MOE_ERR_NULL, "moe_combine: null pointer");
-    if (!h_packed && (!H_cache || ctx->shape.n_shared != 0))
-        return fail(ctx, MOE_ERR_NULL, "moe_combine: h_packed may be null only with a cache and without shared experts");
-    if (mask && (!H_cache || !S_cache))
-        return fail(ctx, MOE_ERR_CACHE_COLD, "moe_combine: a refresh mask was given without a cache");
-    if ((H_cache == nullptr) != (S_cache == nullptr))
-        return fail(ctx, MOE_ERR_NULL, "moe_combine: H_cache and S_cache must be given together");
+    if (int rc = check_combine(ctx, h_packed, inv, scores, mask, T, H_cache, S_cache, y)) return rc;
     const moe_shape& s = ctx->shape;
     return hip_result(ctx,
                       launch_combine(is_bf16(ctx), h_packed, inv, scores, mask, T, s.d, slots(ctx), s.k, H_cache,
@@ -409,21 +447,31 @@ int moe_layer_forward(moe_ctx* ctx, const moe_layer_args* a, const moe_policy* p
 {
     if (!ctx) return MOE_ERR_NULL;
     if (!a) return fail(ctx, MOE_ERR_NULL, "moe_layer_forward: args is null");
-    int32_t rows = a->max_rows;
-    if (a->imply_rows) {
-        if (int rc = check_T(ctx, a->T)) return rc;
-        rows = a->T * slots(ctx);
-        if (policy)
-            if (int rc = moe_policy_refreshed_pairs(ctx, policy, a->T, &rows, nullptr)) return rc;
-    }
+    // everything that the host can see, before the first launch: a refused call writes nothing
+    const bool to_cache = a->rows_to_cache != 0, fuse = a->fuse_gather != 0;
+    if (int rc = check_gate(ctx, a->x, a->Wg, a->T, a->scores, a->expert_idx)) return rc;
+    int32_t routed = a->T * ctx->shape.k;
+    if (policy)
+        if (int rc = check_refresh(ctx, a->scores, a->T, policy, a->mask, a->n_refresh, &routed)) return rc;
+    const int32_t rows = a->imply_rows ? routed + a->T * ctx->shape.n_shared : a->max_rows;
+    if (to_cache && (!policy || !fuse || ctx->shape.n_shared != 0))
+        return fail(ctx, MOE_ERR_NULL, "moe_layer_forward: rows_to_cache needs a policy, fuse_gather and no shared experts");
+    if (!fuse && !a->x_packed) return fail(ctx, MOE_ERR_NULL, "moe_layer_forward: x_packed is null");
+    if (int rc = check_dispatch(ctx, a->x, a->expert_idx, a->T, a->x_packed, a->counts, a->offsets, a->perm, a->inv, a->workspace))
+        return rc;
+    const uint8_t* const mask = policy ? a->mask : nullptr;
+    void* const H_cache = policy ? a->H_cache : nullptr;
+    float* const S_cache = policy ? a->S_cache : nullptr;
+    void* const h_packed = to_cache ? nullptr : a->h_packed;
+    if (int rc = check_ffn(ctx, "moe_layer_forward", a->x, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->W2,
+                           to_cache ? H_cache : h_packed, a->workspace))
+        return rc;
+    if (int rc = check_combine(ctx, h_packed, a->inv, a->scores, mask, a->T, H_cache, S_cache, a->y)) return rc;
+
     if (int rc = moe_gate(ctx, a->x, a->Wg, a->bg, a->T, a->scores, a->expert_idx, a->probs_all, a->logits, stream)) return rc;
-    const uint8_t* mask = nullptr;
-    if (policy) {
+    if (policy)
         if (int rc = moe_conditional_refresh(ctx, a->scores, a->expert_idx, a->T, policy, a->mask, a->n_refresh, a->workspace, stream))
             return rc;
-        mask = a->mask;
-    }
-    const bool to_cache = a->rows_to_cache != 0, fuse = a->fuse_gather != 0;
     if (int rc = moe_dispatch(ctx, a->x, a->expert_idx, mask, a->T, fuse ? nullptr : a->x_packed, a->counts, a->offsets, a->perm,
                               a->inv, a->workspace, stream))
         return rc;
@@ -438,8 +486,8 @@ int moe_layer_forward(moe_ctx* ctx, const moe_layer_args* a, const moe_policy* p
         rc = moe_expert_ffn(ctx, a->x_packed, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2, a->b2,
                             a->h_packed, a->workspace, stream);
     if (rc) return rc;
-    return moe_combine(ctx, to_cache ? nullptr : a->h_packed, a->inv, a->scores, mask, a->T, policy ? a->H_cache : nullptr,
-                       policy ? a->S_cache : nullptr, policy ? policy->use_fresh_scores : 0, a->y, stream);
+    return moe_combine(ctx, h_packed, a->inv, a->scores, mask, a->T, H_cache, S_cache, policy ? policy->use_fresh_scores : 0, a->y,
+                       stream);
 }
 
 int moe_ep_segments(moe_ctx* ctx, const int32_t* recv_counts, int32_t W, int32_t E_loc, int32_t* seg_offsets,

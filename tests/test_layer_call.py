@@ -20,6 +20,52 @@ def test_layer_args_match_the_header():
     assert declared == bound
 
 
+def layer_args(**over):
+    """A call that passes every check, on dummy addresses: none of them is read on the paths below."""
+    a = B.MoeLayerArgs(*([16] * 24), T=8, n_segments=4, max_rows=0, imply_rows=1, fuse_gather=1, rows_to_cache=0)
+    for name, value in over.items():
+        setattr(a, name, value)
+    return a
+
+
+POLICY = (B.REFRESH_ALG4, 1, 2, 0, 0)
+REFUSED = [
+    # (arguments that differ, policy, shared experts, status)
+    ({"T": 65}, None, 0, B.MOE_ERR_SHAPE),
+    ({"T": -1}, None, 0, B.MOE_ERR_SHAPE),
+    ({"imply_rows": 0, "max_rows": -1}, None, 0, B.MOE_ERR_SHAPE),
+    ({"imply_rows": 0, "max_rows": 129}, None, 0, B.MOE_ERR_SHAPE),
+    ({"n_segments": 0}, None, 0, B.MOE_ERR_SHAPE),
+    ({"n_segments": 1025}, None, 0, B.MOE_ERR_SHAPE),
+    ({}, (B.REFRESH_ALG4, 1, 0, 0, 0), 0, B.MOE_ERR_POLICY),
+    ({"imply_rows": 0, "max_rows": 8}, (99, 0, 1, 0, 0), 0, B.MOE_ERR_POLICY),
+    ({"H_cache": None, "S_cache": None}, POLICY, 0, B.MOE_ERR_CACHE_COLD),
+    ({"S_cache": None, "rows_to_cache": 1}, POLICY, 0, B.MOE_ERR_CACHE_COLD),
+    ({"H_cache": None, "rows_to_cache": 1}, POLICY, 0, B.MOE_ERR_NULL),
+    # the FFN writes rows into the cache only with a policy, the fused gather and no shared experts
+    ({"rows_to_cache": 1}, None, 0, B.MOE_ERR_NULL),
+    ({"rows_to_cache": 1, "fuse_gather": 0}, POLICY, 0, B.MOE_ERR_NULL),
+    ({"rows_to_cache": 1}, POLICY, 2, B.MOE_ERR_NULL),
+    ({"workspace": None}, None, 0, B.MOE_ERR_WORKSPACE),
+    ({"h_packed": None}, None, 0, B.MOE_ERR_NULL),
+    ({"h_packed": None}, POLICY, 0, B.MOE_ERR_NULL),
+    ({"x_packed": None, "fuse_gather": 0}, None, 0, B.MOE_ERR_NULL),
+    ({"mask": None}, POLICY, 0, B.MOE_ERR_NULL),
+    ({"n_refresh": None}, POLICY, 0, B.MOE_ERR_NULL),
+] + [({name: None}, None, 0, B.MOE_ERR_NULL) for name in ("x", "Wg", "W1", "W2", "scores", "expert_idx", "counts", "offsets", "perm",
+                                                          "inv", "seg_expert", "y")]
+
+
+@pytest.mark.parametrize("case", range(len(REFUSED)))
+def test_refused_before_the_first_launch(case):
+    """Host-visible errors of any part come back before the first part is launched (without a GPU, a launch would be MOE_ERR_HIP)."""
+    over, policy, n_shared, status = REFUSED[case]
+    ctx = B.Context(T_max=64, d=64, F=256, E=4, k=2, dtype="f32", n_shared=n_shared)
+    pol = None if policy is None else B.ctypes.byref(B.MoePolicy(*policy))
+    assert B.lib().moe_layer_forward(ctx._h, B.ctypes.byref(layer_args(**over)), pol, None) == status
+    assert B.lib().moe_last_error(ctx._h) != b""
+
+
 FORMS = [
     # (policy, n_shared, keywords)
     (None, 0, {}),
@@ -100,3 +146,28 @@ def test_one_call_refuses_what_the_separate_ones_refuse():
     with pytest.raises(ValueError):
         B.moe_layer_forward(ctx, buf, dev[0].t(), *dev[1:])
     torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n_shared,over,status", [(2, {}, B.MOE_ERR_NULL), (0, {"imply_rows": 0, "max_rows": -1}, B.MOE_ERR_SHAPE),
+                                                  (0, {"S_cache": None}, B.MOE_ERR_CACHE_COLD)])
+def test_a_refused_call_writes_nothing(n_shared, over, status):
+    T, d, F, E, k = 16, 64, 64, 4, 2
+    x, Wg, bg, *_ = G.small_inputs(84, T, d, E, F, "f32")
+    *_, W1, b1, W2, b2 = G.small_inputs(85, T, d, E + n_shared, F, "f32")
+    ctx = B.Context(T, d, F, E, k, "f32", n_shared=n_shared)
+    dev = {"x": G.to_dev(x, "f32"), "Wg": G.to_dev(Wg, "f32"), "W1": G.to_dev(W1, "f32"), "W2": G.to_dev(W2, "f32")}
+    buf = B.LayerBuffers(ctx, G.DEV, with_cache=True)
+    dev |= {n: getattr(buf, n) for n in ("scores", "expert_idx", "mask", "n_refresh", "h_packed", "counts", "offsets", "perm", "inv",
+                                         "seg_expert", "H_cache", "S_cache", "y", "workspace")}
+    outputs = ("scores", "expert_idx", "mask", "n_refresh", "h_packed", "counts", "offsets", "perm", "inv", "H_cache", "S_cache", "y")
+    for name in outputs:
+        dev[name].fill_(7)
+    a = B.MoeLayerArgs(**{n: t.data_ptr() for n, t in dev.items()}, T=T, n_segments=ctx.experts, imply_rows=1, fuse_gather=1, rows_to_cache=1)
+    for name, value in over.items():
+        setattr(a, name, value)
+    pol = B.MoePolicy(*POLICY)
+    assert B.lib().moe_layer_forward(ctx._h, B.ctypes.byref(a), B.ctypes.byref(pol), None) == status
+    torch.cuda.synchronize()
+    for name in outputs:
+        assert (dev[name] == 7).all(), name
