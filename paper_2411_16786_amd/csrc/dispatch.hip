@@ -12,7 +12,7 @@
 //     has done that once for all of them), scans the totals into the experts' offsets,
 //     ranks its own pairs (lanes that hold the same expert find each other with one ballot per bit
 //     of the expert id; per-wave, per-expert running counts in LDS), and writes perm / inv.
-//     Up to 8192 pairs one workgroup of 1024 threads places them all: no table and no count launch.
+//     Up to 4096 pairs one workgroup of 1024 threads places them all: no table and no count launch.
 // All integer work; the only atomics are integer adds in LDS: the result is unique.
 //
 // dispatch_gather_kernel: one wavefront per token reads the row once (16 bytes per lane per
@@ -27,10 +27,11 @@ namespace dicemoe {
 
 constexpr int kIdxThreads = 256;
 constexpr int kIdxWaves = kIdxThreads / kWave;
-// Pairs that one workgroup sorts alone.  At 8192 its eight steps take 9.3 us, the two launches 5.0 + 6.1 and the gap between
-// them; at 4096 four steps take 5.1 against 4.6 + 4.7; twice as many steps would no longer gain.  (Up to 256 pairs four
-// wavefronts do it: fewer to wait for at the barriers, 2.3 us.)
-constexpr int kAlonePairs = 8192;
+// Pairs that one workgroup sorts alone.  One call of 28 in a graph, us, alone / counting and placing over many workgroups: 8 experts,
+// 2049 pairs 3.8 / 4.8, 4096: 4.7 / 4.9, 4097: 5.5 / 4.9, 8192: 7.4 / 5.0; 64 experts, 4096: 5.6 / 6.2, 4097: 6.6 / 6.6, 8192: 9.1 / 7.7.
+// (Durations of a kernel trace mislead here: about 2 us of each are a launch's own, which in a row of launches overlap.)  Up to 256
+// pairs four wavefronts do it: fewer to wait for at the barriers.
+constexpr int kAlonePairs = 4096;
 
 // order this wavefront's LDS accesses: reads before the point complete before writes after it
 // are issued, and the compiler keeps them on their side
@@ -376,8 +377,7 @@ hipError_t launch_dispatch(bool bf16, const void* x, const int32_t* idx, const u
     if (N <= kIdxThreads) launch_dispatch_alone<1, kIdxThreads>(idx, mask, N, E, counts, offsets, perm, inv, stream);
     else if (N <= 1024) launch_dispatch_alone<1, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
     else if (N <= 2048) launch_dispatch_alone<2, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
-    else if (N <= 4096) launch_dispatch_alone<4, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
-    else if (N <= kAlonePairs) launch_dispatch_alone<8, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
+    else if (N <= kAlonePairs) launch_dispatch_alone<4, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
     else switch (steps) {
     case 1: launch_dispatch_index<1>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
     case 2: launch_dispatch_index<2>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;

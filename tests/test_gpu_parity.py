@@ -169,8 +169,8 @@ def test_refresh_mask_bit_exact(T, k):
     (8192, 8, 2, 1152, "bf16", True),
     (17, 3, 3, 64, "f32", True),
     (1, 4, 2, 64, "bf16", False),
-    # pair counts that take each launch shape of the index kernels: one workgroup with 1, 2, 4, 8 steps per
-    # wave (up to 2048 pairs), then count + place over several workgroups with 1, 2, 4, 8 steps, and a
+    # pair counts that take each launch shape of the index kernels: one workgroup with 1, 2, 4 steps per
+    # wave (up to 4096 pairs), then count + place over several workgroups with 1, 2, 4, 8 steps, and a
     # grid beyond 256 workgroups
     (100, 4, 2, 64, "bf16", True),
     (250, 8, 2, 64, "bf16", False),
