@@ -2,7 +2,8 @@
 // Follows Algorithm 1 of the paper ("[s, idx] <- router(x)") with K activated experts per
 // token (Conditional Communication figure caption).
 //
-// gate_mfma_kernel puts the skinny GEMM on the matrix cores, bf16 and float storage alike.
+// gate_mfma_kernel puts the skinny GEMM on the matrix cores, bf16 and float storage alike; gate_few_kernel serves float
+// rows of more than 1024 columns with one to four experts, where most of a 16 x 16 block of logits would be padding.
 #include <type_traits>
 #include "common.hpp"
 #include "kernels.hpp"
@@ -33,8 +34,9 @@ __device__ __forceinline__ void for_row_rotations(F&& f) {
 // (wavefront w takes k-steps w, w+4, ...).  Operands come straight from global memory in MFMA
 // layout: lane l supplies row l%16 (a token for x, an expert for Wg) and the 16 bytes l/16 of
 // the step, i.e. one 16-byte load each; all loads of a batch are issued before
-// its MFMAs.  Float storage keeps four accumulators per component of those 16 bytes (step mod 4), so that no running
-// sum is longer than a sixteenth of a wavefront's share: the error of the scores stays that of a butterfly over the lanes.  Accumulator register v of lane l is logits[token 4*(l/16)+v][expert l%16].  The four
+// its MFMAs.  Float storage keeps four accumulators per component of those 16 bytes (a step takes the one of its place in the
+// batch mod 4), so that a running sum is a sixteenth of a wavefront's share where batches have four steps or twelve, a twelfth with
+// three, six or nine, and 3 / 40 with ten: the error of the scores stays that of a butterfly over the lanes.  Accumulator register v of lane l is logits[token 4*(l/16)+v][expert l%16].  The four
 // partial sums meet in LDS and are added in wavefront order (fixed, reproducible).  With at most 16
 // experts thread (t, e) then finishes logit e of token t: the 16 lanes of a DPP row hold one token and
 // rank, maximum and softmax sum come from rotating the row (no further LDS trip, all 16 tokens at once);
@@ -209,6 +211,130 @@ __global__ __launch_bounds__(256) void gate_mfma_kernel(const T* __restrict__ x,
     }
 }
 
+// Float rows, at most four experts.  A wavefront owns TPW tokens: each lane loads its 16-byte slices of all TPW rows (NCH per row,
+// whole lines, in flight while the workgroup stages the router matrix in LDS), multiplies them with the matching slices of
+// every router row, and the E x TPW sums are reduced over the 64 lanes with a fixed butterfly; then lane e plays expert e.
+// Bound by the latency of one round trip to memory where the matrix cores' k-steps are a chain of several.
+constexpr int kFewExperts = 4;
+template <int NCH, int TPW>
+__global__ __launch_bounds__(256) void gate_few_kernel(const float* __restrict__ x, const float* __restrict__ Wg,
+                                                       const float* __restrict__ bg, int T_tok, int d, int E, int k,
+                                                       int n_shared, int renorm, float* __restrict__ scores,
+                                                       int32_t* __restrict__ expert_idx, float* __restrict__ probs_all,
+                                                       float* __restrict__ logits)
+{
+    constexpr int V = Store<float>::kVec;
+    extern __shared__ u32x4_t lds_w[];
+    const int nvec = d / V;
+    const u32x4_t* wsrc = reinterpret_cast<const u32x4_t*>(Wg);
+    const int wave = threadIdx.x / kWave;
+    const int lane = lane_id();
+    const int tok0 = (blockIdx.x * (blockDim.x / kWave) + wave) * TPW;
+
+    // this lane's slices of the TPW rows (rows past the end repeat the last token; never written)
+    u32x4_t xv[TPW][NCH];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        int tok = tok0 + t;
+        if (tok >= T_tok) tok = T_tok - 1;
+        const u32x4_t* xr = reinterpret_cast<const u32x4_t*>(x + static_cast<size_t>(tok) * d);
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+            const int i = lane + c * kWave;
+            xv[t][c] = xr[i < nvec ? i : 0];
+        }
+    }
+    for (int v = threadIdx.x; v < E * nvec; v += blockDim.x) lds_w[v] = wsrc[v];
+    __syncthreads();
+    if (tok0 >= T_tok) return;
+
+    float acc[TPW][kFewExperts];
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+        for (int e = 0; e < kFewExperts; ++e) acc[t][e] = 0.f;
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) {
+        const int i = lane + c * kWave;
+        if (i < nvec) {
+            float xf[TPW][V];
+#pragma unroll
+            for (int t = 0; t < TPW; ++t) Store<float>::unpack(xv[t][c], xf[t]);
+#pragma unroll
+            for (int e = 0; e < kFewExperts; ++e) {
+                if (e < E) {
+                    float wf[V];
+                    Store<float>::unpack(lds_w[e * nvec + i], wf);
+#pragma unroll
+                    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+                        for (int u = 0; u < V; ++u) acc[t][e] = fmaf(xf[t][u], wf[u], acc[t][e]);
+                }
+            }
+        }
+    }
+
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+        const int tok = tok0 + t;
+        if (tok >= T_tok) break;                 // uniform across the wavefront
+        float zmax = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < kFewExperts; ++e) {
+            if (e < E) {
+                acc[t][e] = wave_sum(acc[t][e]);
+                if (bg) acc[t][e] += bg[e];
+                zmax = fmaxf(zmax, acc[t][e]);
+            }
+        }
+        // lane e is expert e
+        float z_me = -INFINITY;
+        float denom = 0.f;
+#pragma unroll
+        for (int e = 0; e < kFewExperts; ++e) {
+            if (e < E) {
+                if (lane == e) z_me = acc[t][e];
+                denom += expf(acc[t][e] - zmax);
+            }
+        }
+        int rank = 0;
+#pragma unroll
+        for (int e = 0; e < kFewExperts; ++e)
+            if (e < E) rank += (acc[t][e] > z_me || (acc[t][e] == z_me && e < lane)) ? 1 : 0;
+        const bool is_expert = lane < E;
+        const float p_me = is_expert ? expf(z_me - zmax) / denom : 0.f;
+        const bool chosen = is_expert && rank < k;
+        float s_me = p_me;
+        if (renorm) {
+            const float ssum = wave_sum(chosen ? p_me : 0.f);
+            s_me = p_me / ssum;
+        }
+        const size_t row = static_cast<size_t>(tok) * (k + n_shared);
+        if (chosen) {
+            scores[row + rank] = s_me;
+            expert_idx[row + rank] = lane;
+        }
+        if (lane < n_shared) {                      // shared experts: every token, score 1
+            scores[row + k + lane] = 1.0f;
+            expert_idx[row + k + lane] = E + lane;
+        }
+        if (is_expert) {
+            if (probs_all) probs_all[static_cast<size_t>(tok) * E + lane] = p_me;
+            if (logits) logits[static_cast<size_t>(tok) * E + lane] = z_me;
+        }
+    }
+}
+
+template <int NCH, int TPW>
+static hipError_t launch_gate_few(const float* x, const float* Wg, const float* bg, int T_tok, int d, int E, int k, int n_shared,
+                                  int renorm, float* scores, int32_t* idx, float* probs, float* logits, hipStream_t stream)
+{
+    hipLaunchKernelGGL((gate_few_kernel<NCH, TPW>), dim3((T_tok + 4 * TPW - 1) / (4 * TPW)), dim3(256),
+                       static_cast<size_t>(E) * d * sizeof(float), stream, x, Wg, bg, T_tok, d, E, k, n_shared, renorm, scores, idx,
+                       probs, logits);
+    return hipGetLastError();
+}
+
 template <typename T, int NB>
 static hipError_t launch_gate_mfma_nb(const T* x, const T* Wg, const float* bg, int T_tok, int d, int E, int k,
                                       int n_shared, int renorm, float* scores, int32_t* idx, float* probs, float* logits,
@@ -216,6 +342,17 @@ static hipError_t launch_gate_mfma_nb(const T* x, const T* Wg, const float* bg, 
 {
     const int blocks = (T_tok + 15) / 16;
     const int need = (d / RowMfma<T>::kUnit + 3) / 4;      // k-steps per wavefront
+    // Float, up to 16 experts: long rows in batches of four.  In batches of sixteen the 18 steps of d = 1152 cost as much as 32; full
+    // batches lose too, at the same register count (why was not separated).  us at 500 and 8192 tokens, batches of 16 / of 4: 8 experts
+    // of 1152, 11.8 / 7.0 and 20.4 / 11.0; 16 experts of 2048, 13.1 / 10.2 and 26.0 / 18.1.  Up to ten steps one batch is faster
+    // (16 experts of 576, 5.2 / 5.9).  The accumulator of a step is its number mod 4 either way: the same bits.
+    if constexpr (RowMfma<T>::kMfma > 1 && NB == 1) {
+        if (need > 10) {
+            hipLaunchKernelGGL((gate_mfma_kernel<T, NB, 4>), dim3(blocks), dim3(256), 0, stream, x, Wg, bg, T_tok, d, E, k, n_shared,
+                               renorm, scores, idx, probs, logits);
+            return hipGetLastError();
+        }
+    }
     // registers per lane: 4 * U * (1 + NB) for the operands of a batch
     constexpr int UMAX = NB == 1 ? 16 : (NB == 2 ? 10 : 6);
 #define DICEMOE_GATE_U(U_)                                                                                          \
@@ -241,6 +378,15 @@ static hipError_t launch_gate_mfma(const void* x, const void* Wg, const float* b
 {
     const T* xs = static_cast<const T*>(x);
     const T* ws = static_cast<const T*>(Wg);
+    // us, few / matrix cores: one expert of 2048 columns, 1024 tokens 4.6 / 8.9, 8192: 13.4 / 14.6; two of 1152: 5.4 / 6.7 and 9.0 / 10.2;
+    // four of 4096, 1024 tokens: 11.2 / 13.6, 6000: 39 / 25 (41 with batches of sixteen), 8192: 54 / 28; up to 1024 columns a router of
+    // two and more is faster on the matrix cores.
+    if constexpr (std::is_same_v<T, float>) {
+        if (d > 1024 && d <= 4096 && (E <= 2 || (E <= kFewExperts && T_tok <= 6144))) {
+            if (d <= 2048) return launch_gate_few<8, 2>(xs, ws, bg, T_tok, d, E, k, n_shared, renorm, scores, idx, probs, logits, stream);
+            return launch_gate_few<16, 1>(xs, ws, bg, T_tok, d, E, k, n_shared, renorm, scores, idx, probs, logits, stream);
+        }
+    }
     if (E <= 16) return launch_gate_mfma_nb<T, 1>(xs, ws, bg, T_tok, d, E, k, n_shared, renorm, scores, idx, probs, logits, stream);
     if (E <= 32) return launch_gate_mfma_nb<T, 2>(xs, ws, bg, T_tok, d, E, k, n_shared, renorm, scores, idx, probs, logits, stream);
     return launch_gate_mfma_nb<T, 4>(xs, ws, bg, T_tok, d, E, k, n_shared, renorm, scores, idx, probs, logits, stream);

@@ -101,6 +101,35 @@ def test_float_gate(d, E, k):
         assert (np.abs(np.delete(zi, 1, 1) - np.delete(z, 1, 1)) <= np.delete(bound, 1, 1) + 1e-12).all()
 
 
+@pytest.mark.parametrize("d,E,k,T", [
+    (1024, 2, 1, 33), (1040, 1, 1, 9), (1040, 2, 2, 33), (2048, 4, 2, 1), (2064, 4, 3, 8), (4096, 3, 2, 19),   # few experts, long rows
+    (1040, 4, 2, 6144), (1040, 4, 2, 6145), (1040, 2, 2, 6145),                                                # on both sides of the line
+    (1040, 5, 2, 33), (448, 8, 2, 33), (1152, 8, 2, 33)])                                                      # batches of four k-steps
+@pytest.mark.parametrize("renorm,n_shared", [(False, 2), (True, 0)])
+def test_float_gate_long_rows(d, E, k, T, renorm, n_shared):
+    print(f"\nfloat gate d={d} E={E} k={k} T={T}", flush=True)
+    x, Wg, bg, *_ = G.small_inputs(76 + d + E, T, d, E, 16, "f32")
+    ctx = B.Context(T, d, 16, E, k, "f32", renorm_topk=renorm, n_shared=n_shared)
+    scores = torch.full((T + 1, k + n_shared), 9.0, dtype=torch.float32, device=G.DEV)
+    idx = torch.full((T + 1, k + n_shared), 9, dtype=torch.int32, device=G.DEV)
+    probs, logits = (torch.full((T + 1, E), 9.0, dtype=torch.float32, device=G.DEV) for _ in range(2))
+    ctx.moe_gate(G.to_dev(x, "f32"), G.to_dev(Wg, "f32"), G.f32_dev(bg), scores, idx, probs, logits)
+    torch.cuda.synchronize()
+    z = O.router_logits(x, Wg, bg)
+    got = G.to_np(logits)[:T]
+    # as in test_float_gate: sums of d / 4 terms and a few more additions
+    assert (np.abs(got - z) <= (d / 4 + 8) * 2.0 ** -24 * (np.abs(x).astype(np.float64) @ np.abs(Wg).astype(np.float64).T + np.abs(bg)) + 1e-12).all()
+    picked = O.topk(got.astype(np.float64), k)
+    np.testing.assert_array_equal(G.to_np(idx)[:T, :k], picked)
+    np.testing.assert_array_equal(G.to_np(idx)[:T, k:], np.broadcast_to(E + np.arange(n_shared), (T, n_shared)))
+    p, s = O.scores(z, picked, renorm_topk=renorm)
+    np.testing.assert_allclose(G.to_np(scores)[:T, :k], s, rtol=5e-5, atol=1e-9)
+    assert (G.to_np(scores)[:T, k:] == 1.0).all()
+    np.testing.assert_allclose(G.to_np(probs)[:T], p, rtol=5e-5, atol=1e-9)
+    for t in (scores, idx, probs, logits):
+        assert (G.to_np(t)[T:] == 9).all()
+
+
 @pytest.mark.parametrize("n_pairs", [1, 255, 256, 257, 1023, 1024, 1025, 2048, 2049, 4095, 4097, 8191, 8192, 8193])
 @pytest.mark.parametrize("E,masked", [(1, False), (16, True), (64, False)])
 def test_dispatch_of_one_workgroup(n_pairs, E, masked):
