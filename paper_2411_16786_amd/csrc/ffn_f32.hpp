@@ -1,19 +1,20 @@
 // Grouped GEMM of the expert FFN for float storage, on the matrix cores: small tiles whose reduction is shared by the
-// wavefronts of a workgroup.
+// wavefronts of a workgroup, larger ones once they fill the chip.
 //
 // What bounds it.  Float workloads here are small (a few hundred rows, 16 experts): a 64 x 64 tile on the vector units
 // walked all of K = 1536 in 96 barrier-separated steps of LDS stores and reads, and the second GEMM has too few such tiles for
 // the chip.  Hence
-//   * a workgroup's four wavefronts each take a contiguous quarter of K for the same 32 x 32 tile; they meet once, in LDS,
-//     where the partial sums are added in wavefront order (the same bits in every run, and for a row wherever it lies).  No
-//     barrier and no LDS in the main loop;
+//   * a workgroup's four wavefronts each take a contiguous quarter of K for the same tile; they meet once, in LDS,
+//     where the partial sums are added in wavefront order (the same bits in every run, for a row wherever it lies, and on
+//     either tile).  No barrier and no LDS in the main loop;
 //   * operands come from global memory in MFMA layout (RowMfma): a 64-byte unit of a 16-row block is one 16-byte load per
-//     lane, and three units are in flight per wavefront, sixteen wavefronts per compute unit.
-// Both GEMMs, graph of ten calls: DiT-MoE-S widths, 500 tokens top-2: 137 us on the vector units, 56 here; 100 tokens 127 ->
-// 28; 600 tokens top-3 144 -> 80; 2000 tokens 186 -> 162; 64 x 256, 4 experts, 64 tokens 28 -> 10.  Larger tiles (32 x 64, 64 x 64),
-// more wavefronts per tile and deeper rings were within 5 us of it at 500 tokens, slower at 100.  What bounds it now was
-// not separated: 33 us and 28 us at 500 tokens (kernel trace) move 185 MB each into the compute units, 38 MB of them cold
-// weights; the matrix pipes need 8 us each.
+//     lane.  32 x 32 tiles have three units in flight per wavefront, sixteen wavefronts per compute unit; 64 x 64 tiles, which
+//     move half the bytes per flop, one unit and eight wavefronts (with two and three units 5 - 20 % slower).
+// Both GEMMs, graph of ten calls, against 64 x 64 tiles on the vector units: DiT-MoE-S widths, 500 tokens top-2: 137 -> 56 us; 100
+// tokens 127 -> 28; 64 x 256, 4 experts, 64 tokens 28 -> 10, all on 32 x 32 tiles.  On those alone many rows lose what few
+// gain: 16384 rows of the DiT-MoE-S widths 577 us on the vector units, 595 on 32 x 32 tiles, 493 on 64 x 64; 8192 of DiT-MoE-XL 2422, 2604
+// and 1769.  What bounds the small tiles now was not separated: 33 us and 28 us at 500 tokens (kernel trace) move 185 MB each
+// into the compute units, 38 MB of them cold weights; the matrix pipes need 8 us each.
 #pragma once
 #include "ffn_mfma.hpp"
 #include "ffn_stream.hpp"
@@ -21,19 +22,19 @@
 
 namespace dicemoe {
 
-constexpr int kDirectTM = 2, kDirectTN = 2;              // 16-row blocks of a tile: rows and columns
-constexpr int kDirectShares = 4, kDirectUnits = 3;       // wavefronts sharing K; units in flight
+constexpr int kDirectShares = 4;                         // wavefronts sharing K
 constexpr long long kDirectGrid = 1 << 20;
 
-template <bool GELU>
-__global__ __launch_bounds__(64 * kDirectShares, 4) void ffn_gemm_f32_kernel(
+// TM, TN: 16-row blocks of a tile, rows and columns; U: units in flight
+template <bool GELU, int TM, int TN, int U>
+__global__ __launch_bounds__(64 * kDirectShares, TM * TN > 4 ? 2 : 4) void ffn_gemm_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias, float* __restrict__ C, int N, int K,
     const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert, int n_seg, int n_tiles_n,
     const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index, int max_rows,
     int32_t* __restrict__ status)
 {
     typedef RowMfma<float> M;
-    constexpr int TM = kDirectTM, TN = kDirectTN, KS = kDirectShares, U = kDirectUnits;
+    constexpr int KS = kDirectShares;
     constexpr int BM = 16 * TM, BN = 16 * TN, BLOCKS = TM * TN;
     constexpr int CH = 4;                                // 16-byte chunks per unit
     __shared__ __attribute__((aligned(16))) f32x4_t part[KS][BLOCKS][64];
@@ -155,20 +156,38 @@ __global__ __launch_bounds__(64 * kDirectShares, 4) void ffn_gemm_f32_kernel(
     }
 }
 
+template <bool GELU, int TM, int TN, int U>
+static hipError_t launch_gemm_f32_tile(const float* A, const float* W, const float* bias, float* C, int N, int K,
+                                       const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
+                                       hipStream_t stream, const int32_t* row_index, int row_div, const int32_t* out_index,
+                                       int32_t* status)
+{
+    constexpr int BM = 16 * TM, BN = 16 * TN;
+    const int n_tiles_n = (N + BN - 1) / BN;
+    const long long tiles = (static_cast<long long>(max_rows) + BM - 1) / BM * n_tiles_n + static_cast<long long>(n_seg) * n_tiles_n;
+    const long long blocks = (tiles + 7) / 8 * 8;        // every XCD gets room for ceil(tiles / 8)
+    hipLaunchKernelGGL((ffn_gemm_f32_kernel<GELU, TM, TN, U>), dim3(static_cast<unsigned>(blocks < kDirectGrid ? blocks : kDirectGrid)),
+                       dim3(64 * kDirectShares), 0, stream, A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, n_tiles_n, row_index,
+                       row_div, out_index, max_rows, status);
+    return hipGetLastError();
+}
+
+// 64 x 64 tiles once they fill two and a half rounds of the 256 compute units and the experts have rows for one and a half of them
+// (a segment ends in half a tile on average).  One GEMM, us, 32 x 32 tiles / what 64 x 64 change: second GEMM of DiT-MoE-S, 330 tiles
+// + 5, 612: - 4, 798: - 42, 1584: - 126; 2048 x 8192, 4 experts, 576 tiles + 10; first GEMM of DiT-MoE-S, 94 rows an expert + 5,
+// 125 rows, 940 tiles - 3, 375 rows - 21; 512 x 2048, 64 experts, 31 rows an expert, 2048 tiles + 10, 128 rows - 69.
 template <bool GELU>
 static hipError_t launch_gemm_f32(const void* A, const void* W, const float* bias, void* C, int N, int K,
                                   const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
                                   hipStream_t stream, const int32_t* row_index = nullptr, int row_div = 1,
                                   const int32_t* out_index = nullptr, int32_t* status = nullptr)
 {
-    constexpr int BM = 16 * kDirectTM, BN = 16 * kDirectTN;
-    const int n_tiles_n = (N + BN - 1) / BN;
-    const long long tiles = (static_cast<long long>(max_rows) + BM - 1) / BM * n_tiles_n + static_cast<long long>(n_seg) * n_tiles_n;
-    const long long blocks = (tiles + 7) / 8 * 8;        // every XCD gets room for ceil(tiles / 8)
-    hipLaunchKernelGGL((ffn_gemm_f32_kernel<GELU>), dim3(static_cast<unsigned>(blocks < kDirectGrid ? blocks : kDirectGrid)), dim3(64 * kDirectShares), 0, stream,
-                       static_cast<const float*>(A), static_cast<const float*>(W), bias, static_cast<float*>(C), N, K, seg_offsets,
-                       seg_expert, n_seg, n_tiles_n, row_index, row_div, out_index, max_rows, status);
-    return hipGetLastError();
+    const float *a = static_cast<const float*>(A), *w = static_cast<const float*>(W);
+    float* c = static_cast<float*>(C);
+    const long long tiles = (max_rows / 64 + n_seg / 2ll) * ((N + 63) / 64);
+    if (tiles >= 640 && max_rows >= 96ll * n_seg)
+        return launch_gemm_f32_tile<GELU, 4, 4, 1>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+    return launch_gemm_f32_tile<GELU, 2, 2, 3>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
 }
 
 }  // namespace dicemoe

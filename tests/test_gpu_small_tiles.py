@@ -1,7 +1,7 @@
 """The kernels for few rows, narrow outputs and float storage where their tiles and shares can go wrong: the 64- and 128-row
 tiles of the expert FFN at their edges (the shortest reduction their rings take, a split one, columns that do not
 fill the last tile), the float GEMM's shared reduction with fewer units than wavefronts and with more segments than a wavefront
-has lanes, the float router over remainders of its k-steps and experts, and the one-workgroup dispatch at each size where it
+has lanes, on both of its tiles, the float router over remainders of its k-steps and experts, and the one-workgroup dispatch at each size where it
 takes another number of steps.
 
 Against the oracle, with the tolerances of tests/gpu_util.py; integers bit for bit.
@@ -32,6 +32,9 @@ FFN_CASES = [
     ("f32-five-units", [31, 32, 33, 64], 80, 48, "f32"),
     ("f32-many-units", [17, 65, 1, 96], 208, 400, "f32"),
     ("f32-70-segments", [1, 33, 0, 7, 32, 2, 40] * 10, 48, 80, "f32"),             # the segment table exceeds 64 lanes
+    ("f32-64x64-tiles", [639, 0, 64, 65, 127, 300, 1], 48, 2704, "f32"),           # first GEMM: 43 columns of tiles, the last a quarter full
+    ("f32-64x64-second", [513, 448, 1], 2576, 48, "f32"),                          # second GEMM, three units for four shares
+    ("f32-64x64-70-segments", [300, 2, 64, 0, 130, 65, 200] * 10, 16, 336, "f32"), # more segments than lanes, one unit of K
 ]
 
 
@@ -69,6 +72,25 @@ def test_ffn_small_tiles(case, scatter):
         G.assert_close_storage(got, ref, "f32", name)
     else:
         G.assert_close_expert_rows(got, ref, name)
+
+
+def test_float_ffn_bits_do_not_depend_on_the_tile():
+    """The first segment alone runs on 32 x 32 tiles, with the others on 64 x 64 (first GEMM, 43 columns of tiles)."""
+    seg_rows, d, F = [300, 200, 700], 48, 2704
+    rows = sum(seg_rows)
+    _, _, _, W1, b1, W2, b2 = G.small_inputs(77, 4, d, 3, F, "f32", bias=True, w_std=0.02)
+    x = np.random.Generator(np.random.PCG64(78)).standard_normal((rows, d), dtype=np.float32)
+    ctx = B.Context(rows, d, F, 3, 1, "f32")
+    ws = torch.empty(ctx.workspace_bytes(), dtype=torch.uint8, device=G.DEV)
+    weights = (G.to_dev(W1, "f32"), G.f32_dev(b1), G.to_dev(W2, "f32"), G.f32_dev(b2))
+    h = []
+    for n_seg in (3, 1):
+        off = np.concatenate([[0], np.cumsum(seg_rows[:n_seg])]).astype(np.int32)
+        out = torch.zeros((rows, d), device=G.DEV)
+        ctx.moe_expert_ffn(G.to_dev(x, "f32"), G.i32_dev(off), G.i32_dev(np.arange(n_seg, dtype=np.int32)), int(off[-1]), *weights, out, ws)
+        h.append(out[:seg_rows[0]])
+    torch.cuda.synchronize()
+    assert torch.equal(h[0], h[1]) and bool(h[0].any())
 
 
 @pytest.mark.parametrize("d", [16, 48, 64, 80, 400, 1040, 4096])
