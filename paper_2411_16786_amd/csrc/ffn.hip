@@ -262,28 +262,7 @@ static hipError_t launch_gemm_bf16(const void* A, const void* W, const float* bi
     return hipGetLastError();
 }
 
-// Tile shape for one bf16 grouped GEMM.  With at most 64 segments and enough tiles the persistent kernel of
-// ffn_stream.hpp, 192 or 256 columns, whichever its cost model expects to be faster.  The line for the first GEMM: 96 tiles
-// of 256 x 192 and 128 rows per expert.  For the second, more tiles of 256 x 192 than compute units: with one tile per
-// workgroup there is nothing to run on into, and the wide kernel starts sooner (kernel trace, DiT-MoE-XL widths: 8192 rows,
-// 240 tiles, 90 us against 94 - 98; 4096 rows, 120 tiles, 61 against 66; 16384 rows with two shared experts, 384
-// tiles, 160 against 145 on the persistent kernel).
-// Otherwise the wide kernel, a workgroup per tile, hand-scheduled wavefronts:
-//   256 x 192, one workgroup of eight wavefronts (4 x 2, each a 64 x 96 block; two per SIMD cover each
-//     other's waits, +1 % over four wavefronts of 128 x 96) per compute unit, two stages of activations
-//     and four of weights (all 160 KB of LDS; three with short reductions): the GEMM with the plain
-//     epilogue, when that grid covers most of the 256 compute units.
-//     The weights stream from HBM exactly once, and a barrier waits for the slowest of a step's loads:
-//     every weight stage more gives those loads another step of flight (DiT-MoE-XL shape, GEMM2, same
-//     box: 98 us with two weight stages, 86 - 91 with three, 82 - 86 with four);
-//   128 x 192, two stages (80 KB of LDS), two workgroups per compute unit: the GEMM whose epilogue
-//     evaluates GELU (one workgroup's MFMAs cover the other's epilogue arithmetic), and GEMMs between
-//     one and two 256-wide rounds;
-//   128 x 192, three stages, one workgroup per compute unit: grids of a quarter to one workgroup per
-//     compute unit (few refreshed rows, or narrow outputs).  Alone on a compute unit a workgroup has nobody to hide its load
-//     latency, and the third stage gives every load two steps of flight instead of one
-//     (57 us instead of 78 us for GEMM2 at 4096 rows of the DiT-MoE-XL widths).
-// Tiny problems stay on the 128 x 128 kernel, three workgroups per compute unit.
+// One bf16 grouped GEMM on the kernel that plan_ffn_gemm picks
 template <bool GELU>
 static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const float* bias, void* C, int N, int K,
                                         const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg,
@@ -291,97 +270,61 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
                                         int row_div = 1, const int32_t* out_index = nullptr, float* partial = nullptr,
                                         size_t partial_bytes = 0, int32_t* status = nullptr)
 {
-    constexpr int kComputeUnits = 256;
-    // tiles dealt to the XCDs by expert (one L2 per XCD: an expert's weight slabs are then fetched by one
-    // XCD) whenever the segment table fits the lanes of a wavefront; else bands of row tiles
     const int by_expert = n_seg <= 64 ? 1 : 0;
-    // expected tiles: every segment ends in a partial row tile, half a tile on average
-    auto tiles = [&](int bm, int bn) {
-        const long long m_tiles = (static_cast<long long>(max_rows) + static_cast<long long>(n_seg) * bm / 2 + bm - 1) / bm;
-        return m_tiles * ((N + bn - 1) / bn);
-    };
-    const bool fits_192 = (N + 191) / 192 * 192 * 8 <= N * 9;          // at most 1/8 of the columns computed in vain
-    const bool fits_128 = (N + 127) / 128 * 128 * 8 <= N * 9;
-    const bool full_rows = max_rows >= 128 * n_seg;                    // (row tiles half full on average)
-    if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (GELU ? 96 : kComputeUnits + 1)) {
-        const bool wide = !fits_192 || stream_cost(256, N, K, GELU, max_rows, n_seg) < stream_cost(192, N, K, GELU, max_rows, n_seg);
-        if (wide) return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+    const FfnPlan plan = plan_ffn_gemm(GELU, N, K, max_rows, n_seg, partial ? partial_bytes : 0);
+#define DICEMOE_WIDE(...)                                                                                                    \
+    return launch_gemm_bf16_wide<__VA_ARGS__>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, \
+                                              row_div, out_index, by_expert, nullptr, 1, status)
+    switch (plan.tile) {
+    case FfnTile::Stream192:
         return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
-    }
-    // Few rows per expert, or few tiles altogether: 64 x 128 tiles, three stages in 72 KB of LDS, so that two workgroups share
-    // a compute unit and cover each other's waits, and a 64-row tile of a small expert is not half padding.
-    // First GEMM (us, 128-row tiles / 64-row tiles): up to 72 rows per expert, above that a second row tile
-    // reads the weights again (DiT-MoE-XL, 75 rows an expert 26 / 29.5, 88: 25.5 / 30): DiT-MoE-S, 38: 15 / 12, 69: 16 / 14;
-    // DiT-MoE-G, 16: 116 / 90, 64: 122 / 105; and up to 96 rows where the 128 x 192 tiles would take more than one round: DiT-MoE-G, 88:
-    // 121 / 116, 112: 123 / 129; expert-parallel widths, 88: 170 / 145.
-    // Second GEMM: while there is at most one tile per compute unit (128 x 192 tiles, K in two or three shares / 64-row tiles: DiT-MoE-XL,
-    // 900 rows 48 / 29.5, 1400 rows 42 / 34; DiT-MoE-S, 2000 rows 27 / 16; DiT-MoE-G, 256 rows 109 / 84); then 128 x 128 tiles
-    // up to seven eighths of that (a count beyond 256 is a second round: DiT-MoE-G, 1024 rows, 224 tiles 110 / 99; 1200 rows, 252 tiles
-    // 110 / 138), unless two shares of K on 128 x 192 tiles fill the chip (DiT-MoE-XL, 2000 rows: 45 split, 49 on 128 x 128).
-    if (by_expert && fits_128 && K >= 256) {
-        const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t192 = tiles(128, 192);
-        // (not for a long reduction that 128 x 192 tiles do in one round: those have 120 KB of loads in flight per compute unit, which
-        // cold weights need: whole layer, DiT-MoE-XL widths, 256 tokens, other weights in every pass, 72.6 us against 74.1)
-        const bool one_round = t192 <= kComputeUnits && K >= 1024;
-        const bool small_experts = (max_rows <= 72 * n_seg && !one_round) || (max_rows <= 96 * n_seg && t192 > kComputeUnits);
-        // (the same for the second GEMM in three shares of K on one 128-row tile per expert)
-        const bool three_shares = partial && fits_192 && t192 * 3 * 20 <= kComputeUnits * 21 && K / 64 / 3 >= 16 &&
-                                  static_cast<size_t>(3) * max_rows * N * sizeof(float) <= partial_bytes && max_rows <= 100 * n_seg;
-        if (GELU && (small_experts || (full_rows && t64 <= 2 * kComputeUnits)))
-            return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-        if (!GELU && !three_shares && t64 <= kComputeUnits)
-            return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-        const bool splits = partial && fits_192 && t192 * 2 * 20 <= kComputeUnits * 21 && K / 64 / 2 >= 16;
-        if (!GELU && !three_shares && !splits && 8 * t128 <= 7 * kComputeUnits)
-            return launch_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-    }
-    // Few rows and a long reduction (the second GEMM after a small refresh fraction or for a small batch):
-    // the 128 x 192 tiles do not fill the chip and each walks all of K.  With two or three workgroups per
-    // tile, each on a share of K (float partial sums in the workspace, added by a second pass in a fixed
-    // order), more compute units stream the weights at once: 54 -> 47 us at 2048 rows of the DiT-MoE-XL
-    // widths.  Not worth it once the tiles fill the chip by themselves (57 vs 66 us at 4096 rows), nor when a
-    // share is left with fewer than sixteen steps (DiT-MoE-S widths, K = 1536, 4096 rows: 32 us split in
-    // three, 23 in two, 20 unsplit on three-stage tiles): the second pass then costs more than the split saves.
-    if (!GELU && partial && fits_192 && by_expert) {
-        const long long t23 = tiles(128, 192);
-        int splits = 1;
-        for (int sp = 3; sp >= 2 && splits == 1; --sp)       // the deepest split whose shares still fill the chip at most once
-            if (t23 * sp * 20 <= kComputeUnits * 21 && K / 64 / sp >= 16 &&
-                static_cast<size_t>(sp) * max_rows * N * sizeof(float) <= partial_bytes)
-                splits = sp;
-        if (splits > 1) {
-            hipError_t err = launch_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg,
-                                                                       max_rows, stream, row_index, row_div, nullptr,
-                                                                       by_expert, partial, splits, status);
-            return err != hipSuccess ? err : launch_splitk_reduce(partial, splits, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
+    case FfnTile::Stream256:
+        return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+    case FfnTile::Small64: DICEMOE_WIDE(1, 2, 2, 3, 3, GELU);
+    case FfnTile::Small128:
+        if constexpr (!GELU) DICEMOE_WIDE(2, 2, 2, 3, 3, GELU);
+        break;
+    case FfnTile::Mid192Deep:
+        if constexpr (!GELU) {
+            if (plan.shares > 1) {
+                const hipError_t err = launch_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg,
+                                                                                 max_rows, stream, row_index, row_div, nullptr,
+                                                                                 by_expert, partial, plan.shares, status);
+                return err != hipSuccess ? err : launch_splitk_reduce(partial, plan.shares, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
+            }
         }
+        DICEMOE_WIDE(2, 3, 2, 3, 3, GELU);
+    case FfnTile::Mid192: DICEMOE_WIDE(2, 3, 2, 2, 2, GELU);
+    case FfnTile::Wide192W4:
+        if constexpr (!GELU) DICEMOE_WIDE(2, 3, 2, 2, 4, GELU, 4, 2);
+        break;
+    case FfnTile::Wide192W3:
+        if constexpr (!GELU) DICEMOE_WIDE(2, 3, 2, 2, 3, GELU, 4, 2);
+        break;
+    case FfnTile::Wide192:
+        if constexpr (!GELU) DICEMOE_WIDE(4, 3, 2, 2, 2, GELU);
+        break;
+    case FfnTile::Staged128:
+        return launch_gemm_bf16<128, 128, 3, true, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,
+                                                         row_div, out_index, status);
     }
-    if (!GELU && fits_192 && tiles(256, 192) * 10 >= kComputeUnits * 6) {
-        if (K >= 320)      // four weight stages (all 160 KB of LDS): three steps of flight for the cold weight stream
-            return launch_gemm_bf16_wide<2, 3, 2, 2, 4, GELU, 4, 2>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-        if (K >= 256)
-            return launch_gemm_bf16_wide<2, 3, 2, 2, 3, GELU, 4, 2>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-        return launch_gemm_bf16_wide<4, 3, 2, 2, 2, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-    }
-    if (fits_192 && K >= 256 && tiles(128, 192) <= kComputeUnits && tiles(128, 192) * 4 >= kComputeUnits)
-        return launch_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-    if (fits_192 && tiles(128, 192) * 2 >= kComputeUnits)
-        return launch_gemm_bf16_wide<2, 3, 2, 2, 2, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, by_expert, nullptr, 1, status);
-    return launch_gemm_bf16<128, 128, 3, true, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,
-                                                           row_div, out_index, status);
+#undef DICEMOE_WIDE
+    return hipErrorInvalidValue;                 // (the tiles that only the GEMM without GELU takes)
 }
 
-// Every instantiation of the wide kernel that launch_gemm_bf16_auto can pick needs its LDS limit
+// Every instantiation of the wide kernel that launch_gemm_bf16_auto can launch needs its LDS limit
 // raised once per device.
 template <bool GELU>
 static hipError_t configure_gemm_bf16_auto()
 {
     hipError_t err = configure_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>();
-    if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 3, GELU, 4, 2>();
-    if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 4, GELU, 4, 2>();
-    if (err == hipSuccess) err = configure_gemm_bf16_wide<4, 3, 2, 2, 2, GELU>();
     if (err == hipSuccess) err = configure_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>();
-    if (err == hipSuccess && !GELU) err = configure_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>();
+    if constexpr (!GELU) {
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 3, GELU, 4, 2>();
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 4, GELU, 4, 2>();
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<4, 3, 2, 2, 2, GELU>();
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>();
+    }
     if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 2, GELU>();
     if (err == hipSuccess) err = configure_gemm_bf16_stream<3, GELU>();
     if (err == hipSuccess) err = configure_gemm_bf16_stream<4, GELU>();

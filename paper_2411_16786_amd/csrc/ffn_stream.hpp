@@ -26,21 +26,15 @@
 #pragma once
 #include <type_traits>
 #include "ffn_mfma.hpp"
+#include "ffn_plan.hpp"
 #include "ffn_wide.hpp"
 
 namespace dicemoe {
 
 constexpr uint32_t kBeyondBuffer = 0xFFFFFFF0u;          // an offset that every buffer descriptor here rejects
 constexpr int kBufferFlags = 0x00027000;                 // raw buffer, 32-bit data format
-constexpr int kStreamGrid = 256, kStreamSlots = kStreamGrid / 8;      // workgroups, and workgroups per XCD
 constexpr int kStreamThreads = 512;
 constexpr int kStreamLds = 160 * 1024;
-
-// Pieces that each of `left` leftover tiles of an XCD is cut into.
-constexpr __host__ __device__ int leftover_pieces(int bn, int left, int slots)
-{
-    return left == 0 ? 1 : (bn == 256 && 4 * left <= slots ? 4 : (2 * left <= slots ? 2 : 1));
-}
 
 // The tiles of one grouped GEMM dealt to the eight XCDs by expert, as find_tile_by_expert does for a workgroup per tile
 // (home XCD = expert mod 8, an XCD keeps at most cap = ceil(total / 8) tiles of its own list and takes overflow of
@@ -563,28 +557,6 @@ __global__ __launch_bounds__(512, 1) void ffn_gemm_bf16_stream_kernel(
         else if (pieces == 4) stream_tiles<1, 2, 2, 5, 5, GELU, GATHER, 4, 2>(g, smem, 1, p, same);
         else stream_tiles<1, 4, 2, 3, 3, GELU, GATHER, 4, 2>(g, smem, 1, p, same);
     }
-}
-
-// Expected time (us) of one grouped GEMM on 256 x bn tiles.  The segment sizes live on the device; a segment ends in half a
-// row tile on average, and the count is averaged over the row tiles around that.  Measured on the DiT-MoE-XL, DiT-MoE-G
-// and expert-parallel widths: 1.06 (192 columns) and 1.42 us (256) per 64-deep step with all compute units busy,
-// 0.68 / 0.8 for a round of halves and 0.6 for quarters, epilogues 4.3 / 5.5 us with GELU and 2.6 / 4.2 without.
-static float stream_cost(int bn, int N, int K, bool gelu, int rows, int n_seg)
-{
-    const float step[5] = {0.f, bn == 192 ? 1.06f : 1.42f, bn == 192 ? 0.68f : 0.8f, 0.f, 0.6f};      // by pieces
-    const float epilogue = gelu ? (bn == 192 ? 4.3f : 5.5f) : (bn == 192 ? 2.6f : 4.2f);
-    const int nk = K / 64, cols = (N + bn - 1) / bn;
-    float sum = 0.f;
-    for (int d = -2; d <= 2; ++d) {
-        int bands = (rows + 255) / 256 + n_seg / 2 + d;
-        bands = bands < 1 ? 1 : bands;
-        const int per_xcd = (bands * cols + 7) / 8;
-        const int rounds = per_xcd / kStreamSlots, left = per_xcd % kStreamSlots;
-        const int pieces = leftover_pieces(bn, left, kStreamSlots);
-        sum += rounds * (nk * step[1] + epilogue);
-        if (left > 0) sum += nk * step[pieces] + epilogue + (pieces > 1 ? 3.f : 0.f);      // (a piece fills its rings anew)
-    }
-    return sum * 0.2f;
 }
 
 template <int TN, bool GELU>

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "ffn_plan.hpp"
+
 namespace dicemoe {
 
 // scores / idx have k + n_shared columns: the k routed slots, then slot k+s = (expert E+s, score 1)
@@ -51,10 +53,6 @@ hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_i
 // report_row_overflow in ffn_mfma.hpp.
 // Once per device before the first launch_expert_ffn there: raises the dynamic-LDS limit of the wide kernels.
 hipError_t prepare_expert_ffn();
-
-// bytes of float partial sums that the split reduction of the second GEMM may use (beyond `hidden`)
-// (at most about 270 workgroups of 128 x 192 float tiles)
-constexpr size_t kSplitKBytes = static_cast<size_t>(288) * 128 * 192 * sizeof(float);
 
 // S_buffer[p] = scores[p] for the routed slots (j < k_cached) of every pair with mask[p] != 0 (all if mask is null)
 hipError_t launch_commit_scores(const float* scores, const uint8_t* mask, int T_tok, int k, int k_cached,

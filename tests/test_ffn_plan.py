@@ -1,0 +1,71 @@
+"""The tile rule of the expert FFN on the CPU: the cases of the GPU tests run what they are named for, and between them every tile and
+every kind of work item that the rule can lead to."""
+import itertools
+
+import pytest
+
+import plan_util as P
+import test_gpu_ffn_stream as stream
+import test_gpu_parity as parity
+import test_gpu_small_tiles as small
+
+SMALL_TILES = {      # bf16 cases of test_gpu_small_tiles.py: tiles of the first and the second GEMM
+    "64-row-tiles": ("64x128", "staged"),
+    "four-steps": ("64x128", "64x128"),
+    "half-last-column-tile": ("64x128", "64x128"),
+    "long-reduction": ("64x128", "64x128"),
+    "odd-steps": ("64x128", "64x128"),
+    "128-row-tiles": ("stream192", "128x128"),
+    "three-shares-of-k": ("128x192deep", "128x192deep/3"),
+    "first-gemm-many-rows": ("64x128", "64x128"),
+    "second-on-128x192": ("64x128", "128x192"),
+    "second-on-256x192": ("128x192deep", "256x192"),
+}
+
+
+@pytest.mark.parametrize("case", stream.CASES, ids=[c[0] for c in stream.CASES])
+def test_persistent_cases_run_what_they_say(case):
+    name, seg_rows, d, F, first, second = case
+    assert P.describe(seg_rows, stream.segment_experts(len(seg_rows)), d, F) == (first, second)
+
+
+def test_small_cases_run_what_they_say():
+    got = {c[0]: P.ffn_plans(sum(c[1]), len(c[1]), c[2], c[3]) for c in small.FFN_CASES if c[4] == "bf16"}
+    assert got == SMALL_TILES
+
+
+WIDE_TILES = {       # of test_gpu_parity.py
+    "xl-8192-rows": ("stream256", "256x192w4"), "xl-4096-rows": ("stream192", "128x192deep"),
+    "xl-2048-rows": ("stream256", "128x192deep/2"), "xl-700-rows": ("128x192deep", "128x192deep/3"),
+    "k-64": ("128x192", "staged"), "k-128": ("128x192", "64x128"), "k-192": ("128x192", "staged"), "k-256": ("128x192deep", "64x128"),
+    "k-256-few-rows": ("128x192deep", "64x128"),
+    "k2-320": ("staged", "256x192w4"), "k2-384": ("64x128", "256x192w4"), "k2-256": ("64x128", "256x192w3"),
+}
+
+
+def test_wide_cases_run_what_they_say():
+    got = {c[0]: P.ffn_plans(sum(c[1]), len(c[1]), c[2], c[3]) for c in parity.WIDE_FFN_CASES}
+    assert {name: got[name] for name in WIDE_TILES} == WIDE_TILES
+
+
+def test_every_kind_of_persistent_item_is_run_by_either_gemm():
+    seen = {(gemm, line.split()[0], item) for c in stream.CASES for gemm, line in enumerate(c[4:]) for item in line.split()[1:]}
+    for gemm, (tile, items) in itertools.product((0, 1), (("stream192", "whole leftover halves rowless"),
+                                                          ("stream256", "whole leftover halves quarters rowless columnless"))):
+        for item in items.split():
+            assert (gemm, tile, item) in seen
+
+
+def test_every_tile_of_the_rule_is_run_by_a_case():
+    widths = [64, 128, 192, 256, 320, 384, 448, 576, 768, 1024, 1152, 1536, 1792, 2048, 4608, 7168, 8192]
+    rows = [int(2.0 ** (i / 2)) for i in range(0, 36)]
+    reached = set()
+    for d, F, n_seg, R in itertools.product(widths, widths, (1, 2, 4, 8, 16, 32, 64, 80), rows):
+        first, second = P.ffn_plans(R, n_seg, d, F)
+        reached |= {(0, first), (1, second)}
+    run = set()
+    cases = stream.CASES + [c for c in small.FFN_CASES if c[4] == "bf16"] + parity.WIDE_FFN_CASES
+    for c in cases:
+        first, second = P.ffn_plans(sum(c[1]), len(c[1]), c[2], c[3])
+        run |= {(0, first), (1, second)}
+    assert reached <= run, sorted(reached - run)

@@ -18,27 +18,40 @@ import gpu_util as G
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (name, rows per segment, d, F): tiles per XCD of the two GEMMs on 256 rows x 256 (192) columns
-    ("one-round-and-quarters", [1280, 1025, 1150, 1281, 1, 0, 2300, 1290], 1792, 512),
-    ("halves-with-empty-lower-half", [300, 257, 384, 129, 640, 511, 128, 385], 1152, 4608),
-    ("leftover-run-whole", [700, 900, 650, 1100, 820, 760, 905, 1024], 1152, 4608),
-    ("hot-expert", [6000, 30, 0, 200, 61, 90, 263, 1500], 1152, 1536),
-    ("columns-not-a-multiple", [520, 700, 513, 300, 1000, 800, 257, 400], 1088, 1600),
-    ("six-steps", [1391, 612, 1204, 893, 1347, 701, 1120, 924], 384, 4608),
-    ("more-than-64-tiles-each", [16384 - 77], 384, 66560),
+    # (name, rows per segment, d, F, what the first and the second GEMM run: asserted by tests/test_ffn_plan.py)
+    ("halves-of-192", [1280, 1025, 1150, 1281, 1, 0, 2300, 1290], 1792, 512, "stream192 halves rowless",
+     "stream192 halves rowless whole"),
+    ("quarters-without-rows", [300, 257, 384, 129, 640, 511, 128, 385], 1152, 4608, "stream256 quarters rowless whole", "128x192deep"),
+    ("halves-of-256", [241, 459, 194, 99, 481, 1021, 211, 237], 576, 3072, "stream256 halves leftover", "64x128"),
+    ("quarters-without-columns", [524, 656, 1414, 1026, 822, 358, 411, 703, 231], 384, 2176,
+     "stream256 columnless leftover quarters whole", "128x192deep/2"),
+    ("second-halves-of-192", [266, 772, 1415, 446, 260, 793, 564], 2176, 512, "64x128", "stream192 halves leftover rowless whole"),
+    ("second-quarters-without-columns", [1437, 787, 983, 1318, 2394, 1359, 506, 1054, 2086], 1152, 384, "stream192 halves rowless",
+     "stream256 columnless leftover quarters rowless whole"),
+    ("second-halves-of-256", [654, 1625, 1068, 1508, 1235, 1873, 1025, 1028], 2176, 384, "64x128",
+     "stream256 halves leftover rowless whole"),
+    ("leftover-run-whole", [700, 900, 650, 1100, 820, 760, 905, 1024], 1152, 4608, "stream192 leftover whole", "256x192w4"),
+    ("hot-expert", [6000, 30, 0, 200, 61, 90, 263, 1500], 1152, 1536, "stream256 leftover", "256x192w4"),
+    ("columns-not-a-multiple", [520, 700, 513, 300, 1000, 800, 257, 400], 1088, 1600, "stream192 leftover", "128x192deep"),
+    ("six-steps", [1391, 612, 1204, 893, 1347, 701, 1120, 924], 384, 4608, "stream256 leftover whole", "128x128"),
+    ("more-than-64-tiles-each", [16384 - 77], 384, 66560, "stream256 many whole", "128x192deep"),
 ]
+
+
+def segment_experts(E):
+    return np.roll(np.arange(E, dtype=np.int32), 1)
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 def test_persistent_ffn_on_sampled_rows(case):
-    name, seg_rows, d, F = case
+    name, seg_rows, d, F = case[:4]
     E, rows = len(seg_rows), int(sum(seg_rows))
     print(f"\nstream ffn {name}", flush=True)
     _, _, _, W1, b1, W2, b2 = G.small_inputs(61, 4, d, E, F, "bf16", bias=True, w_std=0.02 if F < 10000 else 0.005)
     r = np.random.Generator(np.random.PCG64(62))
     xp = WL.to_storage(r.standard_normal((rows, d), dtype=np.float32), "bf16")
     seg_offsets = np.concatenate([[0], np.cumsum(seg_rows)]).astype(np.int32)
-    seg_expert = np.roll(np.arange(E, dtype=np.int32), 1)
+    seg_expert = segment_experts(E)
     ctx = B.Context(rows + 8, d, F, E, 1, "bf16")
     h = torch.full((rows + 8, d), 9.0, dtype=torch.bfloat16, device=G.DEV)
     ws = torch.empty(ctx.workspace_bytes(), dtype=torch.uint8, device=G.DEV)
@@ -65,3 +78,12 @@ def test_persistent_ffn_on_sampled_rows(case):
     ctx.moe_expert_ffn_rows(x_tok, G.i32_dev(perm), *args, h2, ws)
     torch.cuda.synchronize()
     assert torch.equal(h2[:rows], h[:rows])
+    # ... and scattered on the way out
+    pairs = r.permutation(rows + 8)[:rows].astype(np.int32)
+    h3 = torch.full_like(h, 5.0)
+    ctx.moe_expert_ffn_commit(x_tok, G.i32_dev(perm), G.i32_dev(pairs), *args, None, None, h3, None, ws, T=rows + 8)
+    torch.cuda.synchronize()
+    where = torch.from_numpy(pairs).long().to(G.DEV)
+    assert torch.equal(h3[where], h[:rows])
+    h3[where] = 5.0
+    assert bool((h3 == 5.0).all())

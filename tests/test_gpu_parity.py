@@ -264,13 +264,13 @@ def test_expert_ffn_against_oracle(case):
     assert (h_gpu[rows:] == 9.0).all()          # rows outside every segment are left untouched
 
 
-# Shapes that take each launch configuration of the wide-tile bf16 kernel (tile shape, number of
-# stages, workgroups per compute unit are chosen from rows and widths), checked on sampled rows:
+# Shapes over the launch configurations of the bf16 kernels (tile shape, number of stages, workgroups per compute
+# unit are chosen from rows and widths; test_ffn_plan.py says what each case runs), checked on sampled rows:
 # the first and last rows of every segment (tile and segment boundaries) plus random ones.
 WIDE_FFN_CASES = [
     # (name, rows per segment, d, F)
-    ("xl-8192-rows", [1391, 612, 1204, 893, 1347, 701, 1120, 924], 1152, 4608),   # 128x192 x2 / 256x192
-    ("xl-4096-rows", [695, 306, 602, 446, 673, 350, 560, 464], 1152, 4608),       # 128x192 x2 / three stages
+    ("xl-8192-rows", [1391, 612, 1204, 893, 1347, 701, 1120, 924], 1152, 4608),   # persistent, 256 columns / 256x192
+    ("xl-4096-rows", [695, 306, 602, 446, 673, 350, 560, 464], 1152, 4608),       # persistent, 192 columns / 128x192, three stages
     ("xl-2048-rows", [300, 200, 310, 250, 280, 190, 270, 248], 1152, 4608),       # second GEMM: K split in two
     ("xl-700-rows", [3, 250, 0, 129, 64, 1, 192, 61], 1152, 4608),                # second GEMM: K split in three
     ("column-tails", [700, 0, 1033, 515, 390, 462], 1088, 1600),                  # widths not multiples of 192

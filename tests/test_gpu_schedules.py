@@ -135,7 +135,8 @@ def test_schedule_stack_against_the_oracle(case):
 def test_commit_writes_the_rows_of_the_packed_call_into_the_pair_buffer(cfg, T, dtype):
     """moe_expert_ffn_commit against moe_expert_ffn_rows (itself checked against the oracle): the
     same h rows, bit for bit, at H[perm[r]]; pairs that were not dispatched keep their old rows; the
-    scores of the dispatched pairs are committed.  Covers every tile shape the launcher picks."""
+    scores of the dispatched pairs are committed.  (The persistent kernel's scatter: test_gpu_ffn_stream.py; the small tiles':
+    test_gpu_small_tiles.py.)"""
     li, _ = G.pick_layer(cfg, T=T)
     c = li.cfg
     Tn, k, d, E = li.x.shape[0], c.k, c.d, c.E

@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 
 FFN_CASES = [
     # (name, rows per segment, d, F, dtype)
-    ("64-row-tiles", [63, 0, 64, 65, 1, 128, 129, 40], 320, 384, "bf16"),          # both GEMMs on 64 x 128 tiles
+    ("64-row-tiles", [63, 0, 64, 65, 1, 128, 129, 40], 320, 384, "bf16"),          # first GEMM on 64 x 128 tiles
     ("four-steps", [10, 64, 70, 3], 256, 256, "bf16"),                             # the shortest ring of three stages
     ("half-last-column-tile", [100, 31, 65, 0], 576, 1088, "bf16"),                # N % 128 == 64 in both GEMMs
     ("long-reduction", [64, 127, 1, 30], 256, 2048, "bf16"),
@@ -28,6 +28,8 @@ FFN_CASES = [
     ("128-row-tiles", [127, 128, 129, 700, 1, 0, 416, 400], 1088, 1536, "bf16"),   # second GEMM on 128 x 128, ragged columns
     ("three-shares-of-k", [64, 100, 0, 70], 1152, 4608, "bf16"),                   # second GEMM: 24 steps a share on 128 x 192
     ("first-gemm-many-rows", [500, 400], 256, 384, "bf16"),                        # full row tiles, few of them
+    ("second-on-128x192", [700, 450, 513, 640, 380, 511, 300, 602], 1152, 128, "bf16"),      # two steps of a two-stage ring
+    ("second-on-256x192", [1391, 612, 1204, 893, 1347, 701, 1120, 924], 1152, 192, "bf16"),  # four wavefronts, three steps
     ("f32-one-unit", [5, 33, 0, 32], 16, 16, "f32"),                               # K = 16: three of four shares are empty
     ("f32-five-units", [31, 32, 33, 64], 80, 48, "f32"),
     ("f32-many-units", [17, 65, 1, 96], 208, 400, "f32"),
