@@ -343,7 +343,7 @@ static int expert_ffn_common(moe_ctx* ctx, const char* who, const void* x_rows, 
     char* ws = static_cast<char*>(workspace);
     return hip_result(ctx,
                       launch_expert_ffn(is_bf16(ctx), x_rows, row_pairs, slots(ctx), seg_offsets, seg_expert, n_segments,
-                                        max_rows, s.d, s.F, W1, b1, W2, b2, h_packed, out_pairs, workspace,
+                                        experts(ctx), max_rows, s.d, s.F, W1, b1, W2, b2, h_packed, out_pairs, workspace,
                                         is_bf16(ctx) ? ws + status_offset(ctx) - dicemoe::kSplitKBytes : nullptr,
                                         is_bf16(ctx) ? dicemoe::kSplitKBytes : 0,
                                         reinterpret_cast<int32_t*>(ws + status_offset(ctx)), static_cast<hipStream_t>(stream),

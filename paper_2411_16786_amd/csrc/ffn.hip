@@ -265,13 +265,13 @@ static hipError_t launch_gemm_bf16(const void* A, const void* W, const float* bi
 // One bf16 grouped GEMM on the kernel that plan_ffn_gemm picks
 template <bool GELU>
 static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const float* bias, void* C, int N, int K,
-                                        const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg,
+                                        const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts,
                                         int max_rows, hipStream_t stream, const int32_t* row_index = nullptr,
                                         int row_div = 1, const int32_t* out_index = nullptr, float* partial = nullptr,
                                         size_t partial_bytes = 0, int32_t* status = nullptr)
 {
     const int by_expert = n_seg <= 64 ? 1 : 0;
-    const FfnPlan plan = plan_ffn_gemm(GELU, N, K, max_rows, n_seg, partial ? partial_bytes : 0);
+    const FfnPlan plan = plan_ffn_gemm(GELU, N, K, max_rows, n_seg, n_experts, partial ? partial_bytes : 0);
 #define DICEMOE_WIDE(...)                                                                                                    \
     return launch_gemm_bf16_wide<__VA_ARGS__>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, \
                                               row_div, out_index, by_expert, nullptr, 1, status)
@@ -339,7 +339,7 @@ hipError_t prepare_expert_ffn()
 }
 
 hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_index, int row_div,
-                             const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows, int d,
+                             const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts, int max_rows, int d,
                              int F, const void* W1, const float* b1, const void* W2, const float* b2, void* h_packed,
                              const int32_t* out_index, void* hidden, void* partial, size_t partial_bytes,
                              int32_t* status, hipStream_t stream, hipEvent_t between)
@@ -347,11 +347,11 @@ hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_i
     if (max_rows == 0) return launch_row_overflow_check(status, seg_offsets, n_seg, stream);
     hipError_t err;
     if (bf16) {
-        err = launch_gemm_bf16_auto<true>(x_rows, W1, b1, hidden, F, d, seg_offsets, seg_expert, n_seg, max_rows, stream,
+        err = launch_gemm_bf16_auto<true>(x_rows, W1, b1, hidden, F, d, seg_offsets, seg_expert, n_seg, n_experts, max_rows, stream,
                                           row_index, row_div, nullptr, nullptr, 0, status);
         if (err != hipSuccess) return err;
         if (between != nullptr && (err = hipEventRecord(between, stream)) != hipSuccess) return err;
-        return launch_gemm_bf16_auto<false>(hidden, W2, b2, h_packed, d, F, seg_offsets, seg_expert, n_seg, max_rows, stream,
+        return launch_gemm_bf16_auto<false>(hidden, W2, b2, h_packed, d, F, seg_offsets, seg_expert, n_seg, n_experts, max_rows, stream,
                                             nullptr, 1, out_index, static_cast<float*>(partial), partial_bytes);
     }
     err = launch_gemm_f32<true>(x_rows, W1, b1, hidden, F, d, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,

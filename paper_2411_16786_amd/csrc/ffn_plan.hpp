@@ -60,7 +60,7 @@ inline float stream_cost(int bn, int N, int K, bool gelu, int rows, int n_seg)
 // ffn_stream.hpp, 192 or 256 columns, whichever its cost model expects to be faster.  The line for the first GEMM: 96 tiles
 // of 256 x 192 and 128 rows per expert.  For the second, more tiles of 256 x 192 than compute units: with one tile per
 // workgroup there is nothing to run on into, and the wide kernel starts sooner (kernel trace, DiT-MoE-XL widths: 8192 rows,
-// 240 tiles, 90 us against 94 - 98; 4096 rows, 120 tiles, 61 against 66; 16384 rows with two shared experts, 384
+// 216 tiles, 90 us against 94 - 98; 4096 rows, 120 tiles, 61 against 66; 12288 rows with two shared experts, 318
 // tiles, 160 against 145 on the persistent kernel).
 // Otherwise the wide kernel, a workgroup per tile, hand-scheduled wavefronts:
 //   256 x 192, one workgroup of eight wavefronts (4 x 2, each a 64 x 96 block; two per SIMD cover each
@@ -77,26 +77,53 @@ inline float stream_cost(int bn, int N, int K, bool gelu, int rows, int n_seg)
 //     compute unit (few refreshed rows, or narrow outputs).  Alone on a compute unit a workgroup has nobody to hide its load
 //     latency, and the third stage gives every load two steps of flight instead of one
 //     (57 us instead of 78 us for GEMM2 at 4096 rows of the DiT-MoE-XL widths).
-// Tiny problems stay on the 128 x 128 kernel, three workgroups per compute unit.
+// and below that the small tiles as said beside their lines.  What fits none of them stays on the register-staged 128 x 128 kernel,
+// three workgroups per compute unit.
 //
 // Segments: up to 64, the tiles are dealt to the XCDs by expert (one L2 per XCD: an expert's weight slabs are then fetched by one
-// XCD); beyond, in bands of row tiles.
-inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, size_t partial_bytes)
+// XCD); beyond, in bands of row tiles.  n_experts: distinct weights at most.
+//
+// The lines between the tiles up to 128 rows were drawn from 2641 combinations of nine widths, 2 to 64 experts, 1 to 8 segments per
+// expert and 8 to 2048 rows per segment (graphs of calls with weights from memory, every tile that can run timed for either GEMM);
+// figures beside them are us, or % of the FFN.
+inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, int n_experts, size_t partial_bytes)
 {
     const bool by_expert = n_seg <= 64;
-    // expected tiles: every segment ends in a partial row tile, half a tile on average
-    auto tiles = [&](int bm, int bn) {
-        const long long m_tiles = (static_cast<long long>(max_rows) + static_cast<long long>(n_seg) * bm / 2 + bm - 1) / bm;
-        return m_tiles * ((N + bn - 1) / bn);
-    };
+    const long long rows = max_rows, segs = n_seg;
+    // expected tiles: every segment ends in a partial row tile, half a tile on average ...
+    auto row_tiles = [&](int bm) { return (rows + segs * bm / 2 + bm - 1) / bm; };
+    auto tiles = [&](int bm, int bn) { return row_tiles(bm) * ((N + bn - 1) / bn); };
+    // ... and, however few its rows, has one
+    auto all_tiles = [&](int bm, int bn) { return (row_tiles(bm) > segs ? row_tiles(bm) : segs) * ((N + bn - 1) / bn); };
     const bool fits_192 = (N + 191) / 192 * 192 * 8 <= N * 9;          // at most 1/8 of the columns computed in vain
     const bool fits_128 = (N + 127) / 128 * 128 * 8 <= N * 9;
-    const bool full_rows = max_rows >= 128 * n_seg;                    // (row tiles half full on average)
+    const bool full_rows = rows >= 128 * segs;                         // (row tiles half full on average)
     if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (gelu ? 96 : kComputeUnits + 1)) {
         const bool wide = !fits_192 || stream_cost(256, N, K, gelu, max_rows, n_seg) < stream_cost(192, N, K, gelu, max_rows, n_seg);
         return {wide ? FfnTile::Stream256 : FfnTile::Stream192, 1};
     }
-    const long long t64 = tiles(64, 128), t128 = tiles(128, 128), t192 = tiles(128, 192);
+    const long long t192 = tiles(128, 192);
+    if (gelu && by_expert && fits_128 && K >= 256) {
+        // Few rows per expert: 64 x 128 tiles, three stages in 72 KB of LDS, so that two workgroups share a compute unit and cover each
+        // other's waits, and a 64-row tile of a small expert is not half padding (128-row tiles / 64-row tiles: DiT-MoE-S, 38 rows an
+        // expert 15 / 12, 69: 16 / 14).  In one round of two per compute unit (a little more by the estimate: 384 x 1536, 32 experts, 528
+        // tiles - 12 %, 576 tiles + 11 %), but not for a long reduction that 128 x 192 tiles do in one round: those have 120 KB of loads
+        // in flight per compute unit, which cold weights need (DiT-MoE-XL, 256 tokens, whole layer 72.6 against 74.1).
+        const long long t64 = all_tiles(64, 128);
+        const bool one_round = t192 <= kComputeUnits && K >= 1024;
+        if (t64 <= 560 && rows <= 72 * segs && !one_round) return {FfnTile::Small64, 1};
+        // With so few rows that every segment has one tile also in two rounds that they nearly fill (1024 tiles: 512 x 2048, 64 experts - 8 %,
+        // 1024 x 4096, 32 segments - 5 %; 768 tiles: 384 x 1536, 64 experts + 6 %; in four and more, 1152 x 4608, 8 experts in 64 segments + 5 %).
+        if (t64 <= 1024 && 8 * t64 >= 7 * 1024 && rows <= 24 * segs && !one_round) return {FfnTile::Small64, 1};
+        // In several rounds where the weights are what the time goes to: 128 MB of them, at most K / 16 rows for each expert's, and few
+        // tiles altogether (DiT-MoE-G, 64 rows an expert: - 7 %, 96: - 1 %, 128: + 7 %; 1024 x 4096, 32 experts, 48: - 10 %, 96: 0; four
+        // experts of 1152 x 4608 in 16 or 32 segments + 2 to + 15 % at any number of rows).
+        const long long weights = (n_experts < n_seg ? n_experts : n_seg) * static_cast<long long>(K);      // x N
+        if (weights * N >= (1 << 26) && 16 * rows <= weights && rows * N <= 12 * (1 << 20) && rows <= 96 * segs && t64 >= 640 &&
+            t192 > kComputeUnits)
+            return {FfnTile::Small64, 1};
+        if (full_rows && tiles(64, 128) <= 2 * kComputeUnits) return {FfnTile::Small64, 1};
+    }
     // Few rows and a long reduction (the second GEMM after a small refresh fraction or for a small batch):
     // the 128 x 192 tiles do not fill the chip and each walks all of K.  With two or three workgroups per
     // tile, each on a share of K (float partial sums in the workspace, added by a second pass in a fixed
@@ -104,34 +131,35 @@ inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, s
     // widths.  Not worth it once the tiles fill the chip by themselves (57 vs 66 us at 4096 rows), nor when a
     // share is left with fewer than sixteen steps (DiT-MoE-S widths, K = 1536, 4096 rows: 32 us split in
     // three, 23 in two, 20 unsplit on three-stage tiles): the second pass then costs more than the split saves.
-    int shares = 1;                      // the deepest split whose shares still fill the chip at most once
-    if (!gelu && by_expert && fits_192)
-        for (int s = 3; s >= 2 && shares == 1; --s)
-            if (t192 * s * 20 <= kComputeUnits * 21 && K / 64 / s >= 16 &&
-                static_cast<size_t>(s) * max_rows * N * sizeof(float) <= partial_bytes)
-                shares = s;
-    // Few rows per expert, or few tiles altogether: 64 x 128 tiles, three stages in 72 KB of LDS, so that two workgroups share
-    // a compute unit and cover each other's waits, and a 64-row tile of a small expert is not half padding.
-    // First GEMM (us, 128-row tiles / 64-row tiles): up to 72 rows per expert, above that a second row tile
-    // reads the weights again (DiT-MoE-XL, 75 rows an expert 26 / 29.5, 88: 25.5 / 30): DiT-MoE-S, 38: 15 / 12, 69: 16 / 14;
-    // DiT-MoE-G, 16: 116 / 90, 64: 122 / 105; and up to 96 rows where the 128 x 192 tiles would take more than one round: DiT-MoE-G, 88:
-    // 121 / 116, 112: 123 / 129; expert-parallel widths, 88: 170 / 145.
-    // Second GEMM: while there is at most one tile per compute unit (128 x 192 tiles, K in two or three shares / 64-row tiles: DiT-MoE-XL,
-    // 900 rows 48 / 29.5, 1400 rows 42 / 34; DiT-MoE-S, 2000 rows 27 / 16; DiT-MoE-G, 256 rows 109 / 84); then 128 x 128 tiles
-    // up to seven eighths of that (a count beyond 256 is a second round: DiT-MoE-G, 1024 rows, 224 tiles 110 / 99; 1200 rows, 252 tiles
-    // 110 / 138), unless two shares of K on 128 x 192 tiles fill the chip (DiT-MoE-XL, 2000 rows: 45 split, 49 on 128 x 128).
-    if (by_expert && fits_128 && K >= 256) {
-        // (not for a long reduction that 128 x 192 tiles do in one round: those have 120 KB of loads in flight per compute unit, which
-        // cold weights need: whole layer, DiT-MoE-XL widths, 256 tokens, other weights in every pass, 72.6 us against 74.1)
-        const bool one_round = t192 <= kComputeUnits && K >= 1024;
-        const bool small_experts = (max_rows <= 72 * n_seg && !one_round) || (max_rows <= 96 * n_seg && t192 > kComputeUnits);
-        if (gelu && (small_experts || (full_rows && t64 <= 2 * kComputeUnits))) return {FfnTile::Small64, 1};
-        // (the same for the second GEMM in three shares of K on one 128-row tile per expert)
-        const bool three_shares = shares == 3 && max_rows <= 100 * n_seg;
-        if (!gelu && !three_shares && t64 <= kComputeUnits) return {FfnTile::Small64, 1};
-        if (!gelu && shares == 1 && 8 * t128 <= 7 * kComputeUnits) return {FfnTile::Small128, 1};
+    // Three shares of experts with more than 100 rows: only if they run in one round even when every segment ends in an empty tile
+    // and the second pass has little to add (two experts of 2048 x 8192, 500 rows, 64 x 128 / three shares 101 / 85; of 1152 x 4608,
+    // 968 rows 57 / 53, 1219 rows 64 / 73; DiT-MoE-XL, 900 rows 29.5 / 48).
+    int shares = 1;
+    if (!gelu && by_expert && fits_192) {
+        auto can = [&](int s, long long t) {
+            return t * s * 20 <= kComputeUnits * 21 && K / 64 / s >= 16 && static_cast<size_t>(s) * max_rows * N * sizeof(float) <= partial_bytes;
+        };
+        const long long worst = (rows + 128 * segs + 127) / 128 * ((N + 191) / 192);
+        if (can(3, t192) && (rows <= 100 * segs || (can(3, worst) && rows * N <= 1150000))) shares = 3;
+        else if (can(2, all_tiles(128, 192))) shares = 2;
+    }
+    if (!gelu && by_expert && fits_128 && K >= 256) {
+        // 64 x 128 tiles while there is at most one per compute unit (128 x 192 tiles, K in two shares / 64-row tiles: DiT-MoE-XL, 1400
+        // rows 42 / 34; DiT-MoE-S, 2000 rows 27 / 16; DiT-MoE-G, 256 rows 109 / 84); then 128 x 128 up to seven eighths of that (a count
+        // beyond 256 is a second round: DiT-MoE-G, 1024 rows, 224 tiles 110 / 99; 1200 rows, 252 tiles 110 / 138), unless two shares of K
+        // on 128 x 192 tiles fill the chip (DiT-MoE-XL, 2000 rows: 45 split, 49 on 128 x 128).
+        // Counted with a tile for every segment, except where 128 x 192 tiles do not fit the columns (640 x 2560, 8 experts in 64 segments
+        // of 12 rows, 320 tiles 79 us, register-staged 128 x 128 103) and, for the small ones, two of which share a compute unit, where
+        // segments share weights (1152 x 4608, 4 experts in 32 segments, 288 tiles 101, 128 x 192 104; with 32 experts 159 and 144).
+        const long long t64 = fits_192 && n_experts >= n_seg ? all_tiles(64, 128) : tiles(64, 128);
+        if (shares != 3 && t64 <= kComputeUnits) return {FfnTile::Small64, 1};
+        const long long t128 = fits_192 ? all_tiles(128, 128) : tiles(128, 128);
+        if (shares == 1 && 8 * tiles(128, 128) <= 7 * kComputeUnits && t128 <= kComputeUnits) return {FfnTile::Small128, 1};
     }
     if (shares > 1) return {FfnTile::Mid192Deep, shares};
+    // (many experts with few rows, one round of 128-row tiles: 1152 x 4608, 32 experts of 30 rows, 64 x 128 tiles 173, 256 x 192 160, these 146)
+    if (!gelu && fits_192 && K >= 256 && rows <= 48 * segs && all_tiles(128, 192) <= kComputeUnits && t192 * 4 >= kComputeUnits)
+        return {FfnTile::Mid192Deep, 1};
     if (!gelu && fits_192 && tiles(256, 192) * 10 >= kComputeUnits * 6) {
         if (K >= 320) return {FfnTile::Wide192W4, 1};      // (four weight stages: three steps of flight for the cold weight stream)
         return {K >= 256 ? FfnTile::Wide192W3 : FfnTile::Wide192, 1};

@@ -44,7 +44,7 @@ hipError_t launch_combine(bool bf16, const void* h_packed, const int32_t* inv, c
 // naming the row that packed row r reads; the h row of packed row r is written to row r of h_out, or
 // to row out_index[r] when out_index is given (scatter into a buffer indexed by pair id)
 hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_index, int row_div,
-                             const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows, int d,
+                             const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts, int max_rows, int d,
                              int F, const void* W1, const float* b1, const void* W2, const float* b2, void* h_out,
                              const int32_t* out_index, void* hidden, void* partial, size_t partial_bytes,
                              int32_t* status, hipStream_t stream, hipEvent_t between = nullptr);

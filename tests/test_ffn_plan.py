@@ -60,8 +60,8 @@ def test_every_tile_of_the_rule_is_run_by_a_case():
     widths = [64, 128, 192, 256, 320, 384, 448, 576, 768, 1024, 1152, 1536, 1792, 2048, 4608, 7168, 8192]
     rows = [int(2.0 ** (i / 2)) for i in range(0, 36)]
     reached = set()
-    for d, F, n_seg, R in itertools.product(widths, widths, (1, 2, 4, 8, 16, 32, 64, 80), rows):
-        first, second = P.ffn_plans(R, n_seg, d, F)
+    for d, F, n_seg, R, experts in itertools.product(widths, widths, (1, 2, 4, 8, 16, 32, 64, 80), rows, (2, 64)):
+        first, second = P.ffn_plans(R, n_seg, d, F, experts)
         reached |= {(0, first), (1, second)}
     run = set()
     cases = stream.CASES + [c for c in small.FFN_CASES if c[4] == "bf16"] + parity.WIDE_FFN_CASES
@@ -69,3 +69,20 @@ def test_every_tile_of_the_rule_is_run_by_a_case():
         first, second = P.ffn_plans(sum(c[1]), len(c[1]), c[2], c[3])
         run |= {(0, first), (1, second)}
     assert reached <= run, sorted(reached - run)
+
+
+@pytest.mark.parametrize("gelu,N,K,rows,n_seg,n_experts,tile", [
+    # second GEMM of a few experts: three shares of K while they run in one round and the second pass is short
+    (False, 2048, 8192, 500, 2, 2, "128x192deep/3"), (False, 1152, 4608, 968, 2, 2, "128x192deep/3"), (False, 1152, 4608, 1219, 2, 2, "64x128"),
+    (False, 1152, 4608, 900, 8, 8, "64x128"),
+    # many experts with few rows each: a tile for every one of them
+    (False, 1152, 4608, 960, 32, 32, "128x192deep"), (False, 1152, 4608, 960, 32, 4, "128x192deep"), (False, 640, 2560, 768, 64, 8, "64x128"),
+    # first GEMM in several rounds: small tiles only where cold weights are what the time goes to
+    (True, 7168, 1792, 1024, 16, 16, "64x128"), (True, 7168, 1792, 1900, 16, 16, "128x192"), (True, 2048, 512, 4864, 64, 64, "128x192"),
+    (True, 4096, 1024, 1536, 32, 32, "64x128"), (True, 4096, 1024, 4608, 64, 64, "128x192"),
+    (True, 4608, 1152, 992, 16, 4, "128x192"),
+    # ... or in whole rounds
+    (True, 4096, 1024, 768, 32, 8, "64x128"), (True, 4608, 1152, 1280, 64, 8, "128x192"), (True, 1536, 384, 1024, 64, 64, "128x192"),
+])
+def test_lines_between_the_small_tiles(gelu, N, K, rows, n_seg, n_experts, tile):
+    assert P.plan(gelu, N, K, rows, n_seg, n_experts) == tile
