@@ -24,12 +24,6 @@ __device__ __forceinline__ void wait_lgkmcnt() {
 
 #define DICEMOE_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-// Build-time timing aid (off in the library build): bit 0 drops the epilogue, bit 1 the stage loads,
-// bit 2 the fragment reads, bit 3 everything after the tile lookup.  Results are wrong with any bit set.
-#ifndef DICEMOE_FFN_DIAG
-#define DICEMOE_FFN_DIAG 0
-#endif
-
 // workgroups per compute unit that the LDS footprint allows (the register budget follows from it)
 constexpr int wide_occupancy(int tm, int tn, int ast, int wst, int wgm, int wgn) {
     return (ast * tm * wgm + wst * tn * wgn) * 32 * 128 <= 80 * 1024 ? 2 : 1;
@@ -43,9 +37,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
     const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index, int by_expert,
     float* __restrict__ partial, int partial_rows, int32_t* __restrict__ status)
 {
-#if DICEMOE_FFN_DIAG
-    constexpr int DIAG = DICEMOE_FFN_DIAG;
-#endif
     constexpr int NW = WGM * WGN;                  // wavefronts, WGM along the rows by WGN along the columns
     constexpr int BM = 32 * TM * WGM, BN = 32 * TN * WGN;
     constexpr int WM = 32 * TM, WN = 32 * TN;
@@ -87,12 +78,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
         if (tile_n >= n_tiles_n) return;
         if (!find_row_tile(seg_offsets, n_seg, BM, tile_m, seg, row0, row_end)) return;
     }
-#if DICEMOE_FFN_DIAG
-    if (DIAG & 8) {                                 // timing aid: the tile lookup alone
-        if (seg + row0 + row_end + tile_n == -12345) C[0] = 1;
-        return;
-    }
-#endif
     if (!by_expert) e = seg_expert[seg];
     const int n0 = tile_n * BN;
 
@@ -140,9 +125,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
     };
     // load i of a stage: i < QA belongs to the A operand (ring slot sa), the others to W (ring slot sw)
     auto dma = [&](int i, int sa, int sw, const char* a_k, const char* w_k) {
-#if DICEMOE_FFN_DIAG
-        if (DIAG & 2) return;
-#endif
         uint32_t off = goff[i];
         asm volatile("" : "+v"(off));          // keeps the zero extension next to the load (scalar base + 32-bit offset form)
         if (i < QA)
@@ -173,9 +155,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
 
     bf16x8_v fr[2][NFRAG];                           // [set][A fragments 0..TM-1, then W fragments]
     auto read_frag = [&](int set, int f, const char* sta, const char* stw, int kk) {
-#if DICEMOE_FFN_DIAG
-        if (DIAG & 4) return;
-#endif
         const char* p = f < TM ? sta + a_off[kk] + f * 4096 : stw + b_off[kk] + (f - TM) * 4096;
         const u32x4_v v = *reinterpret_cast<const u32x4_v*>(p);
         fr[set][f] = *reinterpret_cast<const bf16x8_v*>(&v);
@@ -218,15 +197,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
     block_barrier();
 #pragma unroll
     for (int f = 0; f < NFRAG; ++f) read_frag(0, f, a_lds, w_lds, 0);
-#if DICEMOE_FFN_DIAG
-    if (DIAG & 4) {
-#pragma unroll
-        for (int f = 0; f < NFRAG; ++f) {
-            const u32x4_v v = *reinterpret_cast<const u32x4_v*>(smem + (f < TM ? a_off[0] : b_off[0]) + (f % 4) * 4096);
-            fr[0][f] = fr[1][f] = *reinterpret_cast<const bf16x8_v*>(&v);
-        }
-    }
-#endif
 
     // One 64-deep step kt; its A stage sits in ring slot sa, its W stage in ring slot sw (the rings may
     // differ in depth: the W operand streams from HBM once and gains most from a third stage, the
@@ -389,19 +359,6 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
     wait_lgkmcnt<0>();
     block_barrier();
     if (!live) return;
-#if DICEMOE_FFN_DIAG
-    if (DIAG & 1) {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) s += acc[i][j][v];
-        if (s == 1234.5f) C[0] = 1;
-        return;
-    }
-#endif
     if (partial) {
         // raw sums of this share: lane (m, h) holds, per 32 x 32 block, columns 8g + 4h .. + 3 of row m
         float* dst = partial + static_cast<size_t>(blockIdx.y) * partial_rows * N;
