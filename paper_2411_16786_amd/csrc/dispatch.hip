@@ -32,6 +32,7 @@ constexpr int kIdxWaves = kIdxThreads / kWave;
 // (Durations of a kernel trace mislead here: about 2 us of each are a launch's own, which in a row of launches overlap.)  Up to 256
 // pairs four wavefronts do it: fewer to wait for at the barriers.
 constexpr int kAlonePairs = 4096;
+constexpr int kNoScratchPairs = 2048;         // (a promise of moe_dispatch: up to these the workspace may be null)
 
 // order this wavefront's LDS accesses: reads before the point complete before writes after it
 // are issued, and the compiler keeps them on their side
@@ -321,27 +322,23 @@ __global__ __launch_bounds__(256) void dispatch_gather_kernel(const T* __restric
     }
 }
 
-// Steps per wave and workgroups of the index kernels for N pairs, and with them the scratch that moe_dispatch asks for (nothing
-// up to 2048 pairs).  The fewest steps (1, 2, 4, 8) that keep the grid at 256 workgroups or fewer; beyond 2^19 pairs the grid
-// grows instead.
+// Steps per wave and workgroups of the counting and placing kernels for N pairs: the fewest steps (1, 2, 4, 8) that keep the grid
+// at 256 workgroups or fewer; beyond 2^19 pairs the grid grows instead.
 static void dispatch_plan(long long N, int& steps, int& blocks)
 {
     steps = 1;
-    if (N <= 8 * kIdxThreads) {
-        while (static_cast<long long>(kIdxThreads) * steps < N) steps *= 2;
-        blocks = 1;
-        return;
-    }
     while (steps < 8 && (N + static_cast<long long>(kIdxThreads) * steps - 1) / (kIdxThreads * steps) > 256) steps *= 2;
-    const long long b = (N + static_cast<long long>(kIdxThreads) * steps - 1) / (kIdxThreads * steps);
-    blocks = b > 0 ? static_cast<int>(b) : 1;
+    blocks = static_cast<int>((N + static_cast<long long>(kIdxThreads) * steps - 1) / (kIdxThreads * steps));
 }
 
+// Scratch that the entry points ask their callers for: a row per workgroup, and the totals.  None up to kNoScratchPairs; between those and
+// kAlonePairs it is asked for as ever, but not used.
 size_t dispatch_scratch_bytes(long long n_pairs, int E)
 {
+    if (n_pairs <= kNoScratchPairs) return 0;
     int steps, blocks;
     dispatch_plan(n_pairs, steps, blocks);
-    return blocks > 1 ? static_cast<size_t>(blocks + 1) * E * sizeof(int32_t) : 0;      // one row per workgroup, and the totals
+    return static_cast<size_t>(blocks + 1) * E * sizeof(int32_t);
 }
 
 template <int S>
@@ -349,8 +346,7 @@ static void launch_dispatch_index(const int32_t* idx, const uint8_t* mask, int N
                                   int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv, hipStream_t stream)
 {
     const int scan = blocks > 256 ? 1 : 0;      // small grids: every placing workgroup sums the table itself
-    if (blocks > 1)
-        hipLaunchKernelGGL(dispatch_count_kernel<S>, dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch);
+    hipLaunchKernelGGL(dispatch_count_kernel<S>, dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch);
     if (scan)
         hipLaunchKernelGGL(dispatch_scan_kernel, dim3(1), dim3(1024), 0, stream, scratch, blocks, E);
     hipLaunchKernelGGL((dispatch_place_kernel<S, kIdxThreads>), dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch,
@@ -371,9 +367,9 @@ hipError_t launch_dispatch(bool bf16, const void* x, const int32_t* idx, const u
                            int32_t* inv, int32_t* scratch, hipStream_t stream)
 {
     const int N = T_tok * k;
+    if (N > kNoScratchPairs && scratch == nullptr) return hipErrorInvalidValue;
     int steps, blocks;
     dispatch_plan(N, steps, blocks);
-    if (blocks > 1 && scratch == nullptr) return hipErrorInvalidValue;
     if (N <= kIdxThreads) launch_dispatch_alone<1, kIdxThreads>(idx, mask, N, E, counts, offsets, perm, inv, stream);
     else if (N <= 1024) launch_dispatch_alone<1, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
     else if (N <= 2048) launch_dispatch_alone<2, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);

@@ -74,7 +74,7 @@ def test_struct_layouts_match_the_header():
     (dict(T_max=64, d=60, F=256, E=4, k=2, dtype="f32"), B.MOE_ERR_SHAPE),       # d % 16
     (dict(T_max=64, d=96, F=256, E=4, k=2, dtype="bf16"), B.MOE_ERR_SHAPE),      # d % 64 for bf16
     (dict(T_max=-1, d=64, F=256, E=4, k=2, dtype="f32"), B.MOE_ERR_SHAPE),
-    (dict(T_max=64, d=4112, F=256, E=4, k=2, dtype="f32"), B.MOE_ERR_SHAPE),     # float rows wider than the router holds
+    (dict(T_max=64, d=4112, F=256, E=4, k=2, dtype="f32"), B.MOE_ERR_SHAPE),     # float rows beyond 4096 columns
     (dict(T_max=64, d=64, F=256, E=4, k=2, dtype="f32", n_shared=2), 0),
     (dict(T_max=64, d=64, F=256, E=4, k=2, dtype="f32", n_shared=-1), B.MOE_ERR_SHAPE),
     (dict(T_max=64, d=64, F=256, E=63, k=2, dtype="f32", n_shared=2), B.MOE_ERR_SHAPE),  # E + shared > 64
@@ -140,6 +140,9 @@ def test_host_detectable_errors_return_before_any_launch():
     assert L.moe_expert_ffn_commit(h, one, None, one, one, one, 4, 8, one, None, one, None, one, None, 8, one, one,
                                    None, None) == B.MOE_ERR_WORKSPACE
     assert L.moe_dispatch(h, None, one, None, 8, one, one, one, one, one, None, None) == B.MOE_ERR_NULL  # rows wanted, no x
+    big = B.Context(T_max=4096, d=64, F=256, E=4, k=2, dtype="f32")               # the sort asks for scratch beyond 2048 pairs
+    for T in (1025, 2048, 2049, 4096):
+        assert L.moe_dispatch(big._h, one, one, None, T, None, one, one, one, one, None, None) == B.MOE_ERR_WORKSPACE, T
     assert L.moe_ep_segments(h, one, 4, 8, one, one, None) == B.MOE_ERR_SHAPE     # E_loc > E
     # T = 0 launches nothing
     assert L.moe_gate(h, one, one, None, 0, one, one, None, None, None) == B.MOE_OK
