@@ -34,6 +34,8 @@ FFN_CASES = [
     ("f32-five-units", [31, 32, 33, 64], 80, 48, "f32"),
     ("f32-many-units", [17, 65, 1, 96], 208, 400, "f32"),
     ("f32-70-segments", [1, 33, 0, 7, 32, 2, 40] * 10, 48, 80, "f32"),             # the segment table exceeds 64 lanes
+    ("f32-1024-segments", [(g * 7) % 5 * (g % 3 != 1) + 70 * (g % 256 == 255) for g in range(1024)], 32, 48, "f32"),      # many of them empty
+    ("f32-65-segments", [0] * 64 + [33], 16, 16, "f32"),                           # the only rows beyond the lanes' first load
     ("f32-64x64-tiles", [639, 0, 64, 65, 127, 300, 1], 48, 2704, "f32"),           # first GEMM: 43 columns of tiles, the last a quarter full
     ("f32-64x64-second", [513, 448, 1], 2576, 48, "f32"),                          # second GEMM, three units for four shares
     ("f32-64x64-70-segments", [300, 2, 64, 0, 130, 65, 200] * 10, 16, 336, "f32"), # more segments than lanes, one unit of K
@@ -126,7 +128,7 @@ def test_float_gate(d, E, k):
 
 
 @pytest.mark.parametrize("d,E,k,T", [
-    (1024, 2, 1, 33), (1040, 1, 1, 9), (1040, 2, 2, 33), (2048, 4, 2, 1), (2064, 4, 3, 8), (4096, 3, 2, 19),   # few experts, long rows
+    (1024, 2, 1, 33), (1040, 1, 1, 9), (1040, 2, 2, 33), (2048, 4, 2, 1), (2064, 4, 3, 8), (4096, 4, 2, 19),   # few experts, long rows
     (1040, 4, 2, 6144), (1040, 4, 2, 6145), (1040, 2, 2, 6145),                                                # on both sides of the line
     (1040, 5, 2, 33), (448, 8, 2, 33), (1152, 8, 2, 33)])                                                      # batches of four k-steps
 @pytest.mark.parametrize("renorm,n_shared", [(False, 2), (True, 0)])
