@@ -328,7 +328,8 @@ int moe_dispatch_noalloc(moe_ctx* ctx, const void* x, const int32_t* expert_idx,
 static int expert_ffn_common(moe_ctx* ctx, const char* who, const void* x_rows, const int32_t* row_pairs,
                              const int32_t* seg_offsets, const int32_t* seg_expert, int32_t n_segments,
                              int32_t max_rows, const void* W1, const float* b1, const void* W2, const float* b2,
-                             void* h_packed, const int32_t* out_pairs, void* workspace, void* stream)
+                             void* h_packed, const int32_t* out_pairs, void* workspace, void* stream,
+                             dicemoe::SplitSums* sums = nullptr)
 {
     const moe_shape& s = ctx->shape;
     if (int rc = check_ffn(ctx, who, x_rows, seg_offsets, seg_expert, n_segments, max_rows, W1, W2, h_packed, workspace)) return rc;
@@ -347,7 +348,7 @@ static int expert_ffn_common(moe_ctx* ctx, const char* who, const void* x_rows, 
                                         is_bf16(ctx) ? ws + status_offset(ctx) - dicemoe::kSplitKBytes : nullptr,
                                         is_bf16(ctx) ? dicemoe::kSplitKBytes : 0,
                                         reinterpret_cast<int32_t*>(ws + status_offset(ctx)), static_cast<hipStream_t>(stream),
-                                        ctx->ffn_between),
+                                        ctx->ffn_between, sums),
                       who);
 }
 
@@ -475,19 +476,21 @@ int moe_layer_forward(moe_ctx* ctx, const moe_layer_args* a, const moe_policy* p
     if (int rc = moe_dispatch(ctx, a->x, a->expert_idx, mask, a->T, fuse ? nullptr : a->x_packed, a->counts, a->offsets, a->perm,
                               a->inv, a->workspace, stream))
         return rc;
-    int rc;
-    if (to_cache)
-        rc = moe_expert_ffn_commit(ctx, a->x, a->perm, a->perm, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2,
-                                   a->b2, nullptr, mask, a->T, a->H_cache, nullptr, a->workspace, stream);
-    else if (fuse)
-        rc = moe_expert_ffn_rows(ctx, a->x, a->perm, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2, a->b2,
-                                 a->h_packed, a->workspace, stream);
-    else
-        rc = moe_expert_ffn(ctx, a->x_packed, a->offsets, a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2, a->b2,
-                            a->h_packed, a->workspace, stream);
-    if (rc) return rc;
-    return moe_combine(ctx, h_packed, a->inv, a->scores, mask, a->T, H_cache, S_cache, policy ? policy->use_fresh_scores : 0, a->y,
-                       stream);
+    // packed rows (read by token through perm, or from the send buffer) -> h rows, in h_packed or at their pairs' places in the
+    // cache.  A split second GEMM leaves its float shares to the combine.
+    dicemoe::SplitSums sums;
+    const bool can_add = is_bf16(ctx) && slots(ctx) <= dicemoe::kSumsMaxSlots && a->n_segments == experts(ctx);
+    if (int rc = expert_ffn_common(ctx, "moe_layer_forward", fuse ? a->x : a->x_packed, fuse ? a->perm : nullptr, a->offsets,
+                                   a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2, a->b2, to_cache ? H_cache : h_packed,
+                                   to_cache ? a->perm : nullptr, a->workspace, stream, can_add ? &sums : nullptr))
+        return rc;
+    const int use_fresh = policy && policy->use_fresh_scores ? 1 : 0;
+    if (sums.shares > 1)
+        return hip_result(ctx,
+                          launch_combine_sums(sums, h_packed, a->inv, a->scores, a->expert_idx, a->seg_expert, mask, a->T, ctx->shape.d, slots(ctx),
+                                              ctx->shape.k, H_cache, S_cache, use_fresh, a->y, static_cast<hipStream_t>(stream)),
+                          "moe_layer_forward");
+    return moe_combine(ctx, h_packed, a->inv, a->scores, mask, a->T, H_cache, S_cache, use_fresh, a->y, stream);
 }
 
 int moe_ep_segments(moe_ctx* ctx, const int32_t* recv_counts, int32_t W, int32_t E_loc, int32_t* seg_offsets,

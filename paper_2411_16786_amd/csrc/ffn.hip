@@ -268,7 +268,7 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
                                         const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts,
                                         int max_rows, hipStream_t stream, const int32_t* row_index = nullptr,
                                         int row_div = 1, const int32_t* out_index = nullptr, float* partial = nullptr,
-                                        size_t partial_bytes = 0, int32_t* status = nullptr)
+                                        size_t partial_bytes = 0, int32_t* status = nullptr, SplitSums* sums = nullptr)
 {
     const int by_expert = n_seg <= 64 ? 1 : 0;
     const FfnPlan plan = plan_ffn_gemm(GELU, N, K, max_rows, n_seg, n_experts, partial ? partial_bytes : 0);
@@ -290,6 +290,10 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
                 const hipError_t err = launch_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg,
                                                                                  max_rows, stream, row_index, row_div, nullptr,
                                                                                  by_expert, partial, plan.shares, status);
+                if (sums) {
+                    *sums = SplitSums{partial, plan.shares, max_rows, bias};
+                    return err;
+                }
                 return err != hipSuccess ? err : launch_splitk_reduce(partial, plan.shares, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
             }
         }
@@ -342,7 +346,7 @@ hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_i
                              const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts, int max_rows, int d,
                              int F, const void* W1, const float* b1, const void* W2, const float* b2, void* h_packed,
                              const int32_t* out_index, void* hidden, void* partial, size_t partial_bytes,
-                             int32_t* status, hipStream_t stream, hipEvent_t between)
+                             int32_t* status, hipStream_t stream, hipEvent_t between, SplitSums* sums)
 {
     if (max_rows == 0) return launch_row_overflow_check(status, seg_offsets, n_seg, stream);
     hipError_t err;
@@ -352,7 +356,7 @@ hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_i
         if (err != hipSuccess) return err;
         if (between != nullptr && (err = hipEventRecord(between, stream)) != hipSuccess) return err;
         return launch_gemm_bf16_auto<false>(hidden, W2, b2, h_packed, d, F, seg_offsets, seg_expert, n_seg, n_experts, max_rows, stream,
-                                            nullptr, 1, out_index, static_cast<float*>(partial), partial_bytes);
+                                            nullptr, 1, out_index, static_cast<float*>(partial), partial_bytes, nullptr, sums);
     }
     err = launch_gemm_f32<true>(x_rows, W1, b1, hidden, F, d, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,
                                 row_div, nullptr, status);

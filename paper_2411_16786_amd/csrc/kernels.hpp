@@ -40,6 +40,17 @@ hipError_t launch_combine(bool bf16, const void* h_packed, const int32_t* inv, c
                           const uint8_t* mask, int T_tok, int d, int k, int k_cached, void* H_cache,
                           float* S_cache, int use_fresh, void* y, hipStream_t stream);
 
+// Float partial sums that a split second GEMM has left in the workspace for the combine: row r of share i is
+// partial[(i * rows + r) * d ..], and h row r = bf16(share 0 + share 1 + ... + bias of its expert).
+struct SplitSums { const float* partial = nullptr; int shares = 0, rows = 0; const float* bias = nullptr; };
+constexpr int kSumsMaxSlots = 4;
+// The combine that adds the shares itself (bf16, k <= kSumsMaxSlots slots per token): every fresh row goes to h_packed (its
+// packed row) or, where that is null, to its place in H_cache, as the second pass of the split would have put it, and y, H_cache and
+// S_cache receive what launch_combine writes.  idx: segment of every pair, seg_expert: whose weights that segment has.
+hipError_t launch_combine_sums(const SplitSums& sums, void* h_packed, const int32_t* inv, const float* scores, const int32_t* idx,
+                               const int32_t* seg_expert, const uint8_t* mask, int T_tok, int d, int k, int k_cached, void* H_cache, float* S_cache,
+                               int use_fresh, void* y, hipStream_t stream);
+
 // x_rows is the packed buffer (row_index == nullptr) or the token matrix with row_index[r] / row_div
 // naming the row that packed row r reads; the h row of packed row r is written to row r of h_out, or
 // to row out_index[r] when out_index is given (scatter into a buffer indexed by pair id)
@@ -47,7 +58,9 @@ hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_i
                              const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts, int max_rows, int d,
                              int F, const void* W1, const float* b1, const void* W2, const float* b2, void* h_out,
                              const int32_t* out_index, void* hidden, void* partial, size_t partial_bytes,
-                             int32_t* status, hipStream_t stream, hipEvent_t between = nullptr);
+                             int32_t* status, hipStream_t stream, hipEvent_t between = nullptr, SplitSums* sums = nullptr);
+// sums: if given and the second GEMM is split, its second pass is left to launch_combine_sums and *sums says what to add (h_out and
+// out_index are then not used); otherwise sums->shares stays 0
 // between: if given, recorded on the stream after the first GEMM has been enqueued (per-GEMM timing)
 // status (two int32 on the device, may be null): written by the first GEMM of every call, see
 // report_row_overflow in ffn_mfma.hpp.

@@ -1,0 +1,80 @@
+"""A layer whose second GEMM is split over K: its combine adds the float shares itself.  Same bits as the separate entry points (whose
+second pass adds them), in every buffer the layer leaves behind, for two and three shares, one to four slots, widths that do not fill the
+last wavefront, biases or none, and rows that go to the packed buffer, to the cache, or to both."""
+import pytest
+import torch
+
+from paper_2411_16786_amd import binding as B
+
+import gpu_util as G
+import plan_util as P
+
+CASES = [
+    # (T, T_max, d, F, E, k, n_shared, shares of the second GEMM when every pair is computed)
+    (61, 70, 192, 3072, 4, 2, 0, 3),
+    (40, 40, 1152, 3072, 8, 1, 0, 3),
+    (90, 101, 1344, 3072, 5, 4, 0, 3),
+    (30, 33, 576, 3072, 3, 2, 2, 3),          # two shared experts: four slots
+    (30, 30, 576, 3072, 3, 3, 2, 3),          # five slots: more than the combine takes, the second pass adds
+    (800, 800, 1152, 2048, 8, 2, 0, 2),
+    (1200, 1201, 576, 2048, 9, 3, 0, 2),
+]
+HALF = [None, (B.REFRESH_ALL, 0), (B.REFRESH_ALG4, 0), (B.REFRESH_FRACTION_PAIR, 7)]
+
+
+def test_the_second_gemm_is_split():
+    for T, _, d, F, E, k, ns, shares in CASES:
+        assert P.ffn_plans(T * (k + ns), E + ns, d, F)[1] == f"128x192deep/{shares}"
+
+
+def separate_calls(ctx, buf, x, Wg, bg, w, policy, fuse, to_cache):
+    T = x.shape[0]
+    rows = T * ctx.slots if policy is None else ctx.moe_policy_refreshed_pairs(policy, T)[0]
+    ctx.moe_gate(x, Wg, bg, buf.scores[:T], buf.expert_idx[:T])
+    mask = None
+    if policy is not None:
+        mask = buf.mask[:T]
+        ctx.moe_conditional_refresh(buf.scores[:T], buf.expert_idx[:T], policy, mask, buf.n_refresh, buf.workspace)
+    ctx.moe_dispatch(x, buf.expert_idx[:T], mask, None if fuse else buf.x_packed, buf.counts, buf.offsets, buf.perm, buf.inv, buf.workspace)
+    if to_cache:
+        ctx.moe_expert_ffn_commit(x, buf.perm, buf.perm, buf.offsets, buf.seg_expert, rows, *w, None, mask, buf.H_cache, None, buf.workspace, T=T)
+    elif fuse:
+        ctx.moe_expert_ffn_rows(x, buf.perm, buf.offsets, buf.seg_expert, rows, *w, buf.h_packed, buf.workspace)
+    else:
+        ctx.moe_expert_ffn(buf.x_packed, buf.offsets, buf.seg_expert, rows, *w, buf.h_packed, buf.workspace)
+    ctx.moe_combine(None if to_cache else buf.h_packed, buf.inv, buf.scores[:T], mask, buf.H_cache, buf.S_cache,
+                    policy is not None and policy.use_fresh_scores, buf.y[:T])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(CASES)))
+@pytest.mark.parametrize("kind", range(len(HALF)))
+def test_combine_adds_the_shares(case, kind):
+    T, T_max, d, F, E, k, ns, _ = CASES[case]
+    if kind >= 2 and T > 100:
+        pytest.skip("the refreshed rows of these sizes are not split")
+    print(f"\nshares case {case} policy {kind}", flush=True)
+    x, Wg, bg, *_ = G.small_inputs(91 + case, T, d, E, 64, "bf16")
+    gen = torch.Generator(device=G.DEV).manual_seed(case)
+    normal = lambda *s: torch.randn(s, generator=gen, device=G.DEV) * 0.05
+    W1, W2 = normal(E + ns, F, d).bfloat16(), normal(E + ns, d, F).bfloat16()
+    b1, b2 = (None, None) if case % 3 == 1 else (normal(E + ns, F), normal(E + ns, d))
+    x, Wg, bg = G.to_dev(x, "bf16"), G.to_dev(Wg, "bf16"), G.f32_dev(bg)
+    policy = None if HALF[kind] is None else B.Policy(HALF[kind][0], step_t=1, stride_n=2, n_units=T * k // 2 + HALF[kind][1],
+                                                      use_fresh_scores=case % 2 == 1)
+    for to_cache in ([False] if policy is None or ns else [True, False]):
+        for fuse in [True] if to_cache else [True, False]:
+            ctx = B.Context(T_max, d, F, E, k, "bf16", n_shared=ns)
+            a, b = (B.LayerBuffers(ctx, G.DEV, with_cache=policy is not None) for _ in range(2))
+            for buf in (a, b):
+                buf.y.fill_(3.0)
+                if policy is not None:
+                    buf.H_cache.copy_(torch.linspace(-1, 1, buf.H_cache.numel(), device=G.DEV).view_as(buf.H_cache))
+                    buf.S_cache.fill_(0.25)
+            B.moe_layer_forward(ctx, a, x, Wg, bg, W1, b1, W2, b2, policy, fuse_gather=fuse, rows_to_cache=to_cache)
+            separate_calls(ctx, b, x, Wg, bg, (W1, b1, W2, b2), policy, fuse, to_cache)
+            torch.cuda.synchronize()
+            for name in ("y", "H_cache", "S_cache", "h_packed", "x_packed"):
+                p, q = getattr(a, name), getattr(b, name)
+                assert p is None or torch.equal(p, q), (name, to_cache, fuse)
+            assert torch.isfinite(a.y[:T].float()).all() and a.y[:T].float().abs().sum() > 0
