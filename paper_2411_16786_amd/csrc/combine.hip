@@ -281,11 +281,14 @@ hipError_t launch_combine_sums(const SplitSums& sums, void* h_packed, const int3
     if (k > kSumsMaxSlots || sums.shares < 2 || sums.shares > 3) return hipErrorInvalidValue;
     const int n_chunks = (d / 8 + kWave - 1) / kWave;
     const long long blocks = (static_cast<long long>(T_tok) * n_chunks + 3) / 4;
-#define DICEMOE_SUMS(KK_, S_)                                                                                                         hipLaunchKernelGGL((combine_sums_kernel<KK_, S_>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, sums,                                  static_cast<u32x4_t*>(h_packed), inv, scores, idx, seg_expert, mask, T_tok, d, n_chunks, k_cached,                                            static_cast<u32x4_t*>(H_cache), S_cache, use_fresh, static_cast<u32x4_t*>(y))
-#define DICEMOE_SUMS_K(KK_)                       \
-    do {                                          \
+#define DICEMOE_SUMS(KK_, S_)                                                                                           \
+    hipLaunchKernelGGL((combine_sums_kernel<KK_, S_>), dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, sums, \
+                       static_cast<u32x4_t*>(h_packed), inv, scores, idx, seg_expert, mask, T_tok, d, n_chunks,         \
+                       k_cached, static_cast<u32x4_t*>(H_cache), S_cache, use_fresh, static_cast<u32x4_t*>(y))
+#define DICEMOE_SUMS_K(KK_)                         \
+    do {                                            \
         if (sums.shares == 2) DICEMOE_SUMS(KK_, 2); \
-        else DICEMOE_SUMS(KK_, 3);                \
+        else DICEMOE_SUMS(KK_, 3);                  \
     } while (0)
     if (k == 1) DICEMOE_SUMS_K(1);
     else if (k == 2) DICEMOE_SUMS_K(2);
