@@ -339,6 +339,10 @@ hipError_t prepare_expert_ffn()
 {
     hipError_t err = configure_gemm_bf16_auto<true>();
     if (err == hipSuccess) err = configure_gemm_bf16_auto<false>();
+    if (err == hipSuccess) err = configure_gemm_f32_ring<true, 2, 2, 2>();
+    if (err == hipSuccess) err = configure_gemm_f32_ring<false, 2, 2, 2>();
+    if (err == hipSuccess) err = configure_gemm_f32_ring<true, 4, 4, 2>();
+    if (err == hipSuccess) err = configure_gemm_f32_ring<false, 4, 4, 2>();
     return err;
 }
 

@@ -204,7 +204,259 @@ static hipError_t launch_gemm_f32_tile(const float* A, const float* W, const flo
     return hipGetLastError();
 }
 
-// 64 x 64 tiles once they fill two and a half rounds of the 256 compute units and the experts have rows for one and a half of them
+// The ring kernel.  What bounds the kernel above at some tens of rows per expert (DiT-MoE-S widths, 500 tokens: time stamps per workgroup):
+// loads into registers hold a line of the 32 KB vector cache each while they are in flight, so that a compute unit has 32 KB of cold
+// weights on their way at most, and every workgroup waits for segment table, row indices and first loads in turn (8 of its 17 us).  Here
+//   * operands go to LDS directly (a row's whole 128-byte line per eight lanes), into a ring of D stages that each wavefront has to
+//     itself: no barrier in the main loop, because no wavefront reads what another one loaded;
+//   * a wavefront still has a quarter of K, and the quarters meet in LDS in wavefront order: the same bits as above;
+//   * the workgroups that fit the chip walk a list of tiles each, and the rings run on across tiles: row indices, biases and output
+//     rows come through LDS as well, so that no load into a register makes the wavefront wait for the loads behind it.
+// 32 x 32 tiles, two stages, two workgroups per compute unit (one multiplies while the other one's sums meet): three or four stages and one
+// workgroup are slower, also with 32 x 64 tiles (500 tokens of DiT-MoE-S, both GEMMs: 66.6 us above; 55.1; 66.5 four stages; 57.2
+// 32 x 64 in three).  64 x 64 tiles, two stages, one workgroup, move half the bytes per flop and are better once they fill the chip.
+// What bounds it now is the way into LDS: 10 TB/s of stage loads where L2 misses keep 64 to 128 KB per compute unit in flight for
+// about 2 us, as in the bf16 kernels.  Both GEMMs, us, above / here: DiT-MoE-S, 18 tokens top-3 30.5 / 26.8, 2000 tokens 179 / 139, 8192: 508 / 480;
+// DiT-MoE-XL, 100 tokens 157 / 103, 2000: 984 / 880; 2048 x 8192, 4 experts, 200 tokens 458 / 309.
+// K is a multiple of 128 (equal shares of whole stages) and at least kRingMinK (two stages a share).
+constexpr int kRingMinK = 256;
+constexpr int ring_lds(int tm, int tn, int d) { return kDirectShares * (d * 16 * (tm + tn) * 128 + (kDirectShares - 1) * 1024 + 768); }
+template <bool GELU, int TM, int TN, int D>
+__global__ __launch_bounds__(64 * kDirectShares, ring_lds(TM, TN, D) <= 80 * 1024 ? 2 : 1) void ffn_gemm_f32_ring_kernel(
+    const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias, float* __restrict__ C, int N, int K,
+    const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert, int n_seg, int n_tiles_n,
+    const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index, int max_rows,
+    int32_t* __restrict__ status)
+{
+    typedef RowMfma<float> M;
+    constexpr int KS = kDirectShares;
+    constexpr int BM = 16 * TM, BN = 16 * TN;
+    constexpr int QA = BM / 8, QB = BN / 8, Q = QA + QB;  // loads of a stage: eight rows each
+    constexpr int STAGE = (BM + BN) * 128;
+    constexpr int CH = 8;
+    static_assert(32 * KS * D <= kRingMinK, "a share of K has D stages at least: what is asked for a tile ahead has landed by then");
+    static_assert(TM * TN % KS == 0 && BN <= 64 && BM <= 64, "blocks for every wavefront; a lane each for a tile's columns and rows");
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    report_row_overflow(status, seg_offsets, n_seg, max_rows);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int sub = lane & 15, quarter = lane >> 4;
+    char* const ring = smem + wave * D * STAGE;
+    f32x4_t* const meet = reinterpret_cast<f32x4_t*>(smem + KS * D * STAGE);      // [KS][KS - 1][64]
+    char* const aux = smem + KS * D * STAGE + KS * (KS - 1) * 1024 + wave * 768;
+    int32_t* const rows_lds = reinterpret_cast<int32_t*>(aux);                    // row indices of the tile that the ring goes on to
+    int32_t* const dst_lds = reinterpret_cast<int32_t*>(aux + 256);               // output rows and biases of the tile that is multiplied
+    float* const bias_lds = reinterpret_cast<float*>(aux + 512);
+
+    XcdTiles tiles;
+    tiles.deal(seg_offsets, seg_expert, n_seg, BM, BN, n_tiles_n, blockIdx.x & 7, max_rows);
+    const int slot = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
+    const int n_items = tiles.count > slot ? (tiles.count - slot + n_slots - 1) / n_slots : 0;
+    if (n_items == 0) return;
+
+    // ---- this wavefront's stages of K, 32 values each
+    const int n = K / (32 * KS), s0 = n * wave;
+
+    struct Item { int row0, row_end, n0, e; };
+    auto locate = [&](int i) {
+        Item t;
+        tiles.locate(slot + i * n_slots, t.row0, t.row_end, t.n0, t.e);
+        return t;
+    };
+    // 64 values of an array to LDS, lane l's from index `at` of its own
+    auto to_lds = [&](const void* array, int at, void* lds) {
+        __builtin_amdgcn_global_load_lds(DICEMOE_GLOBAL_PTR(reinterpret_cast<const char*>(array) + static_cast<size_t>(at) * 4), DICEMOE_LDS_PTR(lds), 4, 0, 0);
+    };
+    auto row_of = [&](const Item& t, int i) { return t.row0 + i < t.row_end ? t.row0 + i : t.row_end - 1; };      // (rows past the end repeat the last one)
+    auto ask_rows = [&](const Item& t) {
+        if (row_index) to_lds(row_index, row_of(t, lane), rows_lds);
+    };
+    // Load q of a stage fills rows 8q .. 8q + 7; lane l lands at LDS slot (row 8q + l / 8, l % 8) and fetches the chunk that the swizzle
+    // assigns to it.
+    const char* a_src[QA];
+    const char* w_src[QB];
+    auto sources = [&](const Item& t) {                  // its row indices have landed
+#pragma unroll
+        for (int q = 0; q < QA; ++q) {
+            const int i = 8 * q + (lane >> 3);
+            const int r = row_index ? rows_lds[i] / row_div : row_of(t, i);
+            a_src[q] = reinterpret_cast<const char*>(A + static_cast<size_t>(r) * K + s0 * 32) + ((lane & 7) ^ chunk_swizzle<CH>(i)) * 16;
+        }
+#pragma unroll
+        for (int q = 0; q < QB; ++q) {
+            const int i = 8 * q + (lane >> 3);
+            const int c = t.n0 + i < N ? t.n0 + i : N - 1;
+            w_src[q] = reinterpret_cast<const char*>(W + (static_cast<size_t>(t.e) * N + c) * K + s0 * 32) + ((lane & 7) ^ chunk_swizzle<CH>(i)) * 16;
+        }
+    };
+    auto load = [&](int q, int to, int s) {              // load q of stage s of this wavefront's share
+        const char* src = (q < QA ? a_src[q < QA ? q : 0] : w_src[q < QA ? 0 : q - QA]) + s * 128;
+        __builtin_amdgcn_global_load_lds(DICEMOE_GLOBAL_PTR(src), DICEMOE_LDS_PTR(ring + to * STAGE + q * 1024), 16, 0, 0);
+    };
+    int f_off[2];                                        // of 16-row block 0 in a stage; blocks are 2 KB apart (same swizzle)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) f_off[h] = (sub * CH + ((4 * h + quarter) ^ chunk_swizzle<CH>(sub))) * 16;
+    u32x4_t fr[2][TM + TN];
+    auto read = [&](int h, int from) {
+#pragma unroll
+        for (int f = 0; f < TM + TN; ++f) fr[h][f] = *reinterpret_cast<const u32x4_t*>(ring + from * STAGE + f * 2048 + f_off[h]);
+    };
+
+    // ---- the ring's end: stage `is` of item `ii`; `ahead` is the item behind it, whose row indices have been asked for
+    auto landed = [] {                                   // (LDS is read behind the wait, not before it)
+        asm volatile("" ::: "memory");
+        DICEMOE_SCHED_FENCE();
+    };
+    const int total = n_items * n;
+    int is = 0, ii = 0, issued = 0;
+    Item cur = locate(0), nxt = n_items > 1 ? locate(1) : cur, ahead = nxt;
+    ask_rows(cur);
+    wait_vmcnt<0>();
+    landed();
+    sources(cur);
+    wait_lgkmcnt<0>();
+    ask_rows(ahead);
+    auto issued_one = [&] {                              // behind the loads of stage `is`
+        ++issued;
+        if (++is == n) {
+            // (n - 1) Q loads were issued behind the row indices before the last wait for a stage, which left (D - 1) Q
+            is = 0;
+            ++ii;
+            sources(ahead);
+            wait_lgkmcnt<0>();
+            if (ii + 1 < n_items) ahead = locate(ii + 1);
+            ask_rows(ahead);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+        if (issued < total) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) load(q, s, is);
+            if (is == n - 1) { wait_vmcnt<0>(); landed(); }      // (the row indices of the next tile: no wait for a stage so far)
+            issued_one();
+        }
+    }
+    int at = 0, seq = 0;
+    if (issued == D) wait_vmcnt<(D - 1) * Q>(); else wait_vmcnt<0>();
+    landed();
+    read(0, 0);
+    wait_lgkmcnt<0>();
+    for (int it = 0; it < n_items; ++it) {
+        f32x4_t acc[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        if (out_index) to_lds(out_index, row_of(cur, lane), dst_lds);
+        if (bias) to_lds(bias, cur.e * N + (cur.n0 + lane < N ? cur.n0 + lane : N - 1), bias_lds);
+        const int live = (cur.row_end - cur.row0 + 15) / 16;      // 16-row blocks that have rows
+        auto multiply = [&](int h) {                     // products of half h of a stage
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (i == 0 || i < live) {
+#pragma unroll
+                    for (int t = 0; t < M::kMfma; ++t)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j) acc[i][j] = M::step(fr[h][TM + j], fr[h][i], acc[i][j], t);
+                }
+            }
+        };
+        for (int s = 0; s < n; ++s) {
+            DICEMOE_SCHED_FENCE();
+            read(1, at);
+            DICEMOE_SCHED_FENCE();
+            multiply(0);
+            DICEMOE_SCHED_FENCE();
+            wait_lgkmcnt<0>();                           // this stage is in registers: its slot can be filled again
+            const int here = at;
+            at = at + 1 == D ? 0 : at + 1;
+            ++seq;
+            // (all loads of the refill at once: spread over the products of the second half they cost 5 - 9 us of 55)
+            if (issued < total) {
+#pragma unroll
+                for (int q = 0; q < Q; ++q) load(q, here, is);
+                issued_one();
+            }
+            if (issued - seq >= D) wait_vmcnt<(D - 1) * Q>(); else wait_vmcnt<0>();      // the next stage has landed
+            landed();
+            if (seq < total) read(0, at);
+            DICEMOE_SCHED_FENCE();
+            multiply(1);
+            DICEMOE_SCHED_FENCE();
+            wait_lgkmcnt<0>();
+        }
+        // ---- the partial sums meet, KS blocks at a time; wavefront w finishes the w-th of them.  Biases and output rows have landed: they
+        // were asked for n stages ago
+#pragma unroll
+        for (int b0 = 0; b0 < TM * TN; b0 += KS) {
+            f32x4_t own = acc[b0 / TN][b0 % TN];
+#pragma unroll
+            for (int j = 0; j < KS; ++j) {
+                const int b = b0 + j;
+                if (j == wave) own = acc[b / TN][b % TN];
+                else meet[(wave * (KS - 1) + (j > wave ? j - 1 : j)) * 64 + lane] = acc[b / TN][b % TN];
+            }
+            wait_lgkmcnt<0>();
+            block_barrier();
+            f32x4_t part[KS];                            // (this wavefront's own share never went through LDS; some other one is read in its place)
+#pragma unroll
+            for (int w = 0; w < KS; ++w) part[w] = meet[(w * (KS - 1) + (wave > w ? wave - 1 : (wave < w ? wave : 0))) * 64 + lane];
+            f32x4_t sum = wave == 0 ? own : part[0];
+#pragma unroll
+            for (int w = 1; w < KS; ++w) sum += wave == w ? own : part[w];
+            const int i = (b0 + wave) / TN, c_in = 16 * ((b0 + wave) % TN) + 4 * quarter, c = cur.n0 + c_in;
+            f32x4_t b = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            if (bias) b = *reinterpret_cast<const f32x4_t*>(bias_lds + c_in);
+            const int r = cur.row0 + 16 * i + sub;
+            const int dst = r < cur.row_end ? (out_index ? dst_lds[16 * i + sub] : r) : -1;
+            wait_lgkmcnt<0>();
+            block_barrier();
+            if (dst >= 0 && c < N) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    sum[t] += b[t];
+                    if (GELU) sum[t] = gelu_erf(sum[t]);
+                }
+                *reinterpret_cast<f32x4_t*>(C + static_cast<size_t>(dst) * N + c) = sum;
+            }
+        }
+        cur = nxt;
+        if (it + 2 < n_items) nxt = locate(it + 2);
+    }
+}
+
+template <bool GELU, int TM, int TN, int D>
+static hipError_t configure_gemm_f32_ring()
+{
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm_f32_ring_kernel<GELU, TM, TN, D>), hipFuncAttributeMaxDynamicSharedMemorySize, ring_lds(TM, TN, D));
+}
+
+template <bool GELU, int TM, int TN, int D>
+static hipError_t launch_gemm_f32_ring(const float* A, const float* W, const float* bias, float* C, int N, int K,
+                                       const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
+                                       hipStream_t stream, const int32_t* row_index, int row_div, const int32_t* out_index,
+                                       int32_t* status)
+{
+    constexpr int BN = 16 * TN, smem = ring_lds(TM, TN, D);
+    static_assert(smem <= 160 * 1024, "the rings and the meeting place fit a compute unit's LDS");
+    hipLaunchKernelGGL((ffn_gemm_f32_ring_kernel<GELU, TM, TN, D>), dim3(kStreamGrid * (smem <= 80 * 1024 ? 2 : 1)), dim3(64 * kDirectShares), smem, stream, A, W, bias, C, N, K,
+                       seg_offsets, seg_expert, n_seg, (N + BN - 1) / BN, row_index, row_div, out_index, max_rows, status);
+    return hipGetLastError();
+}
+
+// 64 x 64 tiles on the ring kernel.  Short reductions (K < 1536), from four rounds on: one GEMM, us against 32 x 32, DiT-MoE-XL, 850 tiles + 11,
+// 1413: - 11, 2520: - 55; 1024 x 4096, 704 tiles + 5, 1113: - 43; DiT-MoE-S, 942 tiles 0, 1692: - 3.  Long ones, from most of a round on:
+// K = 1536, 142 tiles + 9, 234: - 10, 420: - 11; K = 4608, 212: - 14; but not where many rows a segment make a second round that is nearly
+// empty (K = 2048, 280 tiles, 250 rows a segment + 16; K = 4608, 353 tiles, 125 rows + 2, 630: - 47; 264 tiles of 100 rows - 75).
+static bool ring_wide(int N, int K, int max_rows, int n_seg)
+{
+    const long long tiles = (max_rows / 64 + n_seg / 2ll) * ((N + 63) / 64);
+    if (K < 1536) return tiles >= 4 * kStreamGrid;
+    return tiles >= 200 && !(tiles > kStreamGrid && 2 * tiles < 3 * kStreamGrid && max_rows >= 112ll * n_seg);
+}
+
+// The kernel above takes other reductions and longer tables: 64 x 64 tiles once they fill two and a half rounds of the 256 compute units and the experts have rows for one and a half of them
 // (a segment ends in half a tile on average).  One GEMM, us, 32 x 32 tiles / what 64 x 64 change: second GEMM of DiT-MoE-S, 330 tiles
 // + 5, 612: - 4, 798: - 42, 1584: - 126; 2048 x 8192, 4 experts, 576 tiles + 10; first GEMM of DiT-MoE-S, 94 rows an expert + 5,
 // 125 rows, 940 tiles - 3, 375 rows - 21; 512 x 2048, 64 experts, 31 rows an expert, 2048 tiles + 10, 128 rows - 69.
@@ -216,6 +468,11 @@ static hipError_t launch_gemm_f32(const void* A, const void* W, const float* bia
 {
     const float *a = static_cast<const float*>(A), *w = static_cast<const float*>(W);
     float* c = static_cast<float*>(C);
+    if (n_seg <= 64 && K % 128 == 0 && K >= kRingMinK) {
+        if (ring_wide(N, K, max_rows, n_seg))
+            return launch_gemm_f32_ring<GELU, 4, 4, 2>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+        return launch_gemm_f32_ring<GELU, 2, 2, 2>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+    }
     const long long tiles = (max_rows / 64 + n_seg / 2ll) * ((N + 63) / 64);
     if (tiles >= 640 && max_rows >= 96ll * n_seg)
         return launch_gemm_f32_tile<GELU, 4, 4, 1>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
