@@ -195,6 +195,14 @@ int moe_dispatch_noalloc(moe_ctx* ctx, const void* x, const int32_t* expert_idx,
                          int32_t T, void* x_packed, int32_t* counts, int32_t* offsets, int32_t* perm,
                          int32_t* inv, void* stream);
 
+/* moe_gate, then (policy not NULL) moe_conditional_refresh, then moe_dispatch of the refreshed pairs (policy NULL: of every pair), with
+ * the arguments and results of those calls, in fewer launches: the dispatch forms the mask of the elementwise policies, and of the
+ * fraction policies up to 4096 pairs, itself.  All arguments are checked before the first launch.  mask and n_refresh
+ * are not used without a policy. */
+int moe_route(moe_ctx* ctx, const void* x, const void* Wg, const float* bg, int32_t T, const moe_policy* policy,
+              float* scores, int32_t* expert_idx, float* probs_all, float* logits, uint8_t* mask, int32_t* n_refresh,
+              void* x_packed, int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv, void* workspace, void* stream);
+
 /* Grouped expert FFN (Algorithm 1, "x_e <- expert(x_d)"; experts are feed-forward networks):
  * for every segment g, rows seg_offsets[g] .. seg_offsets[g+1]-1 of x_packed go through expert
  * seg_expert[g]:  h = W2_e . gelu(W1_e . x + b1_e) + b2_e,  gelu(u) = u/2 (1 + erf(u/sqrt 2)).

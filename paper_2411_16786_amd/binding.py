@@ -26,8 +26,8 @@ MOE_ERR_NULL, MOE_ERR_SHAPE, MOE_ERR_DTYPE, MOE_ERR_POLICY = -1, -2, -3, -4
 MOE_ERR_WORKSPACE, MOE_ERR_CACHE_COLD, MOE_ERR_HIP = -5, -6, -7
 
 EXPORTS = ["moe_create", "moe_destroy", "moe_workspace_bytes", "moe_last_error", "moe_status_string",
-           "moe_gate", "moe_policy_refreshed_pairs", "moe_conditional_refresh", "moe_dispatch", "moe_dispatch_noalloc", "moe_expert_ffn", "moe_expert_ffn_rows",
-           "moe_expert_ffn_commit", "moe_expert_ffn_status", "moe_expert_ffn_between_event", "moe_calibrate_copy",
+           "moe_gate", "moe_policy_refreshed_pairs", "moe_conditional_refresh", "moe_dispatch", "moe_dispatch_noalloc", "moe_route",
+           "moe_expert_ffn", "moe_expert_ffn_rows", "moe_expert_ffn_commit", "moe_expert_ffn_status", "moe_expert_ffn_between_event", "moe_calibrate_copy",
            "moe_calibrate_mfma", "moe_combine", "moe_layer_forward", "moe_ep_segments"]
 
 
@@ -80,6 +80,7 @@ def lib() -> ctypes.CDLL:
         L.moe_conditional_refresh.argtypes = [vp, vp, vp, i32, ctypes.POINTER(MoePolicy), vp, vp, vp, vp]
         L.moe_dispatch.argtypes = [vp, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp, vp]
         L.moe_dispatch_noalloc.argtypes = [vp, vp, vp, vp, i32, vp, vp, vp, vp, vp, vp]
+        L.moe_route.argtypes = [vp, vp, vp, vp, i32, ctypes.POINTER(MoePolicy)] + [vp] * 13
         L.moe_expert_ffn.argtypes = [vp, vp, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp, vp]
         L.moe_expert_ffn_rows.argtypes = [vp, vp, vp, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp, vp]
         L.moe_expert_ffn_commit.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, vp, vp, vp, vp, vp, vp, i32, vp, vp, vp, vp]
@@ -195,6 +196,16 @@ class Context:
                                                _ptr(mask, torch.uint8), T, _ptr(x_packed, self.torch_dtype),
                                                _ptr(counts, torch.int32), _ptr(offsets, torch.int32),
                                                _ptr(perm, torch.int32), _ptr(inv, torch.int32), _stream()))
+
+    def moe_route(self, x, Wg, bg, policy: Optional[Policy], scores, expert_idx, mask, n_refresh, x_packed, counts, offsets, perm,
+                  inv, workspace, probs_all=None, logits=None):
+        """moe_gate, moe_conditional_refresh (with a policy) and moe_dispatch in one call and fewer launches."""
+        f32, i32 = torch.float32, torch.int32
+        self._check(lib().moe_route(self._h, _ptr(x, self.torch_dtype), _ptr(Wg, self.torch_dtype), _ptr(bg, f32), x.shape[0],
+                                    None if policy is None else ctypes.byref(policy.c()), _ptr(scores, f32), _ptr(expert_idx, i32),
+                                    _ptr(probs_all, f32), _ptr(logits, f32), _ptr(mask, torch.uint8), _ptr(n_refresh, i32),
+                                    _ptr(x_packed, self.torch_dtype), _ptr(counts, i32), _ptr(offsets, i32), _ptr(perm, i32),
+                                    _ptr(inv, i32), _ptr(workspace), _stream()))
 
     def moe_expert_ffn(self, x_packed, seg_offsets, seg_expert, max_rows, W1, b1, W2, b2, h_packed, workspace):
         n_seg = seg_expert.shape[0]

@@ -114,6 +114,46 @@ int check_refresh(moe_ctx* ctx, const float* scores, int32_t T, const moe_policy
     return MOE_OK;
 }
 
+// A policy that check_refresh has accepted, as the kernels take it
+RefreshRule refresh_rule(const moe_ctx* ctx, const moe_policy* policy, int32_t T, int32_t routed, const float* scores, uint8_t* mask,
+                         int32_t* n_refresh)
+{
+    const moe_shape& s = ctx->shape;
+    RefreshRule rule = {};
+    rule.kind = policy->kind;
+    rule.k = s.k;
+    rule.n_shared = s.n_shared;
+    rule.n_value = routed + T * s.n_shared;            // what the device-side n_refresh receives
+    rule.scores = scores;
+    rule.mask = mask;
+    rule.n_refresh = n_refresh;
+    switch (policy->kind) {
+    case MOE_REFRESH_ALL:
+    case MOE_REFRESH_NONE: break;
+    case MOE_REFRESH_ALG4:
+    case MOE_REFRESH_ALG4_HIGH:
+    case MOE_REFRESH_ALG4_RANDOM:
+        rule.off_step = policy->step_t % policy->stride_n != 0 ? 1 : 0;
+        rule.seed = static_cast<uint32_t>(policy->n_units);
+        break;
+    case MOE_REFRESH_FRACTION_TOKEN:
+        rule.select = rule.token_mode = 1;
+        rule.m = policy->n_units;
+        break;
+    default:        // MOE_REFRESH_FRACTION_PAIR (policy_routed_pairs has rejected every other kind)
+        if (policy->n_units == static_cast<long>(T) * s.k) {
+            rule.kind = MOE_REFRESH_ALL;
+            break;
+        }
+        // slots before `slot` are refreshed for every token, slot `slot` for its m best tokens
+        rule.select = 1;
+        rule.slot = policy->n_units / T;               // (T > 0: without tokens n_units is 0 = T * k)
+        rule.m = policy->n_units % T;
+        break;
+    }
+    return rule;
+}
+
 int check_dispatch(moe_ctx* ctx, const void* x, const int32_t* expert_idx, int32_t T, const void* x_packed, const int32_t* counts,
                    const int32_t* offsets, const int32_t* perm, const int32_t* inv, const void* workspace)
 {
@@ -253,40 +293,8 @@ int moe_conditional_refresh(moe_ctx* ctx, const float* scores, const int32_t* ex
     if (!ctx) return MOE_ERR_NULL;
     int32_t routed = 0;
     if (int rc = check_refresh(ctx, scores, T, policy, mask, n_refresh, &routed)) return rc;
-    const moe_shape& s = ctx->shape;
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    const int n_value = routed + T * s.n_shared;       // what the device-side n_refresh receives
-    const long N = static_cast<long>(T) * s.k;
-    switch (policy->kind) {
-    case MOE_REFRESH_ALL:
-    case MOE_REFRESH_NONE:
-        return hip_result(ctx, launch_refresh_simple(policy->kind, T, s.k, s.n_shared, 0, 0u, n_value, mask, n_refresh, st),
-                          "moe_conditional_refresh");
-    case MOE_REFRESH_ALG4:
-    case MOE_REFRESH_ALG4_HIGH:
-    case MOE_REFRESH_ALG4_RANDOM:
-        return hip_result(ctx,
-                          launch_refresh_simple(policy->kind, T, s.k, s.n_shared,
-                                                policy->step_t % policy->stride_n != 0 ? 1 : 0,
-                                                static_cast<uint32_t>(policy->n_units), n_value, mask, n_refresh, st),
-                          "moe_conditional_refresh");
-    case MOE_REFRESH_FRACTION_TOKEN:
-        return hip_result(ctx,
-                          launch_refresh_select(scores, T, s.k, s.n_shared, 0, policy->n_units, true, n_value, mask,
-                                                n_refresh, st),
-                          "moe_conditional_refresh");
-    default: {      // MOE_REFRESH_FRACTION_PAIR (policy_routed_pairs has rejected every other kind)
-        if (policy->n_units == N)
-            return hip_result(ctx, launch_refresh_simple(MOE_REFRESH_ALL, T, s.k, s.n_shared, 0, 0u, n_value, mask, n_refresh, st),
-                              "moe_conditional_refresh");
-        // slots before `slot` are refreshed for every token, slot `slot` for its m best tokens
-        const int slot = T > 0 ? policy->n_units / T : 0;
-        const int m = T > 0 ? policy->n_units % T : 0;
-        return hip_result(ctx,
-                          launch_refresh_select(scores, T, s.k, s.n_shared, slot, m, false, n_value, mask, n_refresh, st),
-                          "moe_conditional_refresh");
-    }
-    }
+    return hip_result(ctx, launch_refresh(refresh_rule(ctx, policy, T, routed, scores, mask, n_refresh), T, static_cast<hipStream_t>(stream)),
+                      "moe_conditional_refresh");
 }
 
 int moe_dispatch(moe_ctx* ctx, const void* x, const int32_t* expert_idx, const uint8_t* mask, int32_t T,
@@ -352,7 +360,37 @@ static int expert_ffn_common(moe_ctx* ctx, const char* who, const void* x_rows, 
                       who);
 }
 
+// Router, refresh decision (with a policy) and dispatch, all checked by the caller.  The dispatch forms the mask where it can.
+static int route_launches(moe_ctx* ctx, const char* who, const void* x, const void* Wg, const float* bg, int32_t T, const moe_policy* policy,
+                          int32_t routed, float* scores, int32_t* expert_idx, float* probs_all, float* logits, uint8_t* mask,
+                          int32_t* n_refresh, void* x_packed, int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv,
+                          void* workspace, void* stream)
+{
+    if (int rc = moe_gate(ctx, x, Wg, bg, T, scores, expert_idx, probs_all, logits, stream)) return rc;
+    RefreshRule rule;
+    if (policy) rule = refresh_rule(ctx, policy, T, routed, scores, mask, n_refresh);
+    return hip_result(ctx,
+                      launch_dispatch(is_bf16(ctx), x, expert_idx, policy ? mask : nullptr, T, ctx->shape.d, experts(ctx), slots(ctx),
+                                      x_packed, counts, offsets, perm, inv, static_cast<int32_t*>(workspace),
+                                      static_cast<hipStream_t>(stream), policy ? &rule : nullptr),
+                      who);
+}
+
 extern "C" {
+
+int moe_route(moe_ctx* ctx, const void* x, const void* Wg, const float* bg, int32_t T, const moe_policy* policy, float* scores,
+              int32_t* expert_idx, float* probs_all, float* logits, uint8_t* mask, int32_t* n_refresh, void* x_packed,
+              int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv, void* workspace, void* stream)
+{
+    if (!ctx) return MOE_ERR_NULL;
+    int32_t routed = 0;
+    if (int rc = check_gate(ctx, x, Wg, T, scores, expert_idx)) return rc;
+    if (policy)
+        if (int rc = check_refresh(ctx, scores, T, policy, mask, n_refresh, &routed)) return rc;
+    if (int rc = check_dispatch(ctx, x, expert_idx, T, x_packed, counts, offsets, perm, inv, workspace)) return rc;
+    return route_launches(ctx, "moe_route", x, Wg, bg, T, policy, routed, scores, expert_idx, probs_all, logits, mask, n_refresh,
+                          x_packed, counts, offsets, perm, inv, workspace, stream);
+}
 
 int moe_expert_ffn(moe_ctx* ctx, const void* x_packed, const int32_t* seg_offsets, const int32_t* seg_expert,
                    int32_t n_segments, int32_t max_rows, const void* W1, const float* b1, const void* W2,
@@ -469,12 +507,9 @@ int moe_layer_forward(moe_ctx* ctx, const moe_layer_args* a, const moe_policy* p
         return rc;
     if (int rc = check_combine(ctx, h_packed, a->inv, a->scores, mask, a->T, H_cache, S_cache, a->y)) return rc;
 
-    if (int rc = moe_gate(ctx, a->x, a->Wg, a->bg, a->T, a->scores, a->expert_idx, a->probs_all, a->logits, stream)) return rc;
-    if (policy)
-        if (int rc = moe_conditional_refresh(ctx, a->scores, a->expert_idx, a->T, policy, a->mask, a->n_refresh, a->workspace, stream))
-            return rc;
-    if (int rc = moe_dispatch(ctx, a->x, a->expert_idx, mask, a->T, fuse ? nullptr : a->x_packed, a->counts, a->offsets, a->perm,
-                              a->inv, a->workspace, stream))
+    if (int rc = route_launches(ctx, "moe_layer_forward", a->x, a->Wg, a->bg, a->T, policy, routed, a->scores, a->expert_idx, a->probs_all,
+                                a->logits, a->mask, a->n_refresh, fuse ? nullptr : a->x_packed, a->counts, a->offsets, a->perm, a->inv,
+                                a->workspace, stream))
         return rc;
     // packed rows (read by token through perm, or from the send buffer) -> h rows, in h_packed or at their pairs' places in the
     // cache.  A split second GEMM leaves its float shares to the combine.

@@ -19,9 +19,9 @@
 // pass) and stores it to each of its refreshed slots' packed rows; bound by HBM traffic
 // T*d*b read + R*d*b written.
 #include <mutex>
+#include <type_traits>
 
-#include "common.hpp"
-#include "kernels.hpp"
+#include "refresh_rule.hpp"
 
 namespace dicemoe {
 
@@ -56,18 +56,40 @@ __device__ __forceinline__ uint64_t same_expert_peers(bool live, int e, int nbit
     return peers;
 }
 
+// Where the dispatch takes the mask from: an array (or none: every pair), an elementwise policy, or a selection of tokens
+// made by this workgroup (`bits`: one bit per token, in LDS).  The mask of the last two is written out by the way.
+enum MaskSource { kMaskArray, kMaskSimple, kMaskSelect };
+struct NoRule {};
+template <int SOURCE> using Rule = std::conditional_t<SOURCE == kMaskArray, NoRule, RefreshRule>;
+
 // Expert ids of this wave's S steps, -1 where the pair is past the end, not refreshed or carries a
 // bad id.  The loads are unconditional (index clamped) so that all of them are in flight at once.
-template <int S>
+template <int S, int SOURCE>
 __device__ __forceinline__ void load_steps(const int32_t* __restrict__ expert_idx, const uint8_t* __restrict__ mask,
-                                           int p0, int lane, int N, int E, int (&ev)[S]) {
+                                           int p0, int lane, int N, int E, const Rule<SOURCE>& rule, const uint32_t* bits, int (&ev)[S]) {
     uint8_t mv[S];
 #pragma unroll
     for (int u = 0; u < S; ++u) {
         const int p = p0 + u * kWave + lane;
         ev[u] = expert_idx[p < N ? p : N - 1];
     }
-    if (mask != nullptr) {
+    if constexpr (SOURCE == kMaskSimple) {
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            const int p = p0 + u * kWave + lane;
+            mv[u] = simple_mask(rule, p);
+            if (p < N) rule.mask[p] = mv[u];
+        }
+    } else if constexpr (SOURCE == kMaskSelect) {
+        const int kc = rule.k + rule.n_shared;
+#pragma unroll
+        for (int u = 0; u < S; ++u) {
+            const int p = p0 + u * kWave + lane;
+            const int tok = (p < N ? p : N - 1) / kc;
+            mv[u] = selected_mask(rule, p - tok * kc, (bits[tok >> 5] >> (tok & 31)) & 1u);
+            if (p < N) rule.mask[p] = mv[u];
+        }
+    } else if (mask != nullptr) {
 #pragma unroll
         for (int u = 0; u < S; ++u) {
             const int p = p0 + u * kWave + lane;
@@ -85,11 +107,13 @@ __device__ __forceinline__ void load_steps(const int32_t* __restrict__ expert_id
     }
 }
 
-template <int S>
+template <int S, int SOURCE>
 __global__ __launch_bounds__(kIdxThreads) void dispatch_count_kernel(const int32_t* __restrict__ expert_idx,
                                                                     const uint8_t* __restrict__ mask, int N, int E,
-                                                                    int32_t* __restrict__ block_counts)
+                                                                    int32_t* __restrict__ block_counts, Rule<SOURCE> rule)
 {
+    if constexpr (SOURCE == kMaskSimple)
+        if (blockIdx.x == 0 && threadIdx.x == 0) *rule.n_refresh = rule.n_value;
     __shared__ int cnt[kMaxExperts];
     const int tid = threadIdx.x;
     const int wave = tid / kWave;
@@ -100,7 +124,7 @@ __global__ __launch_bounds__(kIdxThreads) void dispatch_count_kernel(const int32
     const int p0 = (static_cast<int>(blockIdx.x) * kIdxWaves + wave) * kWave * S;
     if (p0 < N) {                                           // wave-uniform
         int ev[S];
-        load_steps<S>(expert_idx, mask, p0, lane, N, E, ev);
+        load_steps<S, SOURCE>(expert_idx, mask, p0, lane, N, E, rule, nullptr, ev);
 #pragma unroll
         for (int u = 0; u < S; ++u) {
             const bool live = ev[u] >= 0;
@@ -143,16 +167,19 @@ __global__ __launch_bounds__(1024) void dispatch_scan_kernel(int32_t* __restrict
     }
 }
 
-template <int S, int THREADS>
+// SOURCE other than the array: one workgroup alone, which forms the mask (the selection: of up to 1024 S tokens)
+template <int S, int THREADS, int SOURCE>
 __global__ __launch_bounds__(THREADS) void dispatch_place_kernel(const int32_t* __restrict__ expert_idx,
                                                                     const uint8_t* __restrict__ mask, int N, int E,
                                                                     const int32_t* __restrict__ block_counts,
                                                                     int prefix_ready, int32_t* __restrict__ counts,
                                                                     int32_t* __restrict__ offsets,
                                                                     int32_t* __restrict__ perm,
-                                                                    int32_t* __restrict__ inv)
+                                                                    int32_t* __restrict__ inv, Rule<SOURCE> rule)
 {
     constexpr int WAVES = THREADS / kWave;
+    static_assert(SOURCE != kMaskSelect || THREADS == kSelThreads, "the selection is made by 1024 threads");
+    __shared__ uint32_t sel_bits[SOURCE == kMaskSelect ? 32 * S : 1];
     __shared__ int wave_run[WAVES][kMaxExperts];       // running count of a wave's pairs per expert; then the pairs of the waves before it
     __shared__ int s_tot[kMaxExperts];                 // pairs per expert over all workgroups
     __shared__ int s_pre[kMaxExperts];                 // pairs per expert in the workgroups before this one
@@ -165,6 +192,18 @@ __global__ __launch_bounds__(THREADS) void dispatch_place_kernel(const int32_t* 
     const int nbits = E > 1 ? 32 - __builtin_clz(static_cast<unsigned>(E - 1)) : 0;
     wave_run[tid / kMaxExperts][tid % kMaxExperts] = 0;   // the threads cover the WAVES x 64 table
     if (tid < kMaxExperts) { s_tot[tid] = 0; s_pre[tid] = 0; }
+    if constexpr (SOURCE != kMaskArray)
+        if (tid == 0) *rule.n_refresh = rule.n_value;
+    if constexpr (SOURCE == kMaskSelect) {
+        __shared__ SelectShared sel_shared;
+        bool sel[S];
+        select_tokens<S>(rule, N / (rule.k + rule.n_shared), sel_shared, sel);
+#pragma unroll
+        for (int u = 0; u < S; ++u) {                      // token u * 1024 + tid
+            const uint64_t b = __ballot(sel[u]);
+            if (lane < 2) sel_bits[(u * WAVES + wave) * 2 + lane] = static_cast<uint32_t>(b >> (32 * lane));
+        }
+    }
     __syncthreads();
 
     // the table of the other workgroups' counts: totals, and the part that precedes this workgroup.  Large
@@ -190,7 +229,7 @@ __global__ __launch_bounds__(THREADS) void dispatch_place_kernel(const int32_t* 
     const int p0 = (b * WAVES + wave) * kWave * S;
     int ev[S], rank[S];
     if (p0 < N) {                                           // wave-uniform
-        load_steps<S>(expert_idx, mask, p0, lane, N, E, ev);
+        load_steps<S, SOURCE>(expert_idx, mask, p0, lane, N, E, rule, sel_bits, ev);
 #pragma unroll
         for (int u = 0; u < S; ++u) {
             const bool live = ev[u] >= 0;
@@ -343,42 +382,62 @@ size_t dispatch_scratch_bytes(long long n_pairs, int E)
 
 template <int S>
 static void launch_dispatch_index(const int32_t* idx, const uint8_t* mask, int N, int E, int blocks, int32_t* scratch,
-                                  int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv, hipStream_t stream)
+                                  int32_t* counts, int32_t* offsets, int32_t* perm, int32_t* inv, const RefreshRule* rule, hipStream_t stream)
 {
     const int scan = blocks > 256 ? 1 : 0;      // small grids: every placing workgroup sums the table itself
-    hipLaunchKernelGGL(dispatch_count_kernel<S>, dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch);
+    if (rule)
+        hipLaunchKernelGGL((dispatch_count_kernel<S, kMaskSimple>), dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch, *rule);
+    else
+        hipLaunchKernelGGL((dispatch_count_kernel<S, kMaskArray>), dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch, NoRule{});
     if (scan)
         hipLaunchKernelGGL(dispatch_scan_kernel, dim3(1), dim3(1024), 0, stream, scratch, blocks, E);
-    hipLaunchKernelGGL((dispatch_place_kernel<S, kIdxThreads>), dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch,
-                       scan, counts, offsets, perm, inv);
+    hipLaunchKernelGGL((dispatch_place_kernel<S, kIdxThreads, kMaskArray>), dim3(blocks), dim3(kIdxThreads), 0, stream, idx, mask, N, E, scratch,
+                       scan, counts, offsets, perm, inv, NoRule{});
 }
 
 // One workgroup for all pairs, no counting launch and no table
 template <int S, int THREADS>
 static void launch_dispatch_alone(const int32_t* idx, const uint8_t* mask, int N, int E, int32_t* counts, int32_t* offsets,
-                                  int32_t* perm, int32_t* inv, hipStream_t stream)
+                                  int32_t* perm, int32_t* inv, const RefreshRule* rule, hipStream_t stream)
 {
-    hipLaunchKernelGGL((dispatch_place_kernel<S, THREADS>), dim3(1), dim3(THREADS), 0, stream, idx, mask, N, E,
-                       static_cast<const int32_t*>(nullptr), 0, counts, offsets, perm, inv);
+    if constexpr (THREADS == kSelThreads) {
+        if (rule && rule->select) {
+            hipLaunchKernelGGL((dispatch_place_kernel<S, THREADS, kMaskSelect>), dim3(1), dim3(THREADS), 0, stream, idx, mask, N, E,
+                               static_cast<const int32_t*>(nullptr), 0, counts, offsets, perm, inv, *rule);
+            return;
+        }
+    }
+    if (rule)
+        hipLaunchKernelGGL((dispatch_place_kernel<S, THREADS, kMaskSimple>), dim3(1), dim3(THREADS), 0, stream, idx, mask, N, E,
+                           static_cast<const int32_t*>(nullptr), 0, counts, offsets, perm, inv, *rule);
+    else
+        hipLaunchKernelGGL((dispatch_place_kernel<S, THREADS, kMaskArray>), dim3(1), dim3(THREADS), 0, stream, idx, mask, N, E,
+                           static_cast<const int32_t*>(nullptr), 0, counts, offsets, perm, inv, NoRule{});
 }
 
 hipError_t launch_dispatch(bool bf16, const void* x, const int32_t* idx, const uint8_t* mask, int T_tok, int d,
                            int E, int k, void* x_packed, int32_t* counts, int32_t* offsets, int32_t* perm,
-                           int32_t* inv, int32_t* scratch, hipStream_t stream)
+                           int32_t* inv, int32_t* scratch, hipStream_t stream, const RefreshRule* rule)
 {
     const int N = T_tok * k;
     if (N > kNoScratchPairs && scratch == nullptr) return hipErrorInvalidValue;
+    // Elementwise masks are formed by whoever reads the expert ids first, a selection of tokens by the workgroup that sorts alone;
+    // beyond that the selection is a launch of its own.
+    if (rule && (N == 0 || (rule->select && N > kAlonePairs))) {
+        if (hipError_t err = launch_refresh(*rule, T_tok, stream); err != hipSuccess) return err;
+        rule = nullptr;
+    }
     int steps, blocks;
     dispatch_plan(N, steps, blocks);
-    if (N <= kIdxThreads) launch_dispatch_alone<1, kIdxThreads>(idx, mask, N, E, counts, offsets, perm, inv, stream);
-    else if (N <= 1024) launch_dispatch_alone<1, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
-    else if (N <= 2048) launch_dispatch_alone<2, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
-    else if (N <= kAlonePairs) launch_dispatch_alone<4, 1024>(idx, mask, N, E, counts, offsets, perm, inv, stream);
+    if (N <= kIdxThreads && !(rule && rule->select)) launch_dispatch_alone<1, kIdxThreads>(idx, mask, N, E, counts, offsets, perm, inv, rule, stream);
+    else if (N <= 1024) launch_dispatch_alone<1, 1024>(idx, mask, N, E, counts, offsets, perm, inv, rule, stream);
+    else if (N <= 2048) launch_dispatch_alone<2, 1024>(idx, mask, N, E, counts, offsets, perm, inv, rule, stream);
+    else if (N <= kAlonePairs) launch_dispatch_alone<4, 1024>(idx, mask, N, E, counts, offsets, perm, inv, rule, stream);
     else switch (steps) {
-    case 1: launch_dispatch_index<1>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
-    case 2: launch_dispatch_index<2>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
-    case 4: launch_dispatch_index<4>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
-    default: launch_dispatch_index<8>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, stream); break;
+    case 1: launch_dispatch_index<1>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, rule, stream); break;
+    case 2: launch_dispatch_index<2>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, rule, stream); break;
+    case 4: launch_dispatch_index<4>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, rule, stream); break;
+    default: launch_dispatch_index<8>(idx, mask, N, E, blocks, scratch, counts, offsets, perm, inv, rule, stream); break;
     }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || T_tok == 0 || x_packed == nullptr) return err;   // no packed buffer: index only

@@ -13,23 +13,28 @@ hipError_t launch_gate(bool bf16, const void* x, const void* Wg, const float* bg
                        int n_shared, int renorm, float* scores, int32_t* idx, float* probs, float* logits,
                        hipStream_t stream);
 
-// kind: 0 all, 1 / 5 / 6 Algorithm 4 and its ablation variants, 4 none (elementwise policies); off_step:
-// step_t % stride_n != 0.  mask has k + n_shared columns; the shared slots are refreshed under every
-// policy.  n_value is written to n_refresh (the refreshed pairs, shared slots included).
-hipError_t launch_refresh_simple(int kind, int T_tok, int k, int n_shared, int off_step, uint32_t seed, int n_value,
-                                 uint8_t* mask, int32_t* n_refresh, hipStream_t stream);
-// exact top-m selection of tokens by scores[i*k + slot] (descending, ties to the lower token);
-// token_mode: selected tokens get all k slots; otherwise slots < slot are all refreshed, slot
-// `slot` follows the selection and later slots are not refreshed
-hipError_t launch_refresh_select(const float* scores, int T_tok, int k, int n_shared, int slot, int m,
-                                 bool token_mode, int n_value, uint8_t* mask, int32_t* n_refresh,
-                                 hipStream_t stream);
+// What a step refreshes.  Elementwise policies (select 0), by kind: 0 all, 1 / 5 / 6 Algorithm 4 and its ablation variants, 4 none; off_step:
+// step_t % stride_n != 0.  Selection (select 1): the exact top-m tokens by scores[i * (k + n_shared) + slot] (descending, ties to the
+// lower token); token_mode: selected tokens get all k slots; otherwise slots < slot are all refreshed, slot `slot` follows the selection
+// and later slots are not refreshed.  mask has k + n_shared columns; the shared slots are refreshed under every policy.  n_value is
+// written to n_refresh (the refreshed pairs, shared slots included).
+struct RefreshRule {
+    int select, kind, k, n_shared, off_step;
+    uint32_t seed;
+    int slot, m, token_mode, n_value;
+    const float* scores;
+    uint8_t* mask;
+    int32_t* n_refresh;
+};
+hipError_t launch_refresh(const RefreshRule& rule, int T_tok, hipStream_t stream);
 
 // scratch: dispatch_scratch_bytes(T_tok * k, E) bytes of device memory (per-workgroup expert counts handed
 // from the counting launch to the placing launch); may be null when that size is 0
 hipError_t launch_dispatch(bool bf16, const void* x, const int32_t* idx, const uint8_t* mask, int T_tok, int d,
                            int E, int k, void* x_packed, int32_t* counts, int32_t* offsets, int32_t* perm,
-                           int32_t* inv, int32_t* scratch, hipStream_t stream);
+                           int32_t* inv, int32_t* scratch, hipStream_t stream, const RefreshRule* rule = nullptr);
+// rule: if given, the mask is formed first and written to rule->mask (which `mask` has to be), by the dispatch's own launches
+// where they can and by launch_refresh otherwise
 size_t dispatch_scratch_bytes(long long n_pairs, int E);
 // The library's own scratch for launch_dispatch: a file-scope device array of dispatch_static_scratch_bytes()
 // bytes; *out receives its address on the current device (looked up once per device).  No allocation.

@@ -82,11 +82,9 @@ def moe_layer_step(schedule: str, st: LayerState, x, Wg, bg, W1, b1, W2, b2, pol
         return y
 
     rows_routed = ctx.moe_policy_refreshed_pairs(policy, T)[1]
-    ctx.moe_gate(x, Wg, bg, buf.scores[:T], buf.expert_idx[:T], buf.probs, buf.logits)
-    ctx.moe_conditional_refresh(buf.scores[:T], buf.expert_idx[:T], policy, buf.mask[:T], buf.n_refresh, buf.workspace)
     packed = buf.x_packed if schedule == DISPLACED else None
-    ctx.moe_dispatch(x, buf.expert_idx[:T], buf.mask[:T], packed, buf.counts, buf.offsets, buf.perm, buf.inv,
-                     buf.workspace)
+    ctx.moe_route(x, Wg, bg, policy, buf.scores[:T], buf.expert_idx[:T], buf.mask[:T], buf.n_refresh, packed, buf.counts, buf.offsets,
+                  buf.perm, buf.inv, buf.workspace, buf.probs, buf.logits)
     if ns > 0:
         # shared experts: this step's x, within the step (they are replicated, never stale)
         # (max_rows bounds the packed row ids of the segments, which follow the routed rows)
