@@ -18,6 +18,9 @@ typedef float f32x16_v __attribute__((ext_vector_type(16)));
 typedef float f32x4_v __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_v __attribute__((ext_vector_type(4)));   // 16 bytes in four VGPRs
 
+constexpr uint32_t kBeyondBuffer = 0xFFFFFFF0u;          // an offset that every buffer descriptor here rejects
+constexpr int kBufferFlags = 0x00027000;                 // raw buffer, 32-bit data format
+
 #define DICEMOE_GLOBAL_PTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define DICEMOE_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 

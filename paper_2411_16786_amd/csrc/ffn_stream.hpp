@@ -31,8 +31,6 @@
 
 namespace dicemoe {
 
-constexpr uint32_t kBeyondBuffer = 0xFFFFFFF0u;          // an offset that every buffer descriptor here rejects
-constexpr int kBufferFlags = 0x00027000;                 // raw buffer, 32-bit data format
 constexpr int kStreamThreads = 512;
 constexpr int kStreamLds = 160 * 1024;
 
