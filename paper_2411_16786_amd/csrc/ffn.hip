@@ -271,33 +271,44 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
                                         size_t partial_bytes = 0, int32_t* status = nullptr, SplitSums* sums = nullptr)
 {
     const int by_expert = n_seg <= 64 ? 1 : 0;
-    const FfnPlan plan = plan_ffn_gemm(GELU, N, K, max_rows, n_seg, n_experts, partial ? partial_bytes : 0);
+    const FfnPlan plan = plan_ffn_gemm(GELU, N, K, max_rows, n_seg, n_experts, partial ? partial_bytes : 0, sums != nullptr);
 #define DICEMOE_WIDE(...)                                                                                                    \
     return launch_gemm_bf16_wide<__VA_ARGS__>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, \
                                               row_div, out_index, by_expert, nullptr, 1, status)
+// float shares to `partial`, then the second pass, unless the caller's combine adds them
+#define DICEMOE_SHARES(...)                                                                                                  \
+    do {                                                                                                                     \
+        const hipError_t err = launch_gemm_bf16_wide<__VA_ARGS__>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg,    \
+                                                                  max_rows, stream, row_index, row_div, nullptr, by_expert,  \
+                                                                  partial, plan.shares, status);                             \
+        if (err == hipSuccess && sums) *sums = SplitSums{partial, plan.shares, max_rows, bias};                              \
+        if (err != hipSuccess || sums) return err;                                                                           \
+        return launch_splitk_reduce(partial, plan.shares, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream); \
+    } while (0)
     switch (plan.tile) {
     case FfnTile::Stream192:
         return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
     case FfnTile::Stream256:
         return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
-    case FfnTile::Small64: DICEMOE_WIDE(1, 2, 2, 3, 3, GELU);
+    case FfnTile::Small64:
+        if (plan.shares > 1) DICEMOE_SHARES(1, 2, 2, 3, 3, GELU);
+        DICEMOE_WIDE(1, 2, 2, 3, 3, GELU);
     case FfnTile::Small128:
-        if constexpr (!GELU) DICEMOE_WIDE(2, 2, 2, 3, 3, GELU);
+        if constexpr (!GELU) {
+            if (plan.shares > 1) DICEMOE_SHARES(2, 2, 2, 3, 3, GELU);
+            DICEMOE_WIDE(2, 2, 2, 3, 3, GELU);
+        }
         break;
     case FfnTile::Mid192Deep:
-        if constexpr (!GELU) {
-            if (plan.shares > 1) {
-                const hipError_t err = launch_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>(A, W, nullptr, C, N, K, seg_offsets, seg_expert, n_seg,
-                                                                                 max_rows, stream, row_index, row_div, nullptr,
-                                                                                 by_expert, partial, plan.shares, status);
-                if (sums) {
-                    *sums = SplitSums{partial, plan.shares, max_rows, bias};
-                    return err;
-                }
-                return err != hipSuccess ? err : launch_splitk_reduce(partial, plan.shares, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream);
-            }
+        if constexpr (GELU) {
+            // eight wavefronts: half the GELU epilogue behind a tile's last step, and rows that do not exist leave fewer of them idle
+            // (whole layer, four / eight: DiT-MoE-XL, 48 tokens 57.5 / 55.4 us, 138: 64.1 / 62.6, 256: 69.8 / 69.2; the GEMM without
+            // GELU loses up to 0.8 us)
+            DICEMOE_WIDE(1, 3, 2, 3, 3, GELU, 4, 2);
+        } else {
+            if (plan.shares > 1) DICEMOE_SHARES(2, 3, 2, 3, 3, GELU);
+            DICEMOE_WIDE(2, 3, 2, 3, 3, GELU);
         }
-        DICEMOE_WIDE(2, 3, 2, 3, 3, GELU);
     case FfnTile::Mid192: DICEMOE_WIDE(2, 3, 2, 2, 2, GELU);
     case FfnTile::Wide192W4:
         if constexpr (!GELU) DICEMOE_WIDE(2, 3, 2, 2, 4, GELU, 4, 2);
@@ -312,6 +323,7 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
         return launch_gemm_bf16<128, 128, 3, true, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,
                                                          row_div, out_index, status);
     }
+#undef DICEMOE_SHARES
 #undef DICEMOE_WIDE
     return hipErrorInvalidValue;                 // (the tiles that only the GEMM without GELU takes)
 }
@@ -321,9 +333,11 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
 template <bool GELU>
 static hipError_t configure_gemm_bf16_auto()
 {
-    hipError_t err = configure_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>();
-    if (err == hipSuccess) err = configure_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>();
-    if constexpr (!GELU) {
+    hipError_t err = configure_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>();
+    if constexpr (GELU) {
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<1, 3, 2, 3, 3, GELU, 4, 2>();
+    } else {
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>();
         if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 3, GELU, 4, 2>();
         if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 4, GELU, 4, 2>();
         if (err == hipSuccess) err = configure_gemm_bf16_wide<4, 3, 2, 2, 2, GELU>();

@@ -13,7 +13,7 @@ enum class FfnTile {
     Stream256,      // persistent kernel, 256 x 256
     Small64,        // a workgroup per tile from here on: 64 x 128, three stages, two workgroups per compute unit
     Small128,       // 128 x 128, three stages
-    Mid192Deep,     // 128 x 192, three stages, one workgroup per compute unit
+    Mid192Deep,     // 128 x 192, three stages, one workgroup per compute unit (with GELU eight wavefronts, without four)
     Mid192,         // 128 x 192, two stages, two workgroups per compute unit
     Wide192W4,      // 256 x 192, eight wavefronts, two stages of activations and four of weights
     Wide192W3,      // the same with three stages of weights
@@ -86,7 +86,8 @@ inline float stream_cost(int bn, int N, int K, bool gelu, int rows, int n_seg)
 // The lines between the tiles up to 128 rows were drawn from 2641 combinations of nine widths, 2 to 64 experts, 1 to 8 segments per
 // expert and 8 to 2048 rows per segment (graphs of calls with weights from memory, every tile that can run timed for either GEMM);
 // figures beside them are us, or % of the FFN.
-inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, int n_experts, size_t partial_bytes)
+// sums: the caller's combine adds the shares of a split reduction (no second pass)
+inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, int n_experts, size_t partial_bytes, bool sums = false)
 {
     const bool by_expert = n_seg <= 64;
     const long long rows = max_rows, segs = n_seg;
@@ -134,6 +135,25 @@ inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, i
     // Three shares of experts with more than 100 rows: only if they run in one round even when every segment ends in an empty tile
     // and the second pass has little to add (two experts of 2048 x 8192, 500 rows, 64 x 128 / three shares 101 / 85; of 1152 x 4608,
     // 968 rows 57 / 53, 1219 rows 64 / 73; DiT-MoE-XL, 900 rows 29.5 / 48).
+    // Where the combine adds the shares, a share more costs its part of that traffic and no launch.  Long reductions (the weights are what the
+    // time goes to): 128 x 128 tiles in as many shares, of sixteen steps at least, as one round has room for, with a row tile to spare
+    // once segments are likely to need a second one: an XCD deals its eighth of the tiles to 32 compute units, and one more than these
+    // is a second round (whole layer, 128 x 192 in three shares / so: DiT-MoE-XL, 48 tokens 57.2 / 53.7 us, 138: 63.4 / 59.9; 500 tokens, in
+    // two, 85.5 / 81.9, 700 rows 77.0 / 73.8, 575 rows 75.6 / 76.2; 267 rows of nine experts, 11 tiles an XCD: 68.2 / 76.4 in three).  Short ones:
+    // 64 x 128 tiles in three shares while these fill three quarters of the chip at most (DiT-MoE-S, 60 tokens 30.9 / 27.9, 170: 31.0 / 28.2, 400:
+    // 32.4 / 30.5; 800 tokens top-3, 150 tiles, 36.5 / 38.4; four shares of six steps 1 us behind three).
+    if (sums && !gelu && by_expert && fits_128) {
+        auto room = [&](int s) { return static_cast<size_t>(s) * max_rows * N * sizeof(float) <= partial_bytes; };
+        const int steps = K / 64;
+        if (steps < 48) {
+            if (steps >= 24 && rows <= 64 * segs && 4 * all_tiles(64, 128) <= kComputeUnits && room(3)) return {FfnTile::Small64, 3};
+        } else {
+            const long long t = all_tiles(128, 128) + (rows > 48 * segs ? (N + 127) / 128 : 0);
+            auto fits = [&](int s) { return steps / s >= 16 && (t + 7) / 8 * s <= kStreamSlots && room(s); };
+            if (fits(3)) return {FfnTile::Small128, 3};
+            if (rows > 80 * segs && fits(2)) return {FfnTile::Small128, 2};
+        }
+    }
     int shares = 1;
     if (!gelu && by_expert && fits_192) {
         auto can = [&](int s, long long t) {

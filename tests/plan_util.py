@@ -11,8 +11,8 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 # in the order of the enumeration FfnTile; "/2", "/3" behind a name: that many shares of K
 TILES = ["stream192", "stream256", "64x128", "128x128", "128x192deep", "128x192", "256x192w4", "256x192w3", "256x192", "staged"]
 SHIM = """#include "ffn_plan.hpp"
-extern "C" void plan(int gelu, int N, int K, int rows, int n_seg, int n_experts, int* out) {
-    const dicemoe::FfnPlan p = dicemoe::plan_ffn_gemm(gelu != 0, N, K, rows, n_seg, n_experts, gelu ? 0 : dicemoe::kSplitKBytes);
+extern "C" void plan(int gelu, int N, int K, int rows, int n_seg, int n_experts, int sums, int* out) {
+    const dicemoe::FfnPlan p = dicemoe::plan_ffn_gemm(gelu != 0, N, K, rows, n_seg, n_experts, gelu ? 0 : dicemoe::kSplitKBytes, sums != 0);
     out[0] = static_cast<int>(p.tile);
     out[1] = p.shares;
 }
@@ -30,9 +30,10 @@ def _lib():
         return ctypes.CDLL(out)
 
 
-def plan(gelu, N, K, rows, n_seg, n_experts=None):
+def plan(gelu, N, K, rows, n_seg, n_experts=None, sums=False):
+    """sums: inside the layer call, whose combine adds the shares of a split reduction"""
     out = (ctypes.c_int * 2)()
-    _lib().plan(int(gelu), N, K, rows, n_seg, n_seg if n_experts is None else n_experts, out)
+    _lib().plan(int(gelu), N, K, rows, n_seg, n_seg if n_experts is None else n_experts, int(sums), out)
     return TILES[out[0]] + (f"/{out[1]}" if out[1] > 1 else "")
 
 
