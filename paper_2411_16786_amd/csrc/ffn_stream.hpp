@@ -272,6 +272,8 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
     // therefore fetches the chunk that the swizzle assigns to that slot.  Rows of A come through the row index when
     // there is one.  Weight rows beyond the matrix read as zero (bounds of the buffer).
     const __amdgpu_buffer_rsrc_t a_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, static_cast<int>(kBeyondBuffer), kBufferFlags);
+    // Behind the last item: no rows and no columns, so that the stages asked for there cost no memory access
+    auto nowhere = [](Place pl) { return Place{pl.row0, pl.row0, pl.col0, pl.col0, pl.e}; };
     auto w_buffer = [&](const Place& pl) {
         const int rows = pl.col_end - pl.col0;
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(W + (static_cast<size_t>(pl.e) * N + pl.col0) * K), 0, rows * K * 2, kBufferFlags);
@@ -289,7 +291,7 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
             int r = pl.row0 + (wave * QA + i) * 8 + (lane >> 3);
             if (GATHER) {
                 r = r < pl.row_end ? r : pl.row_end - 1;
-                rows[i] = row_index[r];
+                rows[i] = row_index[r > 0 ? r : 0];
             } else {
                 rows[i] = r;
             }
@@ -415,8 +417,15 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
     };
     auto nothing = [] {};
 
-    // ---- first item: fill the rings (what is left out here, step 0 issues as the carried part of a refill)
+    // ---- first item: fill the rings (what is left out here, step 0 issues as the carried part of a refill).  All row indices are asked for
+    // before the first weight load, so that the wait for them is not one for the weights (with one of them moved behind these, first
+    // products 5.9 us after the start instead of 4.6)
+    auto fetch_bias = [&](const Place& pl) {
+        const int c = pl.col0 + wn * WN;
+        load_bias_columns<WN>(bias ? bias + static_cast<size_t>(pl.e) * N + c : nullptr, N - c, lane, bias_reg);
+    };
     fetch_rows(p, rows);
+    DICEMOE_SCHED_FENCE();
 #pragma unroll
     for (int s = 0; s < WST; ++s)
 #pragma unroll
@@ -426,14 +435,12 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
     for (int s = 0; s < AST; ++s)
 #pragma unroll
         for (int i = 0; i < QA; ++i) if (s < AST - 1 || i < PART) dma_a(i, a_cur[i], s, s);
-    auto fetch_bias = [&](const Place& pl) {
-        const int c = pl.col0 + wn * WN;
-        load_bias_columns<WN>(bias ? bias + static_cast<size_t>(pl.e) * N + c : nullptr, N - c, lane, bias_reg);
-    };
     fetch_bias(p);
-    Place q = n_items > 1 ? place(1) : p;                // (after the last item: its own first stages again, never used)
+    DICEMOE_SCHED_FENCE();
+    Place q = n_items > 1 ? place(1) : nowhere(p);
     fetch_rows(q, rows);
-    wait_vmcnt<0>();
+    DICEMOE_SCHED_FENCE();
+    wait_vmcnt<GATHER ? QA : 0>();                   // (the row indices of the second item may be on their way)
     block_barrier();
 #pragma unroll
     for (int f = 0; f < NFRAG; ++f) read_frag(0, f, a_lds, w_lds, 0);
@@ -478,7 +485,7 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
             dst[i] = r < p.row_end ? r : -1;
             if (!GELU && out_index) dst[i] = r < p.row_end ? out_index[r] : -1;
         }
-        const Place after = it + 2 < n_items ? place(it + 2) : q;
+        const Place after = it + 2 < n_items ? place(it + 2) : nowhere(q);
         fetch_rows(after, rows);
         asm volatile("" ::: "memory");                   // (these loads before the stores below: see stores_behind)
         DICEMOE_SCHED_FENCE();
@@ -539,7 +546,10 @@ __global__ __launch_bounds__(512, 1) void ffn_gemm_bf16_stream_kernel(
             columns(q, BN);
             return q;
         };
-        stream_tiles<2, TN, 2, 2, TN == 3 ? 4 : 3, GELU, GATHER, 4, 2>(g, smem, n_whole, first, place);
+        // 256 columns without GELU: wavefronts of 128 x 64 (2048 x 8192, 4 x 2048 rows, second GEMM: 1.42 - 1.55 us a step against 1.51 - 1.57
+        // of 64 x 128, epilogue 2.7 - 2.9 against 3.1; with GELU, whose stores are the more, 1.69 against 1.59 at DiT-MoE-XL widths)
+        if constexpr (TN == 4 && !GELU) stream_tiles<4, 2, 2, 2, 3, GELU, GATHER, 2, 4>(g, smem, n_whole, first, place);
+        else stream_tiles<2, TN, 2, 2, TN == 3 ? 4 : 3, GELU, GATHER, 4, 2>(g, smem, n_whole, first, place);
     }
     if (pieces > 1 && slot < left * pieces) {
         const int tile = slot / pieces, piece = slot - tile * pieces;
