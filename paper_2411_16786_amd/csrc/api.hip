@@ -337,7 +337,7 @@ static int expert_ffn_common(moe_ctx* ctx, const char* who, const void* x_rows, 
                              const int32_t* seg_offsets, const int32_t* seg_expert, int32_t n_segments,
                              int32_t max_rows, const void* W1, const float* b1, const void* W2, const float* b2,
                              void* h_packed, const int32_t* out_pairs, void* workspace, void* stream,
-                             dicemoe::SplitSums* sums = nullptr)
+                             dicemoe::SplitSums* sums = nullptr, const dicemoe::PairSort* sort = nullptr)
 {
     const moe_shape& s = ctx->shape;
     if (int rc = check_ffn(ctx, who, x_rows, seg_offsets, seg_expert, n_segments, max_rows, W1, W2, h_packed, workspace)) return rc;
@@ -356,7 +356,7 @@ static int expert_ffn_common(moe_ctx* ctx, const char* who, const void* x_rows, 
                                         is_bf16(ctx) ? ws + status_offset(ctx) - dicemoe::kSplitKBytes : nullptr,
                                         is_bf16(ctx) ? dicemoe::kSplitKBytes : 0,
                                         reinterpret_cast<int32_t*>(ws + status_offset(ctx)), static_cast<hipStream_t>(stream),
-                                        ctx->ffn_between, sums),
+                                        ctx->ffn_between, sums, sort),
                       who);
 }
 
@@ -507,17 +507,25 @@ int moe_layer_forward(moe_ctx* ctx, const moe_layer_args* a, const moe_policy* p
         return rc;
     if (int rc = check_combine(ctx, h_packed, a->inv, a->scores, mask, a->T, H_cache, S_cache, a->y)) return rc;
 
-    if (int rc = route_launches(ctx, "moe_layer_forward", a->x, a->Wg, a->bg, a->T, policy, routed, a->scores, a->expert_idx, a->probs_all,
-                                a->logits, a->mask, a->n_refresh, fuse ? nullptr : a->x_packed, a->counts, a->offsets, a->perm, a->inv,
-                                a->workspace, stream))
+    // A few pairs, all of them or as an elementwise policy says: the first GEMM sorts them itself, and the dispatch's launch goes
+    dicemoe::PairSort sort = {a->expert_idx, a->T * slots(ctx), experts(ctx), {}, a->counts, a->offsets, a->perm, a->inv};
+    if (policy) sort.rule = refresh_rule(ctx, policy, a->T, routed, a->scores, a->mask, a->n_refresh);
+    const bool own_sort = fuse && a->n_segments == experts(ctx) && !sort.rule.select &&
+                          ffn_sorts_pairs(is_bf16(ctx), sort.n_pairs, a->n_segments, experts(ctx), rows, ctx->shape.d, ctx->shape.F);
+    if (own_sort) {
+        if (int rc = moe_gate(ctx, a->x, a->Wg, a->bg, a->T, a->scores, a->expert_idx, a->probs_all, a->logits, stream)) return rc;
+    } else if (int rc = route_launches(ctx, "moe_layer_forward", a->x, a->Wg, a->bg, a->T, policy, routed, a->scores, a->expert_idx,
+                                       a->probs_all, a->logits, a->mask, a->n_refresh, fuse ? nullptr : a->x_packed, a->counts, a->offsets,
+                                       a->perm, a->inv, a->workspace, stream)) {
         return rc;
+    }
     // packed rows (read by token through perm, or from the send buffer) -> h rows, in h_packed or at their pairs' places in the
     // cache.  A split second GEMM leaves its float shares to the combine.
     dicemoe::SplitSums sums;
     const bool can_add = is_bf16(ctx) && slots(ctx) <= dicemoe::kSumsMaxSlots && a->n_segments == experts(ctx);
     if (int rc = expert_ffn_common(ctx, "moe_layer_forward", fuse ? a->x : a->x_packed, fuse ? a->perm : nullptr, a->offsets,
                                    a->seg_expert, a->n_segments, rows, a->W1, a->b1, a->W2, a->b2, to_cache ? H_cache : h_packed,
-                                   to_cache ? a->perm : nullptr, a->workspace, stream, can_add ? &sums : nullptr))
+                                   to_cache ? a->perm : nullptr, a->workspace, stream, can_add ? &sums : nullptr, own_sort ? &sort : nullptr))
         return rc;
     const int use_fresh = policy && policy->use_fresh_scores ? 1 : 0;
     if (sums.shares > 1)

@@ -21,7 +21,7 @@
 #include <mutex>
 #include <type_traits>
 
-#include "refresh_rule.hpp"
+#include "pair_sort.hpp"
 
 namespace dicemoe {
 
@@ -33,28 +33,6 @@ constexpr int kIdxWaves = kIdxThreads / kWave;
 // pairs four wavefronts do it: fewer to wait for at the barriers.
 constexpr int kAlonePairs = 4096;
 constexpr int kNoScratchPairs = 2048;         // (a promise of moe_dispatch: up to these the workspace may be null)
-
-// order this wavefront's LDS accesses: reads before the point complete before writes after it
-// are issued, and the compiler keeps them on their side
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-// lanes of this wave that are live and hold the same expert id as the calling lane; nbits = number of
-// bits an expert id can have (ballots are scalar work)
-__device__ __forceinline__ uint64_t same_expert_peers(bool live, int e, int nbits) {
-    uint64_t peers = __ballot(live);
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        if (b < nbits) {                          // uniform
-            const bool bit = (e >> b) & 1;
-            const uint64_t bb = __ballot(bit);
-            peers &= bit ? bb : ~bb;
-        }
-    }
-    return peers;
-}
 
 // Where the dispatch takes the mask from: an array (or none: every pair), an elementwise policy, or a selection of tokens
 // made by this workgroup (`bits`: one bit per token, in LDS).  The mask of the last two is written out by the way.

@@ -268,7 +268,8 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
                                         const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts,
                                         int max_rows, hipStream_t stream, const int32_t* row_index = nullptr,
                                         int row_div = 1, const int32_t* out_index = nullptr, float* partial = nullptr,
-                                        size_t partial_bytes = 0, int32_t* status = nullptr, SplitSums* sums = nullptr)
+                                        size_t partial_bytes = 0, int32_t* status = nullptr, SplitSums* sums = nullptr,
+                                        const PairSort* sort = nullptr)
 {
     const int by_expert = n_seg <= 64 ? 1 : 0;
     const FfnPlan plan = plan_ffn_gemm(GELU, N, K, max_rows, n_seg, n_experts, partial ? partial_bytes : 0, sums != nullptr);
@@ -285,6 +286,17 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
         if (err != hipSuccess || sums) return err;                                                                           \
         return launch_splitk_reduce(partial, plan.shares, bias, C, N, seg_offsets, seg_expert, n_seg, max_rows, out_index, stream); \
     } while (0)
+    if (sort) {                                  // (ffn_sorts_pairs)
+        if constexpr (GELU) {
+            if (plan.tile == FfnTile::Small64)
+                return launch_gemm_bf16_wide<1, 2, 2, 3, 3, GELU, 2, 2, true>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,
+                                                                              row_div, out_index, by_expert, nullptr, 1, status, *sort);
+            if (plan.tile == FfnTile::Mid192Deep)
+                return launch_gemm_bf16_wide<1, 3, 2, 3, 3, GELU, 4, 2, true>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,
+                                                                              row_div, out_index, by_expert, nullptr, 1, status, *sort);
+        }
+        return hipErrorInvalidValue;
+    }
     switch (plan.tile) {
     case FfnTile::Stream192:
         return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
@@ -336,6 +348,8 @@ static hipError_t configure_gemm_bf16_auto()
     hipError_t err = configure_gemm_bf16_wide<1, 2, 2, 3, 3, GELU>();
     if constexpr (GELU) {
         if (err == hipSuccess) err = configure_gemm_bf16_wide<1, 3, 2, 3, 3, GELU, 4, 2>();
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<1, 3, 2, 3, 3, GELU, 4, 2, true>();
+        if (err == hipSuccess) err = configure_gemm_bf16_wide<1, 2, 2, 3, 3, GELU, 2, 2, true>();
     } else {
         if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 3, 3, GELU>();
         if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 3, GELU, 4, 2>();
@@ -354,30 +368,50 @@ hipError_t prepare_expert_ffn()
     hipError_t err = configure_gemm_bf16_auto<true>();
     if (err == hipSuccess) err = configure_gemm_bf16_auto<false>();
     if (err == hipSuccess) err = configure_gemm_f32_ring<true, 2, 2, 2>();
+    if (err == hipSuccess) err = configure_gemm_f32_ring<true, 2, 2, 2, true>();
     if (err == hipSuccess) err = configure_gemm_f32_ring<false, 2, 2, 2>();
     if (err == hipSuccess) err = configure_gemm_f32_ring<true, 4, 4, 2>();
     if (err == hipSuccess) err = configure_gemm_f32_ring<false, 4, 4, 2>();
     return err;
 }
 
+// Where the first GEMM's workgroups run in about one round: each sorts once, while the loads it saves would have taken as long.  In several
+// rounds the sort comes again with every workgroup (whole layers, us, dispatch / own sort: 64 x 256 float, 64 tokens 28.4 / 24.8; DiT-MoE-S, 60
+// tokens 28.2 / 25.4, 500 tokens 33.9 / 32.1; DiT-MoE-XL, 138 tokens 61.2 / 59.4, 256 tokens 69.4 / 67.5; but DiT-MoE-G, 132 tokens with a shared expert,
+// 952 tiles, 214.3 / 215.5; DiT-MoE-XL, 500 tokens, 720 tiles, 82.0 / 82.1).
+bool ffn_sorts_pairs(bool bf16, int n_pairs, int n_seg, int n_experts, int max_rows, int d, int F)
+{
+    if (n_pairs < 1 || n_pairs > kOwnSortPairs || n_seg != n_experts || max_rows < 1) return false;
+    auto tiles = [&](int bm, int bn) {
+        const int row_tiles = max_rows / bm + n_seg / 2;
+        return static_cast<long long>(row_tiles > n_seg ? row_tiles : n_seg) * ((F + bn - 1) / bn);
+    };
+    if (bf16) {
+        const FfnTile tile = plan_ffn_gemm(true, F, d, max_rows, n_seg, n_experts, 0).tile;
+        return (tile == FfnTile::Small64 && tiles(64, 128) <= 2 * kComputeUnits) || (tile == FfnTile::Mid192Deep && tiles(128, 192) <= kComputeUnits);
+    }
+    const F32Tile tile = f32_tile(F, d, max_rows, n_seg);
+    return tile == F32Tile::Ring32 || (tile == F32Tile::Direct32 && tiles(32, 32) <= 4 * kComputeUnits);
+}
+
 hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_index, int row_div,
                              const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts, int max_rows, int d,
                              int F, const void* W1, const float* b1, const void* W2, const float* b2, void* h_packed,
                              const int32_t* out_index, void* hidden, void* partial, size_t partial_bytes,
-                             int32_t* status, hipStream_t stream, hipEvent_t between, SplitSums* sums)
+                             int32_t* status, hipStream_t stream, hipEvent_t between, SplitSums* sums, const PairSort* sort)
 {
     if (max_rows == 0) return launch_row_overflow_check(status, seg_offsets, n_seg, stream);
     hipError_t err;
     if (bf16) {
         err = launch_gemm_bf16_auto<true>(x_rows, W1, b1, hidden, F, d, seg_offsets, seg_expert, n_seg, n_experts, max_rows, stream,
-                                          row_index, row_div, nullptr, nullptr, 0, status);
+                                          row_index, row_div, nullptr, nullptr, 0, status, nullptr, sort);
         if (err != hipSuccess) return err;
         if (between != nullptr && (err = hipEventRecord(between, stream)) != hipSuccess) return err;
         return launch_gemm_bf16_auto<false>(hidden, W2, b2, h_packed, d, F, seg_offsets, seg_expert, n_seg, n_experts, max_rows, stream,
                                             nullptr, 1, out_index, static_cast<float*>(partial), partial_bytes, nullptr, sums);
     }
     err = launch_gemm_f32<true>(x_rows, W1, b1, hidden, F, d, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index,
-                                row_div, nullptr, status);
+                                row_div, nullptr, status, sort);
     if (err != hipSuccess) return err;
     if (between != nullptr && (err = hipEventRecord(between, stream)) != hipSuccess) return err;
     return launch_gemm_f32<false>(hidden, W2, b2, h_packed, d, F, seg_offsets, seg_expert, n_seg, max_rows, stream, nullptr, 1,

@@ -57,24 +57,33 @@ __device__ __forceinline__ bool find_row_tile_by_lanes(const int32_t* __restrict
 
 // TM, TN: 16-row blocks of a tile, rows and columns; U: units in flight; MANY: more segments than a wavefront has lanes (a kernel of
 // its own: with both ways of finding a tile in one, 500 tokens of the DiT-MoE-S widths take 2 us more)
-template <bool GELU, int TM, int TN, int U, bool MANY>
+template <bool GELU, int TM, int TN, int U, bool MANY, bool SELF>
 __global__ __launch_bounds__(64 * kDirectShares, TM * TN > 4 ? 2 : 4) void ffn_gemm_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias, float* __restrict__ C, int N, int K,
     const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert, int n_seg, int n_tiles_n,
     const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index, int max_rows,
-    int32_t* __restrict__ status)
+    int32_t* __restrict__ status, OwnSort<SELF> sort)
 {
     typedef RowMfma<float> M;
     constexpr int KS = kDirectShares;
+    static_assert(!(SELF && MANY), "a workgroup that sorts the pairs itself knows 64 experts at most");
     constexpr int BM = 16 * TM, BN = 16 * TN, BLOCKS = TM * TN;
     constexpr int CH = 4;                                // 16-byte chunks per unit
     __shared__ __attribute__((aligned(16))) f32x4_t part[KS][BLOCKS][64];
-    report_row_overflow(status, seg_offsets, n_seg, max_rows);
+    const int32_t* seg_table = seg_offsets;
+    const uint16_t* own_rows = nullptr;
+    if constexpr (SELF) {                                // this workgroup's own dispatch
+        __shared__ int scratch[own_sort_ints(KS)];
+        __shared__ uint16_t rows_lds[kOwnSortPairs];
+        seg_table = sort_pairs<KS>(sort, blockIdx.x == 0, scratch, rows_lds);
+        own_rows = rows_lds;
+    }
+    report_row_overflow(status, seg_table, n_seg, max_rows);
 
     // ---- place: the tiles of an expert on one XCD (its weights and rows stay in that XCD's L2) while the segment table
     // fits a wavefront, else in segment order
     XcdTiles tiles;
-    if constexpr (!MANY) tiles.deal(seg_offsets, seg_expert, n_seg, BM, BN, n_tiles_n, blockIdx.x & 7, max_rows);
+    if constexpr (!MANY) tiles.deal(seg_table, seg_expert, n_seg, BM, BN, n_tiles_n, blockIdx.x & 7, max_rows);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = lane & 15, quarter = lane >> 4;
@@ -113,7 +122,8 @@ __global__ __launch_bounds__(64 * kDirectShares, TM * TN > 4 ? 2 : 4) void ffn_g
         for (int i = 0; i < TM; ++i) {
             int r = row0 + 16 * i + sub;
             r = r < row_end ? r : row_end - 1;               // rows past the segment repeat its last one; never stored
-            if (row_index) r = row_index[r] / row_div;
+            if constexpr (SELF) r = own_rows[r] / row_div;
+            else if (row_index) r = row_index[r] / row_div;
             a_src[i] = reinterpret_cast<const u32x4_t*>(A + static_cast<size_t>(r) * K) + u0 * CH + quarter;
         }
         f32x4_t acc[TM][TN];
@@ -191,16 +201,23 @@ template <bool GELU, int TM, int TN, int U>
 static hipError_t launch_gemm_f32_tile(const float* A, const float* W, const float* bias, float* C, int N, int K,
                                        const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
                                        hipStream_t stream, const int32_t* row_index, int row_div, const int32_t* out_index,
-                                       int32_t* status)
+                                       int32_t* status, const PairSort* sort = nullptr)
 {
     constexpr int BM = 16 * TM, BN = 16 * TN;
     const int n_tiles_n = (N + BN - 1) / BN;
     const long long tiles = (static_cast<long long>(max_rows) + BM - 1) / BM * n_tiles_n + static_cast<long long>(n_seg) * n_tiles_n;
     const long long blocks = (tiles + 7) / 8 * 8;        // every XCD gets room for ceil(tiles / 8)
-    const auto kern = n_seg > 64 ? &ffn_gemm_f32_kernel<GELU, TM, TN, U, true> : &ffn_gemm_f32_kernel<GELU, TM, TN, U, false>;
-    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(blocks < kDirectGrid ? blocks : kDirectGrid)),
-                       dim3(64 * kDirectShares), 0, stream, A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, n_tiles_n, row_index,
-                       row_div, out_index, max_rows, status);
+    const dim3 grid(static_cast<unsigned>(blocks < kDirectGrid ? blocks : kDirectGrid));
+    if constexpr (GELU && TM * TN <= 4) {
+        if (sort) {
+            hipLaunchKernelGGL((ffn_gemm_f32_kernel<GELU, TM, TN, U, false, true>), grid, dim3(64 * kDirectShares), 0, stream, A, W, bias, C, N, K,
+                               seg_offsets, seg_expert, n_seg, n_tiles_n, row_index, row_div, out_index, max_rows, status, *sort);
+            return hipGetLastError();
+        }
+    }
+    const auto kern = n_seg > 64 ? &ffn_gemm_f32_kernel<GELU, TM, TN, U, true, false> : &ffn_gemm_f32_kernel<GELU, TM, TN, U, false, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(64 * kDirectShares), 0, stream, A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, n_tiles_n, row_index,
+                       row_div, out_index, max_rows, status, NoSort{});
     return hipGetLastError();
 }
 
@@ -220,13 +237,16 @@ static hipError_t launch_gemm_f32_tile(const float* A, const float* W, const flo
 // DiT-MoE-XL, 100 tokens 157 / 103, 2000: 984 / 880; 2048 x 8192, 4 experts, 200 tokens 458 / 309.
 // K is a multiple of 128 (equal shares of whole stages) and at least kRingMinK (two stages a share).
 constexpr int kRingMinK = 256;
-constexpr int ring_lds(int tm, int tn, int d) { return kDirectShares * (d * 16 * (tm + tn) * 128 + (kDirectShares - 1) * 1024 + 768); }
-template <bool GELU, int TM, int TN, int D>
-__global__ __launch_bounds__(64 * kDirectShares, ring_lds(TM, TN, D) <= 80 * 1024 ? 2 : 1) void ffn_gemm_f32_ring_kernel(
+constexpr int ring_lds(int tm, int tn, int d, bool self = false)
+{
+    return kDirectShares * (d * 16 * (tm + tn) * 128 + (kDirectShares - 1) * 1024 + (self ? 512 : 768)) + (self ? kOwnSortPairs * 2 : 0);
+}
+template <bool GELU, int TM, int TN, int D, bool SELF>
+__global__ __launch_bounds__(64 * kDirectShares, ring_lds(TM, TN, D, SELF) <= 80 * 1024 ? 2 : 1) void ffn_gemm_f32_ring_kernel(
     const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ bias, float* __restrict__ C, int N, int K,
     const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert, int n_seg, int n_tiles_n,
     const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index, int max_rows,
-    int32_t* __restrict__ status)
+    int32_t* __restrict__ status, OwnSort<SELF> sort)
 {
     typedef RowMfma<float> M;
     constexpr int KS = kDirectShares;
@@ -237,19 +257,27 @@ __global__ __launch_bounds__(64 * kDirectShares, ring_lds(TM, TN, D) <= 80 * 102
     static_assert(32 * KS * D <= kRingMinK, "a share of K has D stages at least: what is asked for a tile ahead has landed by then");
     static_assert(TM * TN % KS == 0 && BN <= 64 && BM <= 64, "blocks for every wavefront; a lane each for a tile's columns and rows");
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    report_row_overflow(status, seg_offsets, n_seg, max_rows);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int sub = lane & 15, quarter = lane >> 4;
     char* const ring = smem + wave * D * STAGE;
     f32x4_t* const meet = reinterpret_cast<f32x4_t*>(smem + KS * D * STAGE);      // [KS][KS - 1][64]
-    char* const aux = smem + KS * D * STAGE + KS * (KS - 1) * 1024 + wave * 768;
-    int32_t* const rows_lds = reinterpret_cast<int32_t*>(aux);                    // row indices of the tile that the ring goes on to
-    int32_t* const dst_lds = reinterpret_cast<int32_t*>(aux + 256);               // output rows and biases of the tile that is multiplied
-    float* const bias_lds = reinterpret_cast<float*>(aux + 512);
+    char* const behind = smem + KS * D * STAGE + KS * (KS - 1) * 1024;
+    char* const aux = behind + wave * (SELF ? 512 : 768);
+    int32_t* const dst_lds = reinterpret_cast<int32_t*>(aux);                     // output rows and biases of the tile that is multiplied
+    float* const bias_lds = reinterpret_cast<float*>(aux + 256);
+    int32_t* const rows_lds = reinterpret_cast<int32_t*>(aux + 512);              // row indices of the tile that the ring goes on to
+    uint16_t* const own_rows = reinterpret_cast<uint16_t*>(behind + KS * 512);    // SELF: all of them, sorted by this workgroup
 
+    const int32_t* seg_table = seg_offsets;
+    if constexpr (SELF) {
+        static_assert(own_sort_ints(KS) * 4 <= KS * (KS - 1) * 1024, "the sort's scratch fits the place where the sums meet");
+        seg_table = sort_pairs<KS>(sort, blockIdx.x == 0, reinterpret_cast<int*>(meet), own_rows);
+    }
+    report_row_overflow(status, seg_table, n_seg, max_rows);
     XcdTiles tiles;
-    tiles.deal(seg_offsets, seg_expert, n_seg, BM, BN, n_tiles_n, blockIdx.x & 7, max_rows);
+    tiles.deal(seg_table, seg_expert, n_seg, BM, BN, n_tiles_n, blockIdx.x & 7, max_rows);
+    if constexpr (SELF) __syncthreads();                 // every wavefront has the table: sums can meet where it was
     const int slot = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
     const int n_items = tiles.count > slot ? (tiles.count - slot + n_slots - 1) / n_slots : 0;
     if (n_items == 0) return;
@@ -269,7 +297,7 @@ __global__ __launch_bounds__(64 * kDirectShares, ring_lds(TM, TN, D) <= 80 * 102
     };
     auto row_of = [&](const Item& t, int i) { return t.row0 + i < t.row_end ? t.row0 + i : t.row_end - 1; };      // (rows past the end repeat the last one)
     auto ask_rows = [&](const Item& t) {
-        if (row_index) to_lds(row_index, row_of(t, lane), rows_lds);
+        if (!SELF && row_index) to_lds(row_index, row_of(t, lane), rows_lds);
     };
     // Load q of a stage fills rows 8q .. 8q + 7; lane l lands at LDS slot (row 8q + l / 8, l % 8) and fetches the chunk that the swizzle
     // assigns to it.
@@ -279,7 +307,7 @@ __global__ __launch_bounds__(64 * kDirectShares, ring_lds(TM, TN, D) <= 80 * 102
 #pragma unroll
         for (int q = 0; q < QA; ++q) {
             const int i = 8 * q + (lane >> 3);
-            const int r = row_index ? rows_lds[i] / row_div : row_of(t, i);
+            const int r = SELF ? own_rows[row_of(t, i)] / row_div : row_index ? rows_lds[i] / row_div : row_of(t, i);
             a_src[q] = reinterpret_cast<const char*>(A + static_cast<size_t>(r) * K + s0 * 32) + ((lane & 7) ^ chunk_swizzle<CH>(i)) * 16;
         }
 #pragma unroll
@@ -426,22 +454,22 @@ __global__ __launch_bounds__(64 * kDirectShares, ring_lds(TM, TN, D) <= 80 * 102
     }
 }
 
-template <bool GELU, int TM, int TN, int D>
+template <bool GELU, int TM, int TN, int D, bool SELF = false>
 static hipError_t configure_gemm_f32_ring()
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm_f32_ring_kernel<GELU, TM, TN, D>), hipFuncAttributeMaxDynamicSharedMemorySize, ring_lds(TM, TN, D));
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm_f32_ring_kernel<GELU, TM, TN, D, SELF>), hipFuncAttributeMaxDynamicSharedMemorySize, ring_lds(TM, TN, D, SELF));
 }
 
-template <bool GELU, int TM, int TN, int D>
+template <bool GELU, int TM, int TN, int D, bool SELF = false>
 static hipError_t launch_gemm_f32_ring(const float* A, const float* W, const float* bias, float* C, int N, int K,
                                        const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
                                        hipStream_t stream, const int32_t* row_index, int row_div, const int32_t* out_index,
-                                       int32_t* status)
+                                       int32_t* status, OwnSort<SELF> sort = {})
 {
-    constexpr int BN = 16 * TN, smem = ring_lds(TM, TN, D);
+    constexpr int BN = 16 * TN, smem = ring_lds(TM, TN, D, SELF);
     static_assert(smem <= 160 * 1024, "the rings and the meeting place fit a compute unit's LDS");
-    hipLaunchKernelGGL((ffn_gemm_f32_ring_kernel<GELU, TM, TN, D>), dim3(kStreamGrid * (smem <= 80 * 1024 ? 2 : 1)), dim3(64 * kDirectShares), smem, stream, A, W, bias, C, N, K,
-                       seg_offsets, seg_expert, n_seg, (N + BN - 1) / BN, row_index, row_div, out_index, max_rows, status);
+    hipLaunchKernelGGL((ffn_gemm_f32_ring_kernel<GELU, TM, TN, D, SELF>), dim3(kStreamGrid * (smem <= 80 * 1024 ? 2 : 1)), dim3(64 * kDirectShares), smem, stream, A, W, bias, C, N, K,
+                       seg_offsets, seg_expert, n_seg, (N + BN - 1) / BN, row_index, row_div, out_index, max_rows, status, sort);
     return hipGetLastError();
 }
 
@@ -460,23 +488,39 @@ static bool ring_wide(int N, int K, int max_rows, int n_seg)
 // (a segment ends in half a tile on average).  One GEMM, us, 32 x 32 tiles / what 64 x 64 change: second GEMM of DiT-MoE-S, 330 tiles
 // + 5, 612: - 4, 798: - 42, 1584: - 126; 2048 x 8192, 4 experts, 576 tiles + 10; first GEMM of DiT-MoE-S, 94 rows an expert + 5,
 // 125 rows, 940 tiles - 3, 375 rows - 21; 512 x 2048, 64 experts, 31 rows an expert, 2048 tiles + 10, 128 rows - 69.
+enum class F32Tile { Ring32, Ring64, Direct32, Direct64 };
+static F32Tile f32_tile(int N, int K, int max_rows, int n_seg)
+{
+    if (n_seg <= 64 && K % 128 == 0 && K >= kRingMinK) return ring_wide(N, K, max_rows, n_seg) ? F32Tile::Ring64 : F32Tile::Ring32;
+    const long long tiles = (max_rows / 64 + n_seg / 2ll) * ((N + 63) / 64);
+    return tiles >= 640 && max_rows >= 96ll * n_seg ? F32Tile::Direct64 : F32Tile::Direct32;
+}
+
 template <bool GELU>
 static hipError_t launch_gemm_f32(const void* A, const void* W, const float* bias, void* C, int N, int K,
                                   const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
                                   hipStream_t stream, const int32_t* row_index = nullptr, int row_div = 1,
-                                  const int32_t* out_index = nullptr, int32_t* status = nullptr)
+                                  const int32_t* out_index = nullptr, int32_t* status = nullptr, const PairSort* sort = nullptr)
 {
     const float *a = static_cast<const float*>(A), *w = static_cast<const float*>(W);
     float* c = static_cast<float*>(C);
-    if (n_seg <= 64 && K % 128 == 0 && K >= kRingMinK) {
-        if (ring_wide(N, K, max_rows, n_seg))
-            return launch_gemm_f32_ring<GELU, 4, 4, 2>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
-        return launch_gemm_f32_ring<GELU, 2, 2, 2>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+#define DICEMOE_F32(fn, ...) return fn<GELU, __VA_ARGS__>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status
+    switch (f32_tile(N, K, max_rows, n_seg)) {
+    case F32Tile::Ring64:
+        if (sort) break;                                 // (ffn_sorts_pairs)
+        DICEMOE_F32(launch_gemm_f32_ring, 4, 4, 2));
+    case F32Tile::Ring32:
+        if constexpr (GELU) {
+            if (sort) DICEMOE_F32(launch_gemm_f32_ring, 2, 2, 2, true), *sort);
+        }
+        DICEMOE_F32(launch_gemm_f32_ring, 2, 2, 2));
+    case F32Tile::Direct64:
+        if (sort) break;
+        DICEMOE_F32(launch_gemm_f32_tile, 4, 4, 1));
+    case F32Tile::Direct32: DICEMOE_F32(launch_gemm_f32_tile, 2, 2, 3), sort);
     }
-    const long long tiles = (max_rows / 64 + n_seg / 2ll) * ((N + 63) / 64);
-    if (tiles >= 640 && max_rows >= 96ll * n_seg)
-        return launch_gemm_f32_tile<GELU, 4, 4, 1>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
-    return launch_gemm_f32_tile<GELU, 2, 2, 3>(a, w, bias, c, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+#undef DICEMOE_F32
+    return hipErrorInvalidValue;
 }
 
 }  // namespace dicemoe

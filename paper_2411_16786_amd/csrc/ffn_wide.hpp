@@ -14,6 +14,7 @@
 #pragma once
 #include <type_traits>
 #include "ffn_mfma.hpp"
+#include "pair_sort.hpp"
 
 namespace dicemoe {
 
@@ -29,13 +30,17 @@ constexpr int wide_occupancy(int tm, int tn, int ast, int wst, int wgm, int wgn)
     return (ast * tm * wgm + wst * tn * wgn) * 32 * 128 <= 80 * 1024 ? 2 : 1;
 }
 
-template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, int WGM, int WGN>
+// Kernels that sort the pairs themselves (SELF) have one argument more
+struct NoSort {};
+template <bool SELF> using OwnSort = std::conditional_t<SELF, PairSort, NoSort>;
+
+template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, int WGM, int WGN, bool SELF = false>
 __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WGM, WGN)) void ffn_gemm_bf16_wide_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const float* __restrict__ bias,
     bf16_t* __restrict__ C, int N, int K, const int32_t* __restrict__ seg_offsets,
     const int32_t* __restrict__ seg_expert, int n_seg, int n_tiles_n, int m_tiles_max,
     const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index, int by_expert,
-    float* __restrict__ partial, int partial_rows, int32_t* __restrict__ status)
+    float* __restrict__ partial, int partial_rows, int32_t* __restrict__ status, OwnSort<SELF> sort)
 {
     constexpr int NW = WGM * WGN;                  // wavefronts, WGM along the rows by WGN along the columns
     constexpr int BM = 32 * TM * WGM, BN = 32 * TN * WGN;
@@ -58,12 +63,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
     char* const a_lds = smem;
     char* const w_lds = smem + AST * ABYTES;
 
+    // ---- SELF: this workgroup's own dispatch, in the LDS that the activations' ring takes later
+    const int32_t* seg_table = seg_offsets;
+    const uint16_t* own_rows = nullptr;
+    if constexpr (SELF) {
+        static_assert(own_sort_ints(NW) * 4 + kOwnSortPairs * 2 <= AST * ABYTES, "the sort fits the activations' ring");
+        int* const scratch = reinterpret_cast<int*>(a_lds);
+        uint16_t* const rows_lds = reinterpret_cast<uint16_t*>(scratch + own_sort_ints(NW));
+        seg_table = sort_pairs<NW>(sort, blockIdx.x == 0 && blockIdx.y == 0, scratch, rows_lds);
+        own_rows = rows_lds;
+    }
     // launch check for the caller: did the segment table hold more rows than the grid was sized for?
-    report_row_overflow(status, seg_offsets, n_seg, partial_rows);
+    report_row_overflow(status, seg_table, n_seg, partial_rows);
     // ---- which tile (bands of GROUP_M row tiles, XCD x takes the x-th eighth of the sequence)
     int seg, row0, row_end, tile_n, e = -1;
     if (by_expert) {
-        if (!find_tile_by_expert(seg_offsets, seg_expert, n_seg, BM, n_tiles_n, GROUP_M, blockIdx.x, seg, row0, row_end,
+        if (!find_tile_by_expert(seg_table, seg_expert, n_seg, BM, n_tiles_n, GROUP_M, blockIdx.x, seg, row0, row_end,
                                  tile_n, e))
             return;
     } else {
@@ -106,12 +121,15 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
         a_row[i] = row0 + (wave * QA + i) * 8 + (lane >> 3);
         if (a_row[i] >= row_end) a_row[i] = row_end - 1;      // tail rows repeat the last row
     }
-    if (row_index) {
+    if constexpr (SELF) {
+#pragma unroll
+        for (int i = 0; i < QA; ++i) a_row[i] = own_rows[a_row[i]];
+    } else if (row_index) {
 #pragma unroll
         for (int i = 0; i < QA; ++i) a_row[i] = row_index[a_row[i]];
     }
     auto a_offsets = [&] {
-        if (row_index) {
+        if (SELF || row_index) {
 #pragma unroll
             for (int i = 0; i < QA; ++i) a_row[i] /= row_div;
         }
@@ -203,6 +221,10 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
         for (int s = 0; s < nk; ++s) ask_weights(s);
     }
     a_offsets();
+    if constexpr (SELF) {                            // every wavefront has its rows: their place can take stages
+        wait_lgkmcnt<0>();
+        block_barrier();
+    }
 #pragma unroll
     for (int s = 0; s < AST; ++s) {
         if (s < nk) {
@@ -417,23 +439,25 @@ __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WG
 
 // The wide kernels use more dynamic LDS than a launch may ask for by default; the limit is a
 // per-device attribute of each kernel, raised by prepare_expert_ffn() before the first launch on a device.
-template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, int WGM = 2, int WGN = 2>
+template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, int WGM = 2, int WGN = 2, bool SELF = false>
 static hipError_t configure_gemm_bf16_wide()
 {
     constexpr int smem = (AST * 32 * TM * WGM + WST * 32 * TN * WGN) * 128;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm_bf16_wide_kernel<TM, TN, SPREAD, AST, WST, GELU, WGM, WGN>),
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm_bf16_wide_kernel<TM, TN, SPREAD, AST, WST, GELU, WGM, WGN, SELF>),
                                hipFuncAttributeMaxDynamicSharedMemorySize, smem);
 }
 
-template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, int WGM = 2, int WGN = 2>
+template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, int WGM = 2, int WGN = 2, bool SELF = false>
 static hipError_t launch_gemm_bf16_wide(const void* A, const void* W, const float* bias, void* C, int N, int K,
                                         const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg,
                                         int max_rows, hipStream_t stream, const int32_t* row_index = nullptr,
                                         int row_div = 1, const int32_t* out_index = nullptr, int by_expert = 0,
-                                        float* partial = nullptr, int k_splits = 1, int32_t* status = nullptr)
+                                        float* partial = nullptr, int k_splits = 1, int32_t* status = nullptr,
+                                        OwnSort<SELF> sort = {})
 {
     constexpr int BM = 32 * TM * WGM, BN = 32 * TN * WGN;
-    auto kern = ffn_gemm_bf16_wide_kernel<TM, TN, SPREAD, AST, WST, GELU, WGM, WGN>;
+    auto kern = ffn_gemm_bf16_wide_kernel<TM, TN, SPREAD, AST, WST, GELU, WGM, WGN, SELF>;
+    if (SELF && !by_expert) return hipErrorInvalidValue;
     constexpr int smem = (AST * BM + WST * BN) * 128;
     if (k_splits < 1 || (k_splits > 1 && (!partial || GELU))) return hipErrorInvalidValue;
     const int nk_min = K / 64 / k_splits;                         // steps of the smallest share
@@ -447,7 +471,7 @@ static hipError_t launch_gemm_bf16_wide(const void* A, const void* W, const floa
                        dim3(64 * WGM * WGN), smem, stream,
                        static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(W), bias, static_cast<bf16_t*>(C), N,
                        K, seg_offsets, seg_expert, n_seg, n_tiles_n, m_tiles, row_index, row_div, out_index, by_expert,
-                       k_splits > 1 ? partial : nullptr, max_rows, status);
+                       k_splits > 1 ? partial : nullptr, max_rows, status, sort);
     return hipGetLastError();
 }
 

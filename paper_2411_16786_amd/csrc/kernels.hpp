@@ -56,6 +56,17 @@ hipError_t launch_combine_sums(const SplitSums& sums, void* h_packed, const int3
                                const int32_t* seg_expert, const uint8_t* mask, int T_tok, int d, int k, int k_cached, void* H_cache, float* S_cache,
                                int use_fresh, void* y, hipStream_t stream);
 
+// The dispatch of a small layer, left to the first GEMM: pairs p of token p / slots with expert expert_idx[p], all of them (rule.mask null) or
+// those that an elementwise policy refreshes.  Its index outputs and the mask are written as launch_dispatch writes them.
+struct PairSort {
+    const int32_t* expert_idx;
+    int n_pairs, experts;
+    RefreshRule rule;
+    int32_t *counts, *offsets, *perm, *inv;
+};
+// Can the first GEMM of these sizes do it?
+bool ffn_sorts_pairs(bool bf16, int n_pairs, int n_seg, int n_experts, int max_rows, int d, int F);
+
 // x_rows is the packed buffer (row_index == nullptr) or the token matrix with row_index[r] / row_div
 // naming the row that packed row r reads; the h row of packed row r is written to row r of h_out, or
 // to row out_index[r] when out_index is given (scatter into a buffer indexed by pair id)
@@ -63,9 +74,11 @@ hipError_t launch_expert_ffn(bool bf16, const void* x_rows, const int32_t* row_i
                              const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int n_experts, int max_rows, int d,
                              int F, const void* W1, const float* b1, const void* W2, const float* b2, void* h_out,
                              const int32_t* out_index, void* hidden, void* partial, size_t partial_bytes,
-                             int32_t* status, hipStream_t stream, hipEvent_t between = nullptr, SplitSums* sums = nullptr);
+                             int32_t* status, hipStream_t stream, hipEvent_t between = nullptr, SplitSums* sums = nullptr,
+                             const PairSort* sort = nullptr);
 // sums: if given and the second GEMM is split, its second pass is left to launch_combine_sums and *sums says what to add (h_out and
 // out_index are then not used); otherwise sums->shares stays 0
+// sort: if given (ffn_sorts_pairs), row_index is its perm and seg_offsets its offsets, which the first GEMM writes
 // between: if given, recorded on the stream after the first GEMM has been enqueued (per-GEMM timing)
 // status (two int32 on the device, may be null): written by the first GEMM of every call, see
 // report_row_overflow in ffn_mfma.hpp.

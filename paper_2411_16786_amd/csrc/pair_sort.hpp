@@ -1,0 +1,121 @@
+// The stable sort of refreshed pairs by expert inside one workgroup, for kernels that use its result themselves: the first GEMM of a
+// small layer does its own dispatch, which takes the dispatch's launch out of the chain (every workgroup sorts, the first one leaves
+// the index arrays for the kernels behind).
+#pragma once
+#include "refresh_rule.hpp"
+
+namespace dicemoe {
+
+// order this wavefront's LDS accesses: reads before the point complete before writes after it
+// are issued, and the compiler keeps them on their side
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// lanes of this wave that are live and hold the same expert id as the calling lane; nbits = number of
+// bits an expert id can have (ballots are scalar work)
+__device__ __forceinline__ uint64_t same_expert_peers(bool live, int e, int nbits) {
+    uint64_t peers = __ballot(live);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        if (b < nbits) {                          // uniform
+            const bool bit = (e >> b) & 1;
+            const uint64_t bb = __ballot(bit);
+            peers &= bit ? bb : ~bb;
+        }
+    }
+    return peers;
+}
+
+// Pairs that a workgroup of the first GEMM sorts for itself.  What it costs there is about what the loads of the segment table and of the row
+// indices, one behind the other, cost otherwise; what it saves is a launch (figures at ffn_sorts_pairs).
+constexpr int kOwnSortPairs = 1024;
+constexpr int own_sort_ints(int waves) { return waves * kMaxExperts + kMaxExperts + 4; }      // scratch beside the row list
+
+// off[0 .. E]: offsets of the experts' rows; row[r]: pair of packed row r.  scratch: own_sort_ints(WAVES) ints of LDS, of which `off` is the
+// part behind the first WAVES * kMaxExperts.  All threads of the workgroup, behind whose last barrier the results can be read.
+template <int WAVES>
+__device__ __forceinline__ const int* sort_pairs(const PairSort& s, bool writer, int* scratch, uint16_t* row)
+{
+    constexpr int S = kOwnSortPairs / (WAVES * kWave);      // steps of a wavefront at most
+    int* const run = scratch;                               // [WAVES][kMaxExperts]
+    int* const off = scratch + WAVES * kMaxExperts;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int N = s.n_pairs, E = s.experts;
+    const int steps = (N + WAVES * kWave - 1) / (WAVES * kWave);
+    const int nbits = E > 1 ? 32 - __builtin_clz(static_cast<unsigned>(E - 1)) : 0;
+    const int p0 = wave * steps * kWave + lane;
+    int ev[S], rank[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const int p = p0 + u * kWave;
+        ev[u] = s.expert_idx[p < N ? p : N - 1];
+    }
+    run[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        const int p = p0 + u * kWave;
+        rank[u] = 0;
+        if (u >= steps) { ev[u] = -1; continue; }           // (uniform)
+        bool ok = p < N && static_cast<unsigned>(ev[u]) < static_cast<unsigned>(E);
+        if (s.rule.mask) {
+            const uint8_t m = simple_mask(s.rule, p);
+            if (writer && p < N) s.rule.mask[p] = m;
+            ok = ok && m != 0;
+        }
+        if (!ok) ev[u] = -1;
+        const int e = ok ? ev[u] : 0;
+        const uint64_t peers = same_expert_peers(ok, e, nbits);
+        const int before = __popcll(peers & lanemask_lt());
+        const int so_far = run[wave * kMaxExperts + e];      // every peer reads the same running count ...
+        rank[u] = so_far + before;
+        wave_sync();
+        if (ok && before == 0) run[wave * kMaxExperts + e] = so_far + __popcll(peers);      // ... then the first updates it
+        wave_sync();
+    }
+    __syncthreads();
+    if (wave == 0) {                                         // lane e is expert e
+        int cnt[WAVES], total = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) cnt[w] = run[w * kMaxExperts + lane];
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) { run[w * kMaxExperts + lane] = total; total += cnt[w]; }
+        int incl = total;
+#pragma unroll
+        for (int sh = 1; sh < kWave; sh <<= 1) {
+            const int v = __shfl_up(incl, sh, kWave);
+            if (lane >= sh) incl += v;
+        }
+        if (lane == 0) off[0] = 0;
+        off[lane + 1] = incl;                                // (experts from E on have no pairs)
+        if (writer) {
+            if (lane < E) { s.counts[lane] = total; s.offsets[lane] = incl - total; }
+            if (lane == E - 1) s.offsets[E] = incl;
+            if (s.rule.mask && lane == 0) *s.rule.n_refresh = s.rule.n_value;
+        }
+    }
+    __syncthreads();
+    const int R = off[E];
+#pragma unroll
+    for (int u = 0; u < S; ++u) {
+        if (u >= steps) break;                               // (uniform)
+        const int p = p0 + u * kWave;
+        int r = -1;
+        if (ev[u] >= 0) {
+            r = off[ev[u]] + run[wave * kMaxExperts + ev[u]] + rank[u];
+            row[r] = static_cast<uint16_t>(p);
+        }
+        if (writer && p < N) {
+            if (r >= 0) s.perm[r] = p;
+            s.inv[p] = r;
+            if (p >= R) s.perm[p] = -1;                      // packed rows beyond the refreshed ones
+        }
+    }
+    __syncthreads();
+    return off;
+}
+
+}  // namespace dicemoe
