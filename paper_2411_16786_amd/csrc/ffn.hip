@@ -299,9 +299,9 @@ static hipError_t launch_gemm_bf16_auto(const void* A, const void* W, const floa
     }
     switch (plan.tile) {
     case FfnTile::Stream192:
-        return launch_gemm_bf16_stream<3, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+        return launch_gemm_bf16_stream<GELU>(192, A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
     case FfnTile::Stream256:
-        return launch_gemm_bf16_stream<4, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
+        return launch_gemm_bf16_stream<GELU>(256, A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status);
     case FfnTile::Small64:
         if (plan.shares > 1) DICEMOE_SHARES(1, 2, 2, 3, 3, GELU);
         DICEMOE_WIDE(1, 2, 2, 3, 3, GELU);
@@ -358,8 +358,7 @@ static hipError_t configure_gemm_bf16_auto()
         if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 2, 2, 3, 3, GELU>();
     }
     if (err == hipSuccess) err = configure_gemm_bf16_wide<2, 3, 2, 2, 2, GELU>();
-    if (err == hipSuccess) err = configure_gemm_bf16_stream<3, GELU>();
-    if (err == hipSuccess) err = configure_gemm_bf16_stream<4, GELU>();
+    if (err == hipSuccess) err = configure_gemm_bf16_stream<GELU>();
     return err;
 }
 

@@ -217,7 +217,7 @@ static hipError_t launch_gemm_f32_tile(const float* A, const float* W, const flo
     }
     const auto kern = n_seg > 64 ? &ffn_gemm_f32_kernel<GELU, TM, TN, U, true, false> : &ffn_gemm_f32_kernel<GELU, TM, TN, U, false, false>;
     hipLaunchKernelGGL(kern, grid, dim3(64 * kDirectShares), 0, stream, A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, n_tiles_n, row_index,
-                       row_div, out_index, max_rows, status, NoSort{});
+                       row_div, out_index, max_rows, status, NoMore{});
     return hipGetLastError();
 }
 

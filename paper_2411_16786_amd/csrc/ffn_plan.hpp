@@ -34,26 +34,69 @@ constexpr int leftover_pieces(int bn, int left, int slots)
     return left == 0 ? 1 : (bn == 256 && 4 * left <= slots ? 4 : (2 * left <= slots ? 2 : 1));
 }
 
-// Expected time (us) of one grouped GEMM on 256 x bn tiles.  The segment sizes live on the device; a segment ends in half a
-// row tile on average, and the count is averaged over the row tiles around that.  Measured on the DiT-MoE-XL, DiT-MoE-G
-// and expert-parallel widths: 1.06 (192 columns) and 1.42 us (256) per 64-deep step with all compute units busy,
-// 0.68 / 0.8 for a round of halves and 0.6 for quarters, epilogues 4.3 / 5.5 us with GELU and 2.6 / 4.2 without.
+// Expected time (us) of one grouped GEMM of the persistent kernel on 256 x bn tiles: what a round of whole tiles, of halves and of quarters costs.
+// Measured on the DiT-MoE-XL, DiT-MoE-G and expert-parallel widths: 1.06 (192 columns) and 1.42 us (256) per 64-deep step with all
+// compute units busy, 0.68 / 0.8 for a round of halves and 0.6 for quarters, epilogues 4.3 / 5.5 us with GELU and 2.6 / 4.2 without.
+struct StreamCost { int bn, cols; float whole, halves, quarters; };
+
+constexpr StreamCost stream_cost_of(int bn, int N, int K, bool gelu, float step_192 = 1.06f)
+{
+    const int nk = K / 64;
+    const float epilogue = gelu ? (bn == 192 ? 4.3f : 5.5f) : (bn == 192 ? 2.6f : 4.2f);
+    return {bn, (N + bn - 1) / bn, nk * (bn == 192 ? step_192 : 1.42f) + epilogue,
+            nk * (bn == 192 ? 0.68f : 0.8f) + epilogue + 3.f, nk * 0.6f + epilogue + 3.f};      // (a piece fills its rings anew)
+}
+
+// ... and of `bands` row tiles
+constexpr float stream_cost_of_bands(const StreamCost& c, int bands)
+{
+    const int per_xcd = (bands * c.cols + 7) / 8;
+    const int rounds = per_xcd / kStreamSlots, left = per_xcd % kStreamSlots;
+    const int pieces = leftover_pieces(c.bn, left, kStreamSlots);
+    return rounds * c.whole + (left == 0 ? 0.f : pieces == 1 ? c.whole : pieces == 2 ? c.halves : c.quarters);
+}
+
+// The same where the segment sizes are not known (they live on the device): a segment ends in half a row tile on average, and the
+// cost is averaged over the row tiles around that.
 inline float stream_cost(int bn, int N, int K, bool gelu, int rows, int n_seg)
 {
-    const float step[5] = {0.f, bn == 192 ? 1.06f : 1.42f, bn == 192 ? 0.68f : 0.8f, 0.f, 0.6f};      // by pieces
-    const float epilogue = gelu ? (bn == 192 ? 4.3f : 5.5f) : (bn == 192 ? 2.6f : 4.2f);
-    const int nk = K / 64, cols = (N + bn - 1) / bn;
+    const StreamCost c = stream_cost_of(bn, N, K, gelu);
     float sum = 0.f;
     for (int d = -2; d <= 2; ++d) {
-        int bands = (rows + 255) / 256 + n_seg / 2 + d;
-        bands = bands < 1 ? 1 : bands;
-        const int per_xcd = (bands * cols + 7) / 8;
-        const int rounds = per_xcd / kStreamSlots, left = per_xcd % kStreamSlots;
-        const int pieces = leftover_pieces(bn, left, kStreamSlots);
-        sum += rounds * (nk * step[1] + epilogue);
-        if (left > 0) sum += nk * step[pieces] + epilogue + (pieces > 1 ? 3.f : 0.f);      // (a piece fills its rings anew)
+        const int bands = (rows + 255) / 256 + n_seg / 2 + d;
+        sum += stream_cost_of_bands(c, bands < 1 ? 1 : bands);
     }
     return sum * 0.2f;
+}
+
+// at most 1/8 of the columns computed in vain by tiles of 192
+constexpr bool stream_fits_192(int N) { return (N + 191) / 192 * 192 * 8 <= N * 9; }
+
+// Columns of the persistent kernel's tiles once the segment table is known: those that the host planned on its estimate of the row tiles,
+// unless the other width is expected to be faster by more than the model is off (8 us) on the real ones.  Weights from memory make a step of
+// 192 columns 1.11 us where the host's 1.06 were measured warm.  Whole layer, us, with the planned width / with this rule: second GEMM of
+// DiT-MoE-G, 4096 tokens, 504 / 483 (192 -> 256); first of DiT-MoE-XL, 3000 tokens, 174 / 167 (192 -> 256); expert-parallel widths, 4000 tokens,
+// 592 / 568 (192 -> 256); DiT-MoE-XL with two shared experts, 4096 tokens, 295 / 287.
+constexpr int stream_columns(int planned, const StreamCost& c192, const StreamCost& c256, int bands)
+{
+    const float t192 = stream_cost_of_bands(c192, bands), t256 = stream_cost_of_bands(c256, bands);
+    if (planned == 192) return t192 - t256 > 8.f ? 256 : 192;
+    return t256 - t192 > 8.f ? 192 : 256;
+}
+constexpr StreamCost stream_cost_192(int N, int K, bool gelu) { return stream_cost_of(192, N, K, gelu, 1.11f); }
+constexpr StreamCost stream_cost_256(int N, int K, bool gelu) { return stream_cost_of(256, N, K, gelu); }
+
+// Can the table say so?  A kernel that holds both widths costs 0.5 - 1 us (DiT-MoE-S, 2048 tokens x 12 layers 584 / 587 us, DiT-MoE-XL, 4096 tokens
+// 198.2 / 199.0): it runs only where the row tiles that these rows can come to, all in one segment or an empty tile in each, allow
+// either answer and the estimate is not far from where it changes.
+inline bool stream_looks(int planned, int N, int K, bool gelu, int rows, int n_seg)
+{
+    if (!stream_fits_192(N)) return false;
+    const StreamCost c192 = stream_cost_192(N, K, gelu), c256 = stream_cost_256(N, K, gelu);
+    const int least = (rows + 255) / 256, expected = least + n_seg / 2;
+    for (int bands = expected - 3; bands <= expected + 3; ++bands)
+        if (bands >= least && bands <= least + n_seg && stream_columns(planned, c192, c256, bands) != planned) return true;
+    return false;
 }
 
 // Tile shape for one bf16 grouped GEMM.  With at most 64 segments and enough tiles the persistent kernel of
@@ -96,7 +139,7 @@ inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, i
     auto tiles = [&](int bm, int bn) { return row_tiles(bm) * ((N + bn - 1) / bn); };
     // ... and, however few its rows, has one
     auto all_tiles = [&](int bm, int bn) { return (row_tiles(bm) > segs ? row_tiles(bm) : segs) * ((N + bn - 1) / bn); };
-    const bool fits_192 = (N + 191) / 192 * 192 * 8 <= N * 9;          // at most 1/8 of the columns computed in vain
+    const bool fits_192 = stream_fits_192(N);
     const bool fits_128 = (N + 127) / 128 * 128 * 8 <= N * 9;
     const bool full_rows = rows >= 128 * segs;                         // (row tiles half full on average)
     if (by_expert && K >= 384 && (fits_192 || N % 256 == 0) && full_rows && tiles(256, 192) >= (gelu ? 96 : kComputeUnits + 1)) {

@@ -22,7 +22,7 @@
 // Tile shapes (rows x columns, stages of activations + stages of weights in 160 KB of LDS): whole 256 x 192 (2 + 4) and
 // 256 x 256 (2 + 3), halves 128 x 192 (4 + 4) and 128 x 256 (3 + 3), quarters 128 x 128 (5 + 5).  The wide one moves 15 %
 // fewer bytes per flop and has fewer epilogues; which one wins is mostly a matter of how the tile count meets 32
-// compute units per XCD, see stream_cost.
+// compute units per XCD: stream_cost on the host's estimate of it, stream_columns on the real count.
 #pragma once
 #include <type_traits>
 #include "ffn_mfma.hpp"
@@ -48,8 +48,15 @@ struct XcdTiles {
     __device__ __forceinline__ void deal(const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert,
                                          int n_seg_, int bm_, int bn_, int n_tiles_n_, int xcd_, int max_rows)
     {
+        load(seg_offsets, seg_expert, n_seg_, bm_, max_rows);
+        deal_columns(bn_, n_tiles_n_, xcd_);
+    }
+
+    __device__ __forceinline__ void load(const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert,
+                                         int n_seg_, int bm_, int max_rows)
+    {
         const int lane = threadIdx.x & 63;
-        n_seg = n_seg_; bm = bm_; bn = bn_; n_tiles_n = n_tiles_n_; xcd = xcd_;
+        n_seg = n_seg_; bm = bm_;
         begin = end = 0;
         expert = 8;                             // (a home that is nobody's)
         if (lane < n_seg) {
@@ -60,6 +67,19 @@ struct XcdTiles {
             begin = begin < end ? begin : end;
         }
         row_tiles = (end - begin + bm - 1) / bm;
+    }
+
+    __device__ __forceinline__ int all_row_tiles() const
+    {
+        int sum = 0;
+        for (int g = 0; g < n_seg; ++g) sum += __builtin_amdgcn_readlane(row_tiles, g);
+        return sum;
+    }
+
+    __device__ __forceinline__ void deal_columns(int bn_, int n_tiles_n_, int xcd_)
+    {
+        const int lane = threadIdx.x & 63;
+        bn = bn_; n_tiles_n = n_tiles_n_; xcd = xcd_;
         const int home = lane < n_seg ? expert & 7 : 8;
         first = 0;
         int own = 0;
@@ -504,26 +524,19 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
     block_barrier();
 }
 
+// All items of a workgroup on tiles of 256 x 64 TN
 template <int TN, bool GELU, bool GATHER>
-__global__ __launch_bounds__(512, 1) void ffn_gemm_bf16_stream_kernel(
-    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const float* __restrict__ bias,
-    bf16_t* __restrict__ C, int N, int K, const int32_t* __restrict__ seg_offsets,
-    const int32_t* __restrict__ seg_expert, int n_seg, int n_tiles_n,
-    const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index,
-    int max_rows, int32_t* __restrict__ status)
+__device__ __forceinline__ void stream_items(const StreamArgs& g, char* smem, XcdTiles& tiles)
 {
     constexpr int BM = 256, BN = 64 * TN;
-    extern __shared__ __attribute__((aligned(1024))) char smem[];
-    report_row_overflow(status, seg_offsets, n_seg, max_rows);
+    const int N = g.N;
     const int lane = threadIdx.x & 63;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, n_slots = gridDim.x >> 3;
-    XcdTiles tiles;
-    tiles.deal(seg_offsets, seg_expert, n_seg, BM, BN, n_tiles_n, xcd, max_rows);
+    tiles.deal_columns(BN, (N + BN - 1) / BN, xcd);
     const int rounds = tiles.count / n_slots;
     const int left = tiles.count - rounds * n_slots;
     const int pieces = leftover_pieces(BN, left, n_slots);
     const int n_whole = rounds + (pieces == 1 && slot < left ? 1 : 0);
-    const StreamArgs g = {A, W, bias, C, N, K, row_index, row_div, out_index};
     auto columns = [&](Place& p, int width) { p.col_end = p.col0 + width < N ? p.col0 + width : N; };
     if (n_whole > 0) {
         Place first;
@@ -567,31 +580,77 @@ __global__ __launch_bounds__(512, 1) void ffn_gemm_bf16_stream_kernel(
     }
 }
 
-template <int TN, bool GELU>
+// Both widths: `planned` unless the table says the other one
+struct StreamWidths { int planned; StreamCost c192, c256; };
+
+// TN: 3 or 4, 192 or 256 columns, or 0: as StreamWidths says
+template <int TN, bool GELU, bool GATHER>
+__global__ __launch_bounds__(512, 1) void ffn_gemm_bf16_stream_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const float* __restrict__ bias,
+    bf16_t* __restrict__ C, int N, int K, const int32_t* __restrict__ seg_offsets,
+    const int32_t* __restrict__ seg_expert, int n_seg,
+    const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index,
+    int max_rows, int32_t* __restrict__ status, std::conditional_t<TN == 0, StreamWidths, NoMore> widths)
+{
+    extern __shared__ __attribute__((aligned(1024))) char smem[];
+    report_row_overflow(status, seg_offsets, n_seg, max_rows);
+    XcdTiles tiles;
+    tiles.load(seg_offsets, seg_expert, n_seg, 256, max_rows);
+    const StreamArgs g = {A, W, bias, C, N, K, row_index, row_div, out_index};
+    if constexpr (TN == 0) {
+        if (stream_columns(widths.planned, widths.c192, widths.c256, tiles.all_row_tiles()) == 192) stream_items<3, GELU, GATHER>(g, smem, tiles);
+        else stream_items<4, GELU, GATHER>(g, smem, tiles);
+    } else {
+        stream_items<TN, GELU, GATHER>(g, smem, tiles);
+    }
+}
+
+template <bool GELU>
 static hipError_t configure_gemm_bf16_stream()
 {
-    hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm_bf16_stream_kernel<TN, GELU, false>),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
-    if (err == hipSuccess && GELU)
-        err = hipFuncSetAttribute(reinterpret_cast<const void*>(ffn_gemm_bf16_stream_kernel<TN, GELU, GELU>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+    auto raise = [](auto kern) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds); };
+    hipError_t err = raise(&ffn_gemm_bf16_stream_kernel<0, GELU, false>);
+    if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<3, GELU, false>);
+    if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<4, GELU, false>);
+    if constexpr (GELU) {
+        if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<0, GELU, true>);
+        if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<3, GELU, true>);
+        if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<4, GELU, true>);
+    }
     return err;
 }
 
-template <int TN, bool GELU>
-static hipError_t launch_gemm_bf16_stream(const void* A, const void* W, const float* bias, void* C, int N, int K,
+template <int TN, bool GELU, typename Widths>
+static hipError_t launch_gemm_bf16_stream_kernel(const void* A, const void* W, const float* bias, void* C, int N, int K,
+                                                 const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
+                                                 hipStream_t stream, const int32_t* row_index, int row_div,
+                                                 const int32_t* out_index, int32_t* status, Widths widths)
+{
+    const auto kern = GELU && row_index ? &ffn_gemm_bf16_stream_kernel<TN, GELU, GELU> : &ffn_gemm_bf16_stream_kernel<TN, GELU, false>;
+    hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(kStreamThreads), kStreamLds, stream, static_cast<const bf16_t*>(A),
+                       static_cast<const bf16_t*>(W), bias, static_cast<bf16_t*>(C), N, K, seg_offsets, seg_expert, n_seg,
+                       row_index, row_div, out_index, max_rows, status, widths);
+    return hipGetLastError();
+}
+
+// columns: 192 or 256, as planned on the host's estimate
+template <bool GELU>
+static hipError_t launch_gemm_bf16_stream(int columns, const void* A, const void* W, const float* bias, void* C, int N, int K,
                                           const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
                                           hipStream_t stream, const int32_t* row_index, int row_div,
                                           const int32_t* out_index, int32_t* status)
 {
-    constexpr int BN = 64 * TN;
     // every ring needs one step more than it is deep; only the first GEMM gathers its rows
     if (n_seg > 64 || K / 64 < 6 || (!GELU && row_index)) return hipErrorInvalidValue;
-    const auto kern = GELU && row_index ? &ffn_gemm_bf16_stream_kernel<TN, GELU, GELU> : &ffn_gemm_bf16_stream_kernel<TN, GELU, false>;
-    hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(kStreamThreads), kStreamLds, stream, static_cast<const bf16_t*>(A),
-                       static_cast<const bf16_t*>(W), bias, static_cast<bf16_t*>(C), N, K, seg_offsets, seg_expert, n_seg,
-                       (N + BN - 1) / BN, row_index, row_div, out_index, max_rows, status);
-    return hipGetLastError();
+#define DICEMOE_STREAM(TN, widths) \
+    return launch_gemm_bf16_stream_kernel<TN, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status, widths)
+    if (stream_looks(columns, N, K, GELU, max_rows, n_seg)) {
+        const StreamWidths widths = {columns, stream_cost_192(N, K, GELU), stream_cost_256(N, K, GELU)};
+        DICEMOE_STREAM(0, widths);
+    }
+    if (columns == 192) DICEMOE_STREAM(3, NoMore{});
+    DICEMOE_STREAM(4, NoMore{});
+#undef DICEMOE_STREAM
 }
 
 }  // namespace dicemoe

@@ -31,8 +31,8 @@ constexpr int wide_occupancy(int tm, int tn, int ast, int wst, int wgm, int wgn)
 }
 
 // Kernels that sort the pairs themselves (SELF) have one argument more
-struct NoSort {};
-template <bool SELF> using OwnSort = std::conditional_t<SELF, PairSort, NoSort>;
+struct NoMore {};
+template <bool SELF> using OwnSort = std::conditional_t<SELF, PairSort, NoMore>;
 
 template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, int WGM, int WGN, bool SELF = false>
 __global__ __launch_bounds__(64 * WGM * WGN, wide_occupancy(TM, TN, AST, WST, WGM, WGN)) void ffn_gemm_bf16_wide_kernel(

@@ -16,6 +16,9 @@ extern "C" void plan(int gelu, int N, int K, int rows, int n_seg, int n_experts,
     out[0] = static_cast<int>(p.tile);
     out[1] = p.shares;
 }
+extern "C" int columns(int planned, int N, int K, int gelu, int rows, int n_seg, int bands) {
+    return dicemoe::stream_looks(planned, N, K, gelu != 0, rows, n_seg) ? dicemoe::stream_columns(planned, dicemoe::stream_cost_192(N, K, gelu != 0), dicemoe::stream_cost_256(N, K, gelu != 0), bands) : planned;
+}
 extern "C" int pieces(int bn, int left, int slots) { return dicemoe::leftover_pieces(bn, left, slots); }
 """
 
@@ -90,7 +93,10 @@ def stream_items(seg_rows, seg_expert, N, bn):
 def describe(seg_rows, seg_expert, d, F):
     """Tile of either GEMM, and for the persistent kernel what it runs, as one line each."""
     lines = []
-    for tile, N in zip(ffn_plans(sum(seg_rows), len(seg_rows), d, F), (F, d)):
+    bands = sum(-(-n // 256) for n in seg_rows)
+    for tile, N, K, gelu in zip(ffn_plans(sum(seg_rows), len(seg_rows), d, F), (F, d), (d, F), (1, 0)):
+        if tile.startswith("stream"):                    # the kernel takes the other width if the table says so
+            tile = f"stream{_lib().columns(int(tile[6:]), N, K, gelu, sum(seg_rows), len(seg_rows), bands)}"
         items = stream_items(seg_rows, seg_expert, N, int(tile[6:])) if tile.startswith("stream") else ()
         lines.append(" ".join([tile] + sorted(items)))
     return tuple(lines)
