@@ -33,6 +33,9 @@ namespace dicemoe {
 
 constexpr int kStreamThreads = 512;
 constexpr int kStreamLds = 160 * 1024;
+using StreamPairs = CountedPairs<kStreamThreads / kWave>;
+constexpr int kStreamOwnRows = 2 * 256;                    // the rows of a workgroup's first two tiles
+constexpr int kStreamSortBytes = kStreamOwnRows * 2 + StreamPairs::kBytes;
 
 // The tiles of one grouped GEMM dealt to the eight XCDs by expert, as find_tile_by_expert does for a workgroup per tile
 // (home XCD = expert mod 8, an XCD keeps at most cap = ceil(total / 8) tiles of its own list and takes overflow of
@@ -48,24 +51,30 @@ struct XcdTiles {
     __device__ __forceinline__ void deal(const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert,
                                          int n_seg_, int bm_, int bn_, int n_tiles_n_, int xcd_, int max_rows)
     {
-        load(seg_offsets, seg_expert, n_seg_, bm_, max_rows);
+        load(seg_offsets, expert_of(seg_expert, n_seg_), n_seg_, bm_, max_rows);
         deal_columns(bn_, n_tiles_n_, xcd_);
     }
 
-    __device__ __forceinline__ void load(const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert,
-                                         int n_seg_, int bm_, int max_rows)
+    // each lane's entry of seg_expert
+    static __device__ __forceinline__ int expert_of(const int32_t* __restrict__ seg_expert, int n_seg)
     {
         const int lane = threadIdx.x & 63;
+        return lane < n_seg ? seg_expert[lane] : 8;          // (a home that is nobody's)
+    }
+
+    __device__ __forceinline__ void load(const int32_t* seg_offsets, int expert_, int n_seg_, int bm_, int max_rows)
+    {
+        const int lane = threadIdx.x & 63;
+        set(lane < n_seg_ ? seg_offsets[lane] : 0, lane < n_seg_ ? seg_offsets[lane + 1] : 0, expert_, n_seg_, bm_, max_rows);
+    }
+
+    // each lane's segment
+    __device__ __forceinline__ void set(int begin_, int end_, int expert_, int n_seg_, int bm_, int max_rows)
+    {
         n_seg = n_seg_; bm = bm_;
-        begin = end = 0;
-        expert = 8;                             // (a home that is nobody's)
-        if (lane < n_seg) {
-            begin = seg_offsets[lane];
-            end = seg_offsets[lane + 1];
-            expert = seg_expert[lane];
-            end = end < max_rows ? end : max_rows;          // (a table that holds more rows than the caller said)
-            begin = begin < end ? begin : end;
-        }
+        end = end_ < max_rows ? end_ : max_rows;            // (a table that holds more rows than the caller said)
+        begin = begin_ < end ? begin_ : end;
+        expert = expert_;
         row_tiles = (end - begin + bm - 1) / bm;
     }
 
@@ -254,8 +263,9 @@ struct StreamArgs {
 };
 
 // The items first, place(1) .. place(n_items - 1) of this workgroup, each a (32 TM WGM) x (32 TN WGN) tile or part of one.
-template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, bool GATHER, int WGM, int WGN, typename PlaceFn>
-__device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, int n_items, Place first, PlaceFn place)
+// OWN: own_rows is the row index of the first two items, 256 each, in the LDS of the activations' ring.
+template <int TM, int TN, int SPREAD, int AST, int WST, bool GELU, bool GATHER, bool OWN, int WGM, int WGN, typename PlaceFn>
+__device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, int n_items, Place first, PlaceFn place, const uint16_t* own_rows = nullptr)
 {
     constexpr int NW = WGM * WGN;
     constexpr int BM = 32 * TM * WGM, BN = 32 * TN * WGN;
@@ -272,6 +282,7 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
     constexpr int NB = (WN + 63) / 64;
     constexpr int NSTORE = TM * TN * 2;                  // store instructions of a wavefront's epilogue
     static_assert(SPREAD >= 1 && SPREAD <= 4, "a refill is issued within the four slices before it is needed");
+    static_assert(!OWN || kStreamSortBytes <= AST * ABYTES, "the sorted rows fit the activations' ring");
     char* const a_lds = smem;
     char* const w_lds = smem + AST * ABYTES;
     const bf16_t* const A = g.A;
@@ -305,6 +316,15 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
         w_off[i] = static_cast<uint32_t>(row) * static_cast<uint32_t>(K) * 2u + ((lane & 7) ^ chunk_swizzle<CH>(row)) * 16;
     }
     // Rows beyond the item's get an offset beyond the buffer: they read as zero and cost no memory access.
+    auto fetch_own_rows = [&](const Place& pl, int (&rows)[QA], const uint16_t* list) {
+#pragma unroll
+        for (int i = 0; i < QA; ++i) {
+            int r = (wave * QA + i) * 8 + (lane >> 3);
+            const int here = pl.row_end - pl.row0;
+            r = r < here ? r : here - 1;
+            rows[i] = list[r > 0 ? r : 0];
+        }
+    };
     auto fetch_rows = [&](const Place& pl, int (&rows)[QA]) {
 #pragma unroll
         for (int i = 0; i < QA; ++i) {
@@ -444,23 +464,34 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
         const int c = pl.col0 + wn * WN;
         load_bias_columns<WN>(bias ? bias + static_cast<size_t>(pl.e) * N + c : nullptr, N - c, lane, bias_reg);
     };
-    fetch_rows(p, rows);
+    Place q;
+    if constexpr (OWN) fetch_own_rows(p, rows, own_rows);
+    else fetch_rows(p, rows);
     DICEMOE_SCHED_FENCE();
 #pragma unroll
     for (int s = 0; s < WST; ++s)
 #pragma unroll
         for (int i = 0; i < QB; ++i) if (s < WST - 1 || QA + i < PART) dma_w(i, w_cur, s, s);
     row_offsets(p, rows, a_cur);
+    if constexpr (OWN) {                             // (the second item's too, then stages can take their place)
+        q = n_items > 1 ? place(1) : nowhere(p);
+        fetch_own_rows(q, rows, own_rows + 256);
+        asm volatile("" ::: "memory");
+        wait_lgkmcnt<0>();
+        block_barrier();
+    }
 #pragma unroll
     for (int s = 0; s < AST; ++s)
 #pragma unroll
         for (int i = 0; i < QA; ++i) if (s < AST - 1 || i < PART) dma_a(i, a_cur[i], s, s);
     fetch_bias(p);
     DICEMOE_SCHED_FENCE();
-    Place q = n_items > 1 ? place(1) : nowhere(p);
-    fetch_rows(q, rows);
+    if constexpr (!OWN) {
+        q = n_items > 1 ? place(1) : nowhere(p);
+        fetch_rows(q, rows);
+    }
     DICEMOE_SCHED_FENCE();
-    wait_vmcnt<GATHER ? QA : 0>();                   // (the row indices of the second item may be on their way)
+    wait_vmcnt<GATHER && !OWN ? QA : 0>();           // (the row indices of the second item may be on their way)
     block_barrier();
 #pragma unroll
     for (int f = 0; f < NFRAG; ++f) read_frag(0, f, a_lds, w_lds, 0);
@@ -525,8 +556,11 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
 }
 
 // All items of a workgroup on tiles of 256 x 64 TN
-template <int TN, bool GELU, bool GATHER>
-__device__ __forceinline__ void stream_items(const StreamArgs& g, char* smem, XcdTiles& tiles)
+// OWN: the row index comes from `pairs`, before anything is loaded: into LDS for the first two items, and for those that a workgroup comes to
+// after its LDS has been taken by stages, where the kernels behind read it.  Workgroups with an item's first columns leave it there in any
+// case (who writes the same place writes the same).
+template <int TN, bool GELU, bool GATHER, bool OWN>
+__device__ __forceinline__ void stream_items(const StreamArgs& g, char* smem, XcdTiles& tiles, const StreamPairs* pairs = nullptr, const PairSort* sort = nullptr)
 {
     constexpr int BM = 256, BN = 64 * TN;
     const int N = g.N;
@@ -537,7 +571,41 @@ __device__ __forceinline__ void stream_items(const StreamArgs& g, char* smem, Xc
     const int left = tiles.count - rounds * n_slots;
     const int pieces = leftover_pieces(BN, left, n_slots);
     const int n_whole = rounds + (pieces == 1 && slot < left ? 1 : 0);
+    uint16_t* const own_rows = reinterpret_cast<uint16_t*>(smem);
     auto columns = [&](Place& p, int width) { p.col_end = p.col0 + width < N ? p.col0 + width : N; };
+    auto locate_piece = [&](Place& p) {
+        if (pieces == 1 || slot >= left * pieces) return false;
+        const int tile = slot / pieces, piece = slot - tile * pieces;
+        tiles.locate(rounds * n_slots + tile, p.row0, p.row_end, p.col0, p.e);
+        p.row0 += (piece & 1) * (BM / 2);
+        if (p.row_end > p.row0 + BM / 2) p.row_end = p.row0 + BM / 2;
+        p.col0 += (piece >> 1) * (BN / 2);
+        columns(p, pieces == 4 ? BN / 2 : BN);
+        return p.row0 < p.row_end && p.col0 < p.col_end;       // else a piece without rows or columns
+    };
+    if constexpr (OWN) {
+        Place p;
+        const int n_items = n_whole + (locate_piece(p) ? 1 : 0);
+        if (n_items == 0) return;
+#pragma unroll 1
+        for (int i = 0; i < n_items; ++i) {
+            Place at = p;
+            if (i < n_whole) {
+                tiles.locate(slot + i * n_slots, at.row0, at.row_end, at.col0, at.e);
+                if (at.row_end > at.row0 + BM) at.row_end = at.row0 + BM;
+            }
+            const int keep = i == n_whole && i > 0 ? 2 : i;        // (a piece behind whole tiles finds its rows in memory)
+            const int seg = __builtin_ctzll(__ballot(at.row0 >= pairs->begin && at.row0 < pairs->end));
+            pairs->each(seg, at.row0, at.row_end, [&](int r, int pair) {
+                if (keep < 2) own_rows[keep * 256 + r - at.row0] = static_cast<uint16_t>(pair);
+                if (keep >= 2 || at.col0 == 0) sort->perm[r] = pair;
+                if (at.col0 == 0) sort->inv[pair] = r;
+            });
+        }
+        asm volatile("" ::: "memory");                   // the rows are in LDS (stores to memory may be on their way)
+        wait_lgkmcnt<0>();
+        block_barrier();
+    }
     if (n_whole > 0) {
         Place first;
         tiles.locate(slot, first.row0, first.row_end, first.col0, first.e);
@@ -561,61 +629,88 @@ __device__ __forceinline__ void stream_items(const StreamArgs& g, char* smem, Xc
         };
         // 256 columns without GELU: wavefronts of 128 x 64 (2048 x 8192, 4 x 2048 rows, second GEMM: 1.42 - 1.55 us a step against 1.51 - 1.57
         // of 64 x 128, epilogue 2.7 - 2.9 against 3.1; with GELU, whose stores are the more, 1.69 against 1.59 at DiT-MoE-XL widths)
-        if constexpr (TN == 4 && !GELU) stream_tiles<4, 2, 2, 2, 3, GELU, GATHER, 2, 4>(g, smem, n_whole, first, place);
-        else stream_tiles<2, TN, 2, 2, TN == 3 ? 4 : 3, GELU, GATHER, 4, 2>(g, smem, n_whole, first, place);
+        if constexpr (TN == 4 && !GELU) stream_tiles<4, 2, 2, 2, 3, GELU, GATHER, OWN, 2, 4>(g, smem, n_whole, first, place, own_rows);
+        else stream_tiles<2, TN, 2, 2, TN == 3 ? 4 : 3, GELU, GATHER, OWN, 4, 2>(g, smem, n_whole, first, place, own_rows);
     }
-    if (pieces > 1 && slot < left * pieces) {
-        const int tile = slot / pieces, piece = slot - tile * pieces;
-        Place p;
-        tiles.locate(rounds * n_slots + tile, p.row0, p.row_end, p.col0, p.e);
-        p.row0 += (piece & 1) * (BM / 2);
-        if (p.row_end > p.row0 + BM / 2) p.row_end = p.row0 + BM / 2;
-        p.col0 += (piece >> 1) * (BN / 2);
-        columns(p, pieces == 4 ? BN / 2 : BN);
-        if (p.row0 >= p.row_end || p.col0 >= p.col_end) return;       // a piece without rows or columns
+    Place p;
+    if (locate_piece(p)) {
         auto same = [&](int) { return p; };
-        if (TN == 3) stream_tiles<1, 3, 2, 4, 4, GELU, GATHER, 4, 2>(g, smem, 1, p, same);
-        else if (pieces == 4) stream_tiles<1, 2, 2, 5, 5, GELU, GATHER, 4, 2>(g, smem, 1, p, same);
-        else stream_tiles<1, 4, 2, 3, 3, GELU, GATHER, 4, 2>(g, smem, 1, p, same);
+        auto run = [&](auto own) {
+            constexpr bool O = decltype(own)::value;
+            if constexpr (TN == 3) stream_tiles<1, 3, 2, 4, 4, GELU, GATHER, O, 4, 2>(g, smem, 1, p, same, own_rows);
+            else if (pieces == 4) stream_tiles<1, 2, 2, 5, 5, GELU, GATHER, O, 4, 2>(g, smem, 1, p, same, own_rows);
+            else stream_tiles<1, 4, 2, 3, 3, GELU, GATHER, O, 4, 2>(g, smem, 1, p, same, own_rows);
+        };
+        if constexpr (OWN) {
+            if (n_whole == 0) {
+                run(std::true_type{});
+                return;
+            }
+        }
+        run(std::false_type{});
     }
 }
 
 // Both widths: `planned` unless the table says the other one
 struct StreamWidths { int planned; StreamCost c192, c256; };
 
-// TN: 3 or 4, 192 or 256 columns, or 0: as StreamWidths says
-template <int TN, bool GELU, bool GATHER>
+// TN: 3 or 4, 192 or 256 columns, or 0: as StreamWidths says.  OWN: the workgroup sorts the pairs itself (ffn_sorts_pairs).
+template <int TN, bool GELU, bool GATHER, bool OWN>
 __global__ __launch_bounds__(512, 1) void ffn_gemm_bf16_stream_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, const float* __restrict__ bias,
     bf16_t* __restrict__ C, int N, int K, const int32_t* __restrict__ seg_offsets,
     const int32_t* __restrict__ seg_expert, int n_seg,
     const int32_t* __restrict__ row_index, int row_div, const int32_t* __restrict__ out_index,
-    int max_rows, int32_t* __restrict__ status, std::conditional_t<TN == 0, StreamWidths, NoMore> widths)
+    int max_rows, int32_t* __restrict__ status, std::conditional_t<TN == 0, StreamWidths, NoMore> widths, OwnSort<OWN> sort)
 {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
-    report_row_overflow(status, seg_offsets, n_seg, max_rows);
     XcdTiles tiles;
-    tiles.load(seg_offsets, seg_expert, n_seg, 256, max_rows);
-    const StreamArgs g = {A, W, bias, C, N, K, row_index, row_div, out_index};
-    if constexpr (TN == 0) {
-        if (stream_columns(widths.planned, widths.c192, widths.c256, tiles.all_row_tiles()) == 192) stream_items<3, GELU, GATHER>(g, smem, tiles);
-        else stream_items<4, GELU, GATHER>(g, smem, tiles);
+    StreamArgs g = {A, W, bias, C, N, K, row_index, row_div, out_index};
+    const int expert = XcdTiles::expert_of(seg_expert, n_seg);
+    StreamPairs pairs;
+    const PairSort* own = nullptr;
+    if constexpr (OWN) {
+        static_assert((kStreamOwnRows & 255) == 0 && kStreamGrid * kWave >= kStreamSortPairs, "every 64 pairs have a workgroup");
+        pairs.form(sort, smem + kStreamOwnRows * 2);
+        own = &sort;
+        g.row_index = sort.perm;                            // (written here: not through the argument that nobody writes)
+        report_rows(status, pairs.rows, max_rows);
+        tiles.set(pairs.begin, pairs.end, expert, n_seg, 256, max_rows);
+        if (pairs.rows > max_rows)                          // rows that no tile has
+            for (int e = blockIdx.x; e < n_seg; e += gridDim.x) {
+                const int lo = __builtin_amdgcn_readlane(pairs.begin, e), hi = __builtin_amdgcn_readlane(pairs.end, e);
+                pairs.each(e, lo > max_rows ? lo : max_rows, hi, [&](int r, int p) { sort.perm[r] = p; sort.inv[p] = r; });
+            }
     } else {
-        stream_items<TN, GELU, GATHER>(g, smem, tiles);
+        report_row_overflow(status, seg_offsets, n_seg, max_rows);
+        tiles.load(seg_offsets, expert, n_seg, 256, max_rows);
+    }
+    auto items = [&](auto tn) { stream_items<decltype(tn)::value, GELU, GATHER, OWN>(g, smem, tiles, &pairs, own); };
+    if constexpr (TN == 0) {
+        if (stream_columns(widths.planned, widths.c192, widths.c256, tiles.all_row_tiles()) == 192) items(std::integral_constant<int, 3>{});
+        else items(std::integral_constant<int, 4>{});
+    } else {
+        items(std::integral_constant<int, TN>{});
     }
 }
 
 template <bool GELU>
 static hipError_t configure_gemm_bf16_stream()
 {
-    auto raise = [](auto kern) { return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds); };
-    hipError_t err = raise(&ffn_gemm_bf16_stream_kernel<0, GELU, false>);
-    if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<3, GELU, false>);
-    if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<4, GELU, false>);
+    hipError_t err = hipSuccess;
+    auto raise = [&](auto kern) {
+        if (err == hipSuccess) err = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kStreamLds);
+    };
+    raise(&ffn_gemm_bf16_stream_kernel<0, GELU, false, false>);
+    raise(&ffn_gemm_bf16_stream_kernel<3, GELU, false, false>);
+    raise(&ffn_gemm_bf16_stream_kernel<4, GELU, false, false>);
     if constexpr (GELU) {
-        if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<0, GELU, true>);
-        if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<3, GELU, true>);
-        if (err == hipSuccess) err = raise(&ffn_gemm_bf16_stream_kernel<4, GELU, true>);
+        raise(&ffn_gemm_bf16_stream_kernel<0, GELU, true, false>);
+        raise(&ffn_gemm_bf16_stream_kernel<3, GELU, true, false>);
+        raise(&ffn_gemm_bf16_stream_kernel<4, GELU, true, false>);
+        raise(&ffn_gemm_bf16_stream_kernel<0, GELU, true, true>);
+        raise(&ffn_gemm_bf16_stream_kernel<3, GELU, true, true>);
+        raise(&ffn_gemm_bf16_stream_kernel<4, GELU, true, true>);
     }
     return err;
 }
@@ -624,13 +719,19 @@ template <int TN, bool GELU, typename Widths>
 static hipError_t launch_gemm_bf16_stream_kernel(const void* A, const void* W, const float* bias, void* C, int N, int K,
                                                  const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
                                                  hipStream_t stream, const int32_t* row_index, int row_div,
-                                                 const int32_t* out_index, int32_t* status, Widths widths)
+                                                 const int32_t* out_index, int32_t* status, const PairSort* sort, Widths widths)
 {
-    const auto kern = GELU && row_index ? &ffn_gemm_bf16_stream_kernel<TN, GELU, GELU> : &ffn_gemm_bf16_stream_kernel<TN, GELU, false>;
-    hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(kStreamThreads), kStreamLds, stream, static_cast<const bf16_t*>(A),
-                       static_cast<const bf16_t*>(W), bias, static_cast<bf16_t*>(C), N, K, seg_offsets, seg_expert, n_seg,
-                       row_index, row_div, out_index, max_rows, status, widths);
-    return hipGetLastError();
+    auto launch = [&](auto kern, auto own) {
+        hipLaunchKernelGGL(kern, dim3(kStreamGrid), dim3(kStreamThreads), kStreamLds, stream, static_cast<const bf16_t*>(A),
+                           static_cast<const bf16_t*>(W), bias, static_cast<bf16_t*>(C), N, K, seg_offsets, seg_expert, n_seg,
+                           row_index, row_div, out_index, max_rows, status, widths, own);
+        return hipGetLastError();
+    };
+    if constexpr (GELU) {
+        if (sort) return launch(&ffn_gemm_bf16_stream_kernel<TN, true, true, true>, *sort);
+        if (row_index) return launch(&ffn_gemm_bf16_stream_kernel<TN, true, true, false>, NoMore{});
+    }
+    return launch(&ffn_gemm_bf16_stream_kernel<TN, GELU, false, false>, NoMore{});
 }
 
 // columns: 192 or 256, as planned on the host's estimate
@@ -638,12 +739,12 @@ template <bool GELU>
 static hipError_t launch_gemm_bf16_stream(int columns, const void* A, const void* W, const float* bias, void* C, int N, int K,
                                           const int32_t* seg_offsets, const int32_t* seg_expert, int n_seg, int max_rows,
                                           hipStream_t stream, const int32_t* row_index, int row_div,
-                                          const int32_t* out_index, int32_t* status)
+                                          const int32_t* out_index, int32_t* status, const PairSort* sort = nullptr)
 {
     // every ring needs one step more than it is deep; only the first GEMM gathers its rows
-    if (n_seg > 64 || K / 64 < 6 || (!GELU && row_index)) return hipErrorInvalidValue;
+    if (n_seg > 64 || K / 64 < 6 || (!GELU && row_index) || (sort && (!row_index || sort->n_pairs > kStreamSortPairs))) return hipErrorInvalidValue;
 #define DICEMOE_STREAM(TN, widths) \
-    return launch_gemm_bf16_stream_kernel<TN, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status, widths)
+    return launch_gemm_bf16_stream_kernel<TN, GELU>(A, W, bias, C, N, K, seg_offsets, seg_expert, n_seg, max_rows, stream, row_index, row_div, out_index, status, sort, widths)
     if (stream_looks(columns, N, K, GELU, max_rows, n_seg)) {
         const StreamWidths widths = {columns, stream_cost_192(N, K, GELU), stream_cost_256(N, K, GELU)};
         DICEMOE_STREAM(0, widths);

@@ -56,7 +56,7 @@ hipError_t launch_combine_sums(const SplitSums& sums, void* h_packed, const int3
                                const int32_t* seg_expert, const uint8_t* mask, int T_tok, int d, int k, int k_cached, void* H_cache, float* S_cache,
                                int use_fresh, void* y, hipStream_t stream);
 
-// The dispatch of a small layer, left to the first GEMM: pairs p of token p / slots with expert expert_idx[p], all of them (rule.mask null) or
+// The dispatch of a layer, left to the first GEMM: pairs p of token p / slots with expert expert_idx[p], all of them (rule.mask null) or
 // those that an elementwise policy refreshes.  Its index outputs and the mask are written as launch_dispatch writes them.
 struct PairSort {
     const int32_t* expert_idx;
