@@ -308,7 +308,11 @@ int moe_combine(moe_ctx* ctx, const void* h_packed, const int32_t* inv, const fl
  *                   (moe_expert_ffn_commit without scores) and the combine reads every row from there.  MOE_ERR_NULL otherwise
  *   max_rows      : bound on the refreshed pairs; with imply_rows it is not read and the bound is the count that the policy
  *                   implies (T*slots without one)
- * Without a policy mask, n_refresh, H_cache and S_cache are not used. */
+ * Without a policy mask, n_refresh, H_cache and S_cache are not used.
+ * The parts share work where they can, and every output is what the separate calls leave: the dispatch forms the mask of the policies it can;
+ * with fuse_gather, seg tables of one segment per expert and up to 4096 pairs the first GEMM may sort the pairs itself; and
+ * where the second GEMM splits its reduction, the combine adds the float shares (in one order; sizes that only this call
+ * splits round their sums in another order than moe_expert_ffn does). */
 typedef struct moe_layer_args {
     const void* x; const void* Wg; const float* bg;
     const void* W1; const float* b1; const void* W2; const float* b2;
