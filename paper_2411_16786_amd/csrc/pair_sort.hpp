@@ -121,8 +121,9 @@ __device__ __forceinline__ const int* sort_pairs(const PairSort& s, bool writer,
 }
 
 // The rows of single experts out of up to kStreamSortPairs pairs, for a workgroup that computes a few tiles of a large sort: every workgroup counts all
-// pairs, but ranks only those that it computes.  The code is kept short (rolled loops): it runs once, and a straight line of it costs more in
-// instruction fetches than in instructions (counts in registers, unrolled: 2 - 5 us more).  DiT-MoE-S, 2048 tokens x 12 layers, us: dispatched 585,
+// pairs, but ranks only those that it computes.  The loops stay rolled: counts in
+// registers and loops unrolled took 4 us a layer more (613 us below; code that runs once and is long has to be fetched first, which was not
+// measured by itself).  DiT-MoE-S, 2048 tokens x 12 layers, us: dispatched 585,
 // every workgroup ranking all pairs 572, this 561.
 template <int WAVES>
 struct CountedPairs {
