@@ -39,7 +39,7 @@ def kernel_sources_hash():
     """sha256 over the FFN kernel sources: ties a stored counter summary to the code it was taken on."""
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2411_16786_amd", "csrc")
-    for name in ("ffn.hip", "ffn_plan.hpp", "ffn_stream.hpp", "ffn_wide.hpp", "ffn_mfma.hpp", "pair_sort.hpp", "refresh_rule.hpp"):
+    for name in ("ffn.hip", "ffn_plan.hpp", "ffn_ring.hpp", "ffn_stream.hpp", "ffn_wide.hpp", "ffn_mfma.hpp", "pair_sort.hpp", "refresh_rule.hpp"):
         h.update(open(os.path.join(csrc, name), "rb").read())
     return h.hexdigest()[:16]
 

@@ -27,6 +27,7 @@
 #include <type_traits>
 #include "ffn_mfma.hpp"
 #include "ffn_plan.hpp"
+#include "ffn_ring.hpp"
 #include "ffn_wide.hpp"
 
 namespace dicemoe {
@@ -178,22 +179,6 @@ struct XcdTiles {
         e = __builtin_amdgcn_readlane(expert, g);
     }
 };
-
-// Loads of one wavefront that may still be in flight at the barrier of step kt: those issued after the last
-// load of stage kt + 1.  Issue order: prologue W0 .. W(WST-1), A0 .. A(AST-1); refill of step j (after its
-// barrier): A(j + AST), then W(j + WST); loads return in order.
-constexpr int ring_pending(int ast, int wst, int qa, int qb, int nk, int kt)
-{
-    int younger = 0;
-    auto load = [&](bool is_next, int n) { if (is_next) younger = 0; else younger += n; };
-    for (int s = 0; s < wst && s < nk; ++s) load(s == kt + 1, qb);
-    for (int s = 0; s < ast && s < nk; ++s) load(s == kt + 1, qa);
-    for (int j = 0; j < kt; ++j) {
-        if (j + ast < nk) load(j + ast == kt + 1, qa);
-        if (j + wst < nk) load(j + wst == kt + 1, qb);
-    }
-    return younger;
-}
 
 // bias of column `col` of this wavefront's columns, held by lane col % 64 of register col / 64
 template <int NB>
@@ -378,6 +363,9 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
     // loads of the stage that the first step of an item waits for have all been issued before the previous item's epilogue
     constexpr bool EARLY = (AST > 2 || QA <= PART) && (WST > 2 || QW <= PART);
     constexpr int PEND = ring_pending(AST, WST, QA, QB, 8 * DEPTH, 4 * DEPTH);
+    constexpr int FIRST = GATHER && !OWN ? ring_first_pending(QA, PART) : 0;
+    static_assert(ring_waits_hold(AST, WST, QA, QB, PART, FIRST, PEND, EARLY ? NSTORE : 0) && ring_waits_hold(AST, WST, QA, QB, PART, FIRST, PEND, 0),
+                  "every stage has landed before it is read, whether the item before left stores behind or not");
     int sa = 0, sw = 0;
     uint32_t a_cur[QA], a_nxt[QA];
     int rows[QA];
@@ -491,7 +479,7 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
         fetch_rows(q, rows);
     }
     DICEMOE_SCHED_FENCE();
-    wait_vmcnt<GATHER && !OWN ? QA : 0>();           // (the row indices of the second item may be on their way)
+    wait_vmcnt<FIRST>();                             // (the second item's row indices, where it has any, need not be here yet)
     block_barrier();
 #pragma unroll
     for (int f = 0; f < NFRAG; ++f) read_frag(0, f, a_lds, w_lds, 0);
