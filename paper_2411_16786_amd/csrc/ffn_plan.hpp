@@ -28,6 +28,21 @@ constexpr size_t kSplitKBytes = static_cast<size_t>(288) * 128 * 192 * sizeof(fl
 // shares > 1: that many workgroups per tile, each on a share of K, and a second pass that adds their float sums
 struct FfnPlan { FfnTile tile; int shares; };
 
+// One round of workgroups per XCD?  By the times below an XCD's workgroups, those that find no tile among them, go to four groups of eight
+// compute units in turn: of the `tiles` first workgroups of every `slots` that a share of the grid gives to an XCD, no group may get more
+// than eight.  (128 x 128 tiles in three shares, K = 3072, both GEMMs: 27 workgroups an XCD in three times 12 slots, nine of them in one group,
+// 49.8 us where 24 take 39.6; in three times 14 slots, eight at most, 41.4; 30 in three times 15 slots, eight at most, 40.0, in three times 16 52.6.)
+constexpr bool one_round_of_shares(int tiles, int shares, int slots)
+{
+    for (int group = 0; group < 4; ++group) {
+        int here = 0;
+        for (int s = 0; s < shares; ++s)
+            for (int i = 0; i < tiles; ++i) here += (s * slots + i) % 4 == group ? 1 : 0;
+        if (here > kStreamSlots / 4) return false;
+    }
+    return true;
+}
+
 // Pieces that each of `left` leftover tiles of an XCD is cut into by the persistent kernel.
 constexpr int leftover_pieces(int bn, int left, int slots)
 {
@@ -180,9 +195,9 @@ inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, i
     // 968 rows 57 / 53, 1219 rows 64 / 73; DiT-MoE-XL, 900 rows 29.5 / 48).
     // Where the combine adds the shares, a share more costs its part of that traffic and no launch.  Long reductions (the weights are what the
     // time goes to): 128 x 128 tiles in as many shares, of sixteen steps at least, as one round has room for, with a row tile to spare
-    // once segments are likely to need a second one: an XCD deals its eighth of the tiles to 32 compute units, and one more than these
-    // is a second round (whole layer, 128 x 192 in three shares / so: DiT-MoE-XL, 48 tokens 57.2 / 53.7 us, 138: 63.4 / 59.9; 500 tokens, in
-    // two, 85.5 / 81.9, 700 rows 77.0 / 73.8, 575 rows 75.6 / 76.2; 267 rows of nine experts, 11 tiles an XCD: 68.2 / 76.4 in three).  Short ones:
+    // once segments are likely to need a second one (whole layer, 128 x 192 in three shares / so: DiT-MoE-XL, 48 tokens 57.2 / 53.7 us, 138:
+    // 63.4 / 59.9; 500 tokens, in two, 85.5 / 81.9, 700 rows 77.0 / 73.8, 575 rows 75.6 / 76.2; where it would be a second round, 267 rows of nine
+    // experts, 11 tiles an XCD, 68.2 / 76.4 in three; 1280 x 5120, 8 experts, 48 to 384 rows, 10 tiles an XCD, 55 - 68 / 65 - 79).  Short ones:
     // 64 x 128 tiles in three shares while these fill three quarters of the chip at most (DiT-MoE-S, 60 tokens 30.9 / 27.9, 170: 31.0 / 28.2, 400:
     // 32.4 / 30.5; 800 tokens top-3, 150 tiles, 36.5 / 38.4; four shares of six steps 1 us behind three).
     if (sums && !gelu && by_expert && fits_128) {
@@ -191,8 +206,13 @@ inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, i
         if (steps < 48) {
             if (steps >= 24 && rows <= 64 * segs && 4 * all_tiles(64, 128) <= kComputeUnits && room(3)) return {FfnTile::Small64, 3};
         } else {
-            const long long t = all_tiles(128, 128) + (rows > 48 * segs ? (N + 127) / 128 : 0);
-            auto fits = [&](int s) { return steps / s >= 16 && (t + 7) / 8 * s <= kStreamSlots && room(s); };
+            const int cols = (N + 127) / 128;
+            const long long expected = all_tiles(128, 128), t = expected + (rows > 48 * segs ? cols : 0);
+            const int bands = static_cast<int>(((rows + 127) / 128 + segs + 7) / 8);      // of eight row tiles, as the launcher's grid has them
+            auto fits = [&](int s) {
+                return steps / s >= 16 && (t + 7) / 8 * s <= kStreamSlots && room(s) &&
+                       one_round_of_shares(static_cast<int>((expected + 7) / 8), s, bands * cols);
+            };
             if (fits(3)) return {FfnTile::Small128, 3};
             if (rows > 80 * segs && fits(2)) return {FfnTile::Small128, 2};
         }

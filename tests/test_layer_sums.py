@@ -45,6 +45,18 @@ def test_split_inside_the_layer_call():
         assert "/" not in P.plan(False, d, F, T * (k + ns), E + ns)
 
 
+@pytest.mark.parametrize("rows,E,d,F,tile", [
+    (1024, 8, 768, 3072, "128x128/2"),           # three shares: nine tiles an XCD
+    (1220, 4, 768, 3072, "128x128/2"),           # nine, with twelve slots a share: nine of 27 workgroups in one group of compute units
+    (48, 8, 1280, 5120, "128x192deep/3"), (384, 8, 1280, 5120, "128x192deep/3"),
+    (610, 8, 1024, 4096, "128x192deep/3"),
+    (48, 8, 1152, 4608, "128x128/3"), (304, 8, 1152, 4608, "128x128/3"),      # nine, with eighteen slots
+    (610, 8, 768, 3072, "128x128/3"),
+])
+def test_shares_run_in_one_round(rows, E, d, F, tile):
+    assert P.plan(False, d, F, rows, E, sums=True) == tile
+
+
 def separate_calls(ctx, buf, x, Wg, bg, w, policy, fuse, to_cache):
     T = x.shape[0]
     rows = T * ctx.slots if policy is None else ctx.moe_policy_refreshed_pairs(policy, T)[0]
