@@ -17,6 +17,7 @@
 // into the compute units, 38 MB of them cold weights; the matrix pipes need 8 us each.
 #pragma once
 #include "ffn_mfma.hpp"
+#include "ffn_plan.hpp"
 #include "ffn_stream.hpp"
 #include "kernels.hpp"
 
@@ -236,7 +237,6 @@ static hipError_t launch_gemm_f32_tile(const float* A, const float* W, const flo
 // about 2 us, as in the bf16 kernels.  Both GEMMs, us, above / here: DiT-MoE-S, 18 tokens top-3 30.5 / 26.8, 2000 tokens 179 / 139, 8192: 508 / 480;
 // DiT-MoE-XL, 100 tokens 157 / 103, 2000: 984 / 880; 2048 x 8192, 4 experts, 200 tokens 458 / 309.
 // K is a multiple of 128 (equal shares of whole stages) and at least kRingMinK (two stages a share).
-constexpr int kRingMinK = 256;
 constexpr int ring_lds(int tm, int tn, int d, bool self = false)
 {
     return kDirectShares * (d * 16 * (tm + tn) * 128 + (kDirectShares - 1) * 1024 + (self ? 512 : 768)) + (self ? kOwnSortPairs * 2 : 0);
@@ -471,29 +471,6 @@ static hipError_t launch_gemm_f32_ring(const float* A, const float* W, const flo
     hipLaunchKernelGGL((ffn_gemm_f32_ring_kernel<GELU, TM, TN, D, SELF>), dim3(kStreamGrid * (smem <= 80 * 1024 ? 2 : 1)), dim3(64 * kDirectShares), smem, stream, A, W, bias, C, N, K,
                        seg_offsets, seg_expert, n_seg, (N + BN - 1) / BN, row_index, row_div, out_index, max_rows, status, sort);
     return hipGetLastError();
-}
-
-// 64 x 64 tiles on the ring kernel.  Short reductions (K < 1536), from four rounds on: one GEMM, us against 32 x 32, DiT-MoE-XL, 850 tiles + 11,
-// 1413: - 11, 2520: - 55; 1024 x 4096, 704 tiles + 5, 1113: - 43; DiT-MoE-S, 942 tiles 0, 1692: - 3.  Long ones, from most of a round on:
-// K = 1536, 142 tiles + 9, 234: - 10, 420: - 11; K = 4608, 212: - 14; but not where many rows a segment make a second round that is nearly
-// empty (K = 2048, 280 tiles, 250 rows a segment + 16; K = 4608, 353 tiles, 125 rows + 2, 630: - 47; 264 tiles of 100 rows - 75).
-static bool ring_wide(int N, int K, int max_rows, int n_seg)
-{
-    const long long tiles = (max_rows / 64 + n_seg / 2ll) * ((N + 63) / 64);
-    if (K < 1536) return tiles >= 4 * kStreamGrid;
-    return tiles >= 200 && !(tiles > kStreamGrid && 2 * tiles < 3 * kStreamGrid && max_rows >= 112ll * n_seg);
-}
-
-// The kernel above takes other reductions and longer tables: 64 x 64 tiles once they fill two and a half rounds of the 256 compute units and the experts have rows for one and a half of them
-// (a segment ends in half a tile on average).  One GEMM, us, 32 x 32 tiles / what 64 x 64 change: second GEMM of DiT-MoE-S, 330 tiles
-// + 5, 612: - 4, 798: - 42, 1584: - 126; 2048 x 8192, 4 experts, 576 tiles + 10; first GEMM of DiT-MoE-S, 94 rows an expert + 5,
-// 125 rows, 940 tiles - 3, 375 rows - 21; 512 x 2048, 64 experts, 31 rows an expert, 2048 tiles + 10, 128 rows - 69.
-enum class F32Tile { Ring32, Ring64, Direct32, Direct64 };
-static F32Tile f32_tile(int N, int K, int max_rows, int n_seg)
-{
-    if (n_seg <= 64 && K % 128 == 0 && K >= kRingMinK) return ring_wide(N, K, max_rows, n_seg) ? F32Tile::Ring64 : F32Tile::Ring32;
-    const long long tiles = (max_rows / 64 + n_seg / 2ll) * ((N + 63) / 64);
-    return tiles >= 640 && max_rows >= 96ll * n_seg ? F32Tile::Direct64 : F32Tile::Direct32;
 }
 
 template <bool GELU>

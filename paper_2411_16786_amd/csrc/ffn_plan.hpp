@@ -1,4 +1,4 @@
-// Which kernel and tile one bf16 grouped GEMM of the expert FFN runs on: the rule on sizes, in plain C++, so that it can be
+// Which kernel and tile one grouped GEMM of the expert FFN runs on: the rules on sizes, in plain C++, so that they can be
 // evaluated without a GPU.
 #pragma once
 #include <cstddef>
@@ -250,6 +250,52 @@ inline FfnPlan plan_ffn_gemm(bool gelu, int N, int K, int max_rows, int n_seg, i
     if (fits_192 && K >= 256 && t192 <= kComputeUnits && t192 * 4 >= kComputeUnits) return {FfnTile::Mid192Deep, 1};
     if (fits_192 && t192 * 2 >= kComputeUnits) return {FfnTile::Mid192, 1};
     return {FfnTile::Staged128, 1};
+}
+
+// ---- float storage: which kernel of ffn_f32.hpp, and its tile
+enum class F32Tile { Ring32, Ring64, Direct32, Direct64 };
+constexpr int kRingMinK = 256;
+
+// 64 x 64 tiles on the ring kernel, one workgroup per compute unit, in place of 32 x 32?  They move half the bytes per flop, but the last round is
+// as long as a full one, half a tile of rows at the end of a segment is twice as many, and short reductions spend their time elsewhere.
+// One GEMM (weights from memory), what 64 x 64 change, in us of the whole FFN:
+//   K from 1536 on: one round nearly full with 112 rows a segment (K = 1536, 234 tiles, 125 rows: - 6 of 95, 252: - 6 of 87; 2048, 208: - 8 of 97; 3072, 228:
+//     - 12 of 154), or five sixths of the rounds' tiles (four fifths from K = 3072 on) with 128 rows (2048, 888 tiles: - 8 of 340; 4608, 432: - 19 of 359,
+//     756: - 56 of 596; 8192, 416: - 27 of 573; but 1536, 276 tiles: + 20 of 89; 2048, 544: + 10 of 216; 3072, 312: + 20 of 181, 816: 0; and 2048, 64 experts of 38
+//     rows, 560 tiles: + 15 of 186, with one hot expert + 22; 3072, 32 experts of 16 rows: + 6 to + 36 of 148);
+//   K from 768 on: nine tenths of them, 700 tiles and 240 rows a segment (768, 1680 tiles, 250 rows: - 10 of 260, 1248 tiles, 181 rows: - 3 to + 12 of 181; 1024,
+//     732 tiles: - 9 of 170, 868: 0; 1152, 2520 tiles, 250 rows: - 23 of 520, 1872 tiles, 181 rows: - 5 to + 1);
+//   below, nowhere (256, 1056 tiles: + 7 of 70; 384, 1632: + 5 of 135; 512, 64 experts, 1024 tiles and more: + 2 to + 28).
+inline bool ring_wide(int N, int K, int max_rows, int n_seg)
+{
+    const long long rows = max_rows, segs = n_seg;
+    const long long tiles = (rows / 64 + segs / 2) * ((N + 63) / 64);
+    const long long full = (tiles + kStreamGrid - 1) / kStreamGrid * kStreamGrid;      // tiles of so many full rounds
+    if (K < 768) return false;
+    if (K < 1536) return rows >= 240 * segs && tiles >= 700 && 10 * tiles >= 9 * full;
+    if (tiles <= kStreamGrid) return tiles >= 200 && rows >= 112 * segs;
+    return rows >= 128 * segs && (K >= 3072 ? 5 * tiles >= 4 * full : 6 * tiles >= 5 * full);
+}
+
+// The direct kernel takes other reductions and longer tables: 64 x 64 tiles once they fill two and a half rounds of the 256 compute units and the experts have rows for one and a half of them
+// (a segment ends in half a tile on average).  One GEMM, us, 32 x 32 tiles / what 64 x 64 change: second GEMM of DiT-MoE-S, 330 tiles
+// + 5, 612: - 4, 798: - 42, 1584: - 126; 2048 x 8192, 4 experts, 576 tiles + 10; first GEMM of DiT-MoE-S, 94 rows an expert + 5,
+// 125 rows, 940 tiles - 3, 375 rows - 21; 512 x 2048, 64 experts, 31 rows an expert, 2048 tiles + 10, 128 rows - 69.
+// Short reductions leave the ring at either end: two stages a share in a quarter of a round (K = 256, us of the FFN, direct 32 x 32 against the ring: 16
+// to 56 tiles - 0.2 to - 0.5 of 12, 240: - 0.2 of 14, 400: + 1 of 17), and very many rows, where few loads of a tile are first ones (direct 64 x 64:
+// K = 256, 2928 tiles - 9 of 170; 4896: - 17 of 277; 384, 4440: - 6 of 339; 512, 3552: - 8 of 340, 9856: - 35 of 919; 640, 7400: - 19 of 836; but 512, 32 experts of
+// 362 rows, 6304 tiles + 10 of 585).
+inline F32Tile f32_tile(int N, int K, int max_rows, int n_seg)
+{
+    const long long rows = max_rows, segs = n_seg;
+    const long long tiles = (rows / 64 + segs / 2) * ((N + 63) / 64);
+    if (n_seg <= 64 && K % 128 == 0 && K >= kRingMinK) {
+        if (ring_wide(N, K, max_rows, n_seg)) return F32Tile::Ring64;
+        if (K < 768 && tiles >= 3500 && rows >= 700 * segs) return F32Tile::Direct64;
+        if (K < 384 && (rows / 32 + segs / 2) * ((N + 31) / 32) <= kComputeUnits) return F32Tile::Direct32;
+        return F32Tile::Ring32;
+    }
+    return tiles >= 640 && rows >= 96 * segs ? F32Tile::Direct64 : F32Tile::Direct32;
 }
 
 }  // namespace dicemoe

@@ -19,6 +19,7 @@ extern "C" void plan(int gelu, int N, int K, int rows, int n_seg, int n_experts,
 extern "C" int columns(int planned, int N, int K, int gelu, int rows, int n_seg, int bands) {
     return dicemoe::stream_looks(planned, N, K, gelu != 0, rows, n_seg) ? dicemoe::stream_columns(planned, dicemoe::stream_cost_192(N, K, gelu != 0), dicemoe::stream_cost_256(N, K, gelu != 0), bands) : planned;
 }
+extern "C" int f32_tile(int N, int K, int rows, int n_seg) { return static_cast<int>(dicemoe::f32_tile(N, K, rows, n_seg)); }
 extern "C" int pieces(int bn, int left, int slots) { return dicemoe::leftover_pieces(bn, left, slots); }
 """
 
@@ -43,6 +44,15 @@ def plan(gelu, N, K, rows, n_seg, n_experts=None, sums=False):
 def ffn_plans(rows, n_seg, d, F, n_experts=None):
     """Tiles of the first and of the second GEMM (n_experts: as many as segments unless given)."""
     return plan(True, F, d, rows, n_seg, n_experts), plan(False, d, F, rows, n_seg, n_experts)
+
+
+# in the order of the enumeration F32Tile
+F32_TILES = ["ring32", "ring64", "direct32", "direct64"]
+
+
+def f32_plans(rows, n_seg, d, F):
+    """Kernel and tile of the first and of the second float GEMM."""
+    return F32_TILES[_lib().f32_tile(F, d, rows, n_seg)], F32_TILES[_lib().f32_tile(d, F, rows, n_seg)]
 
 
 def stream_tiles(seg_rows, seg_expert, N, bn):

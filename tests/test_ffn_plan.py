@@ -86,3 +86,20 @@ def test_every_tile_of_the_rule_is_run_by_a_case():
 ])
 def test_lines_between_the_small_tiles(gelu, N, K, rows, n_seg, n_experts, tile):
     assert P.plan(gelu, N, K, rows, n_seg, n_experts) == tile
+
+
+@pytest.mark.parametrize("rows,segs,d,F,tiles", [
+    # either end of the ring at K = 256, and reductions and tables that it does not take
+    (64, 4, 64, 256, ("direct32", "direct32")), (861, 8, 256, 256, ("direct32", "direct32")), (1448, 8, 256, 256, ("ring32", "ring32")),
+    (11585, 4, 256, 768, ("ring32", "ring64")), (23170, 4, 256, 1024, ("direct64", "ring64")), (11585, 32, 512, 2048, ("ring32", "ring64")),
+    (300, 65, 384, 1536, ("direct32", "direct32")), (500, 8, 272, 800, ("direct32", "direct32")),
+    # 64 x 64 tiles only where rows and rounds are filled
+    (192, 64, 512, 2048, ("ring32", "ring32")), (1000, 64, 512, 2048, ("ring32", "ring32")), (512, 32, 768, 3072, ("ring32", "ring32")),
+    (2435, 16, 384, 1536, ("ring32", "ring32")), (4096, 16, 384, 1536, ("ring32", "ring64")), (2435, 8, 384, 1536, ("ring32", "ring64")),
+    (1448, 8, 512, 2048, ("ring32", "ring64")), (2435, 8, 512, 2048, ("ring32", "ring32")), (11585, 8, 768, 3072, ("ring64", "ring64")),
+    (864, 8, 1152, 4608, ("ring32", "ring32")), (1448, 8, 1152, 4608, ("ring32", "ring64")), (1000, 16, 384, 1536, ("ring32", "ring32")),
+    (2000, 16, 384, 1536, ("ring32", "ring64")), (1000, 8, 768, 3072, ("ring32", "ring64")), (2000, 8, 1152, 4608, ("ring64", "ring64")),
+    (800, 2, 2048, 8192, ("ring64", "ring64")),
+])
+def test_float_tiles(rows, segs, d, F, tiles):
+    assert P.f32_plans(rows, segs, d, F) == tiles

@@ -1,4 +1,4 @@
-"""The float expert FFN on its ring kernel (K a multiple of 128, from 256 on): the shortest share of K, several tiles per workgroup, row
+"""The float expert FFN where its ring kernel is considered (K a multiple of 128, from 256 on): the shortest share of K, several tiles per workgroup, row
 blocks that do not exist, columns that do not fill the last tile, empty segments, experts whose tiles spill to other XCDs, both tiles, with and
 without gather, scatter and biases.  Against the oracle, with the tolerances of tests/gpu_util.py."""
 import numpy as np
@@ -15,13 +15,17 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # (name, rows per segment, d, F)
-    ("two-stages", [1, 16, 17, 32, 33, 0, 64], 256, 256),
+    ("two-stages", [1, 16, 17, 32, 33, 0, 64], 256, 256),            # few tiles: the other kernel
+    ("two-stages-on-the-ring", [1, 16, 17, 32, 33, 0, 64], 256, 1152),
     ("three-and-five", [31, 5, 0, 40], 384, 640),
-    ("ragged-columns", [33, 1, 65], 256, 272),                       # first GEMM: a last tile of 16 columns (second: K = 272, the other kernel)
+    ("ragged-columns", [33, 1, 65], 256, 272),                       # a last tile of 16 columns, but few tiles at K = 256: the other kernel (second: K = 272)
+    ("ragged-columns-on-the-ring", [33, 1, 65], 384, 272),
     ("many-tiles-each", [700, 0, 30, 333], 256, 1152),               # workgroups with several 32 x 32 tiles; one expert spills
     ("one-expert-of-nine", [0] * 8 + [97], 384, 256),
-    ("wide-first", [1000, 900, 1100, 31], 256, 2176),                # 64 x 64 tiles, K = 256 (second: K = 2176, one round)
+    ("many-tiles-two-stages", [1000, 900, 1100, 31], 256, 2176),     # K = 256 (second: K = 2176)
     ("wide-second", [260, 255, 1, 0, 190], 1152, 1536),
+    ("wide-first", [1000, 0, 900, 1100], 768, 944),                  # 64 x 64 tiles, a last one of 48 columns (second: K = 944, the other kernel)
+    ("very-many-rows", [1500], 256, 10240),                          # first GEMM: 64 x 64 tiles of the other kernel
     ("64-segments", [g % 5 * 3 for g in range(64)], 256, 384),
 ]
 
