@@ -52,7 +52,10 @@ struct XcdTiles {
     __device__ __forceinline__ void deal(const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ seg_expert,
                                          int n_seg_, int bm_, int bn_, int n_tiles_n_, int xcd_, int max_rows)
     {
-        load(seg_offsets, expert_of(seg_expert, n_seg_), n_seg_, bm_, max_rows);
+        const int lane = threadIdx.x & 63;
+        int b = 0, e = 0, x = 8;                             // (a home that is nobody's)
+        if (lane < n_seg_) { b = seg_offsets[lane]; e = seg_offsets[lane + 1]; x = seg_expert[lane]; }
+        set(b, e, x, n_seg_, bm_, max_rows);
         deal_columns(bn_, n_tiles_n_, xcd_);
     }
 
