@@ -120,12 +120,16 @@ __global__ __launch_bounds__(kSelThreads) void refresh_select_kernel(RefreshRule
     if (threadIdx.x == 0) *rule.n_refresh = rule.n_value;
     bool sel[KPT];
     select_tokens<KPT>(rule, T_tok, sh, sel);
+    auto write = [&](auto byte_of) {
 #pragma unroll
-    for (int u = 0; u < KPT; ++u) {
-        const int i = u * kSelThreads + static_cast<int>(threadIdx.x);
-        if (i < T_tok)
-            for (int j = 0; j < kc; ++j) rule.mask[static_cast<size_t>(i) * kc + j] = selected_mask(rule, j, sel[u]);
-    }
+        for (int u = 0; u < KPT; ++u) {
+            const int i = u * kSelThreads + static_cast<int>(threadIdx.x);
+            if (i < T_tok)
+                for (int j = 0; j < kc; ++j) rule.mask[static_cast<size_t>(i) * kc + j] = byte_of(j, sel[u]);
+        }
+    };
+    if (rule.token_mode) write([&](int j, bool s) -> uint8_t { return s || j >= rule.k ? 1 : 0; });
+    else write([&](int j, bool s) { return selected_mask(rule, j, s); });
 }
 
 hipError_t launch_refresh(const RefreshRule& rule, int T_tok, hipStream_t stream)
