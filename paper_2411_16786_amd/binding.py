@@ -109,9 +109,16 @@ def _ptr(t: Optional[torch.Tensor], dtype: Optional[torch.dtype] = None) -> Opti
     return t.data_ptr()
 
 
-def _stream() -> int:
-    """The current stream of the current device; the raw handle, without a torch.cuda.Stream around it (2 us a call)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _stream_source(c=torch._C):
+    """What returns the current stream of the current device: the raw handle, without a torch.cuda.Stream around it (2 us a
+    call), where this torch has those functions."""
+    handle, device = getattr(c, "_cuda_getCurrentRawStream", None), getattr(c, "_cuda_getDevice", None)
+    if handle is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: handle(device())
+
+
+_stream = _stream_source()
 
 
 @dataclass
@@ -302,7 +309,9 @@ def moe_layer_forward(ctx: Context, buf: LayerBuffers, x, Wg, bg, W1, b1, W2, b2
     ``buf.x_packed`` is materialised first (the send buffer of the expert-parallel layout).  With
     ``rows_to_cache`` (default whenever there is a policy, the gather is fused and the shape has no
     shared experts) the expert call scatters the refreshed rows straight into ``buf.H_cache`` and the
-    combine reads every row from there: same results bit for bit, ``buf.h_packed`` stays unwritten."""
+    combine reads every row from there: same results bit for bit, ``buf.h_packed`` stays unwritten.
+    Against the separate calls the results are the same bits but for bf16 sizes whose second GEMM only this call splits over
+    several shares of its reduction: their sums are formed in another order."""
     T = x.shape[0]
     cached = policy is not None
     if rows_to_cache is None:

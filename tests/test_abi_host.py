@@ -156,6 +156,29 @@ def test_binding_refuses_cpu_tensors():
         ctx.moe_gate(x, x, None, x, x)
 
 
+def test_current_stream_of_a_torch_without_the_raw_handle(monkeypatch):
+    """The binding asks for the raw handle where torch has it, and the public call where it has not."""
+    class Raw:
+        _cuda_getDevice = staticmethod(lambda: 3)
+        _cuda_getCurrentRawStream = staticmethod(lambda device: 1000 + device)
+
+    class Stream:
+        cuda_stream = 77
+
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: Stream)
+    assert B._stream_source(Raw)() == 1003
+    for missing in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        assert B._stream_source(type("Old", (), {n: getattr(Raw, n) for n in ("_cuda_getDevice", "_cuda_getCurrentRawStream") if n != missing}))() == 77
+
+
+@pytest.mark.gpu
+def test_current_stream_is_torchs():
+    side = B.torch.cuda.Stream()
+    for stream in (B.torch.cuda.default_stream(), side):
+        with B.torch.cuda.stream(stream):
+            assert B._stream() == B.torch.cuda.current_stream().cuda_stream
+
+
 def test_policy_row_count_matches_the_oracle_mask():
     """moe_policy_refreshed_pairs (the C entry point that sizes the FFN launch from the policy alone,
     without a GPU): the count must equal the number of pairs the oracle's mask (Algorithm 4 and the
