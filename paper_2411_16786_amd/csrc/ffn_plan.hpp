@@ -298,4 +298,35 @@ inline F32Tile f32_tile(int N, int K, int max_rows, int n_seg)
     return tiles >= 640 && rows >= 96 * segs ? F32Tile::Direct64 : F32Tile::Direct32;
 }
 
+// ---- the dispatch of a layer, left to the first GEMM (pair_sort.hpp)
+// Pairs that a workgroup of it sorts for itself.  What it costs there is about what the loads of the segment table and of the row
+// indices, one behind the other, cost otherwise; what it saves is a launch.
+constexpr int kOwnSortPairs = 1024;
+// ... and a workgroup of the persistent kernel, which ranks no more than it computes
+constexpr int kStreamSortPairs = 4096;
+
+// Where the first GEMM's workgroups run in about one round: each sorts once, while the loads it saves would have taken as long.  In several
+// rounds the sort comes again with every workgroup (whole layers, us, dispatch / own sort: 64 x 256 float, 64 tokens 28.4 / 24.8; DiT-MoE-S, 60
+// tokens 28.2 / 25.4, 500 tokens 33.9 / 32.1; DiT-MoE-XL, 138 tokens 61.2 / 59.4, 256 tokens 69.4 / 67.5; but DiT-MoE-G, 132 tokens with a shared expert,
+// 952 tiles, 214.3 / 215.5; DiT-MoE-XL, 500 tokens, 720 tiles, 82.0 / 82.1).  The persistent kernel, dispatch / own sort: DiT-MoE-S, 1200 tokens
+// 36.9 / 35.3, 2048 tokens 42.9 / 40.9; DiT-MoE-XL, 1000 tokens 93.2 / 92.6; with more tiles than compute units nothing or a loss (DiT-MoE-XL, 1500 tokens
+// 122.1 / 122.9), and more than 4096 pairs take longer here than in a dispatch on many compute units (DiT-MoE-S, 8192 tokens 93 / 98).
+inline bool ffn_sorts_pairs(bool bf16, int n_pairs, int n_seg, int n_experts, int max_rows, int d, int F)
+{
+    if (n_pairs < 1 || n_pairs > kStreamSortPairs || n_seg != n_experts || max_rows < 1) return false;
+    auto tiles = [&](int bm, int bn) {
+        const int row_tiles = max_rows / bm + n_seg / 2;
+        return static_cast<long long>(row_tiles > n_seg ? row_tiles : n_seg) * ((F + bn - 1) / bn);
+    };
+    if (bf16) {
+        const FfnTile tile = plan_ffn_gemm(true, F, d, max_rows, n_seg, n_experts, 0).tile;
+        if (tile == FfnTile::Stream192) return tiles(256, 192) <= kComputeUnits;
+        if (tile == FfnTile::Stream256) return tiles(256, 256) <= kComputeUnits;
+        return n_pairs <= kOwnSortPairs && ((tile == FfnTile::Small64 && tiles(64, 128) <= 2 * kComputeUnits) || (tile == FfnTile::Mid192Deep && tiles(128, 192) <= kComputeUnits));
+    }
+    if (n_pairs > kOwnSortPairs) return false;
+    const F32Tile tile = f32_tile(F, d, max_rows, n_seg);
+    return tile == F32Tile::Ring32 || (tile == F32Tile::Direct32 && tiles(32, 32) <= 4 * kComputeUnits);
+}
+
 }  // namespace dicemoe

@@ -57,15 +57,14 @@ hipError_t launch_combine_sums(const SplitSums& sums, void* h_packed, const int3
                                int use_fresh, void* y, hipStream_t stream);
 
 // The dispatch of a layer, left to the first GEMM: pairs p of token p / slots with expert expert_idx[p], all of them (rule.mask null) or
-// those that an elementwise policy refreshes.  Its index outputs and the mask are written as launch_dispatch writes them.
+// those that an elementwise policy refreshes (where ffn_sorts_pairs says that it can).  Its index outputs and the mask are written as
+// launch_dispatch writes them.
 struct PairSort {
     const int32_t* expert_idx;
     int n_pairs, experts;
     RefreshRule rule;
     int32_t *counts, *offsets, *perm, *inv;
 };
-// Can the first GEMM of these sizes do it?
-bool ffn_sorts_pairs(bool bf16, int n_pairs, int n_seg, int n_experts, int max_rows, int d, int F);
 
 // x_rows is the packed buffer (row_index == nullptr) or the token matrix with row_index[r] / row_div
 // naming the row that packed row r reads; the h row of packed row r is written to row r of h_out, or

@@ -28,11 +28,6 @@ __device__ __forceinline__ uint64_t same_expert_peers(bool live, int e, int nbit
     return peers;
 }
 
-// Pairs that a workgroup of the first GEMM sorts for itself.  What it costs there is about what the loads of the segment table and of the row
-// indices, one behind the other, cost otherwise; what it saves is a launch (figures at ffn_sorts_pairs).
-constexpr int kOwnSortPairs = 1024;
-// ... and a workgroup of the persistent kernel, which ranks no more than it computes
-constexpr int kStreamSortPairs = 4096;
 constexpr int own_sort_ints(int waves) { return waves * kMaxExperts + kMaxExperts + 4; }      // scratch beside the row list
 
 // off[0 .. E]: offsets of the experts' rows; row[r]: pair of packed row r.  scratch: own_sort_ints(WAVES) ints of LDS, of which `off` is the

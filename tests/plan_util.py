@@ -20,6 +20,9 @@ extern "C" int columns(int planned, int N, int K, int gelu, int rows, int n_seg,
     return dicemoe::stream_looks(planned, N, K, gelu != 0, rows, n_seg) ? dicemoe::stream_columns(planned, dicemoe::stream_cost_192(N, K, gelu != 0), dicemoe::stream_cost_256(N, K, gelu != 0), bands) : planned;
 }
 extern "C" int f32_tile(int N, int K, int rows, int n_seg) { return static_cast<int>(dicemoe::f32_tile(N, K, rows, n_seg)); }
+extern "C" int sorts_pairs(int bf16, int n_pairs, int n_seg, int n_experts, int rows, int d, int F) {
+    return dicemoe::ffn_sorts_pairs(bf16 != 0, n_pairs, n_seg, n_experts, rows, d, F) ? 1 : 0;
+}
 extern "C" int pieces(int bn, int left, int slots) { return dicemoe::leftover_pieces(bn, left, slots); }
 """
 
@@ -53,6 +56,11 @@ F32_TILES = ["ring32", "ring64", "direct32", "direct64"]
 def f32_plans(rows, n_seg, d, F):
     """Kernel and tile of the first and of the second float GEMM."""
     return F32_TILES[_lib().f32_tile(F, d, rows, n_seg)], F32_TILES[_lib().f32_tile(d, F, rows, n_seg)]
+
+
+def sorts_pairs(dtype, T, slots, experts, d, F, rows=None):
+    """Does the first GEMM of a layer call (gather fused, elementwise policy or none) sort the pairs itself?  rows: refreshed pairs (default: all)."""
+    return bool(_lib().sorts_pairs(int(dtype == "bf16"), T * slots, experts, experts, T * slots if rows is None else rows, d, F))
 
 
 def stream_tiles(seg_rows, seg_expert, N, bn):

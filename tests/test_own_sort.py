@@ -14,8 +14,9 @@ KERNELS = [
     # (dtype, d, F, E): first GEMM on
     ("bf16", 384, 512, 16),       # 64 x 128 tiles
     ("bf16", 1152, 1472, 16),     # 128 x 192, three stages, eight wavefronts
-    ("f32", 256, 192, 5),         # ring
+    ("f32", 256, 192, 5),         # direct, two stages of the ring
     ("f32", 64, 80, 64),          # direct
+    ("f32", 384, 192, 5),         # ring
 ]
 POLICIES = [None, (B.REFRESH_ALL, 0), (B.REFRESH_ALG4, 1), (B.REFRESH_ALG4_HIGH, 1), (B.REFRESH_ALG4_RANDOM, 1), (B.REFRESH_NONE, 0)]
 SIZES = [(1, 1, 0), (32, 2, 0), (33, 2, 0), (85, 2, 1), (171, 3, 0), (512, 2, 0), (341, 3, 0), (513, 2, 0)]
@@ -24,6 +25,23 @@ SIZES = [(1, 1, 0), (32, 2, 0), (33, 2, 0), (85, 2, 1), (171, 3, 0), (512, 2, 0)
 def test_the_kernels_are_those():
     assert P.plan(True, 512, 384, 1024, 16) == "64x128" and P.plan(True, 512, 384, 64, 16) == "64x128"
     assert P.plan(True, 1472, 1152, 1024, 16) == "128x192deep" and P.plan(True, 1472, 1152, 64, 16) == "128x192deep"
+    for rows in (2, 1024):
+        assert [P.f32_plans(rows, E, d, F)[0] for dtype, d, F, E in KERNELS if dtype == "f32"] == ["direct32", "direct32", "ring32"]
+
+
+def refreshed(kind, T, k, ns):
+    return {None: T * k, B.REFRESH_ALL: T * k, B.REFRESH_NONE: 0}.get(kind, T) + T * ns
+
+
+@pytest.mark.parametrize("kernel", range(len(KERNELS)))
+@pytest.mark.parametrize("size", SIZES)
+def test_they_sort_the_pairs(kernel, size):
+    """... up to 1024 pairs, if any is refreshed."""
+    dtype, d, F, E = KERNELS[kernel]
+    T, k, ns = size
+    for entry in POLICIES:
+        rows = refreshed(entry and entry[0], T, k, ns)
+        assert P.sorts_pairs(dtype, T, k + ns, E + ns, d, F, rows) == (T * (k + ns) <= 1024 and rows > 0), entry
 
 
 @pytest.mark.gpu
