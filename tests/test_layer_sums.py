@@ -76,6 +76,19 @@ def separate_calls(ctx, buf, x, Wg, bg, w, policy, fuse, to_cache):
                     policy is not None and policy.use_fresh_scores, buf.y[:T])
 
 
+def same_outputs(a, b, T, F, exact, what):
+    """Outputs of the layer call (a) and of the separate calls (b): bit for bit, or, where only the layer call splits, within the bound above."""
+    for name in ("y", "H_cache", "S_cache", "h_packed"):
+        p, q = getattr(a, name), getattr(b, name)
+        if exact or name == "S_cache":
+            assert p is None or torch.equal(p, q), (name, what)
+        elif p is not None:
+            p, q = p.float(), q.float()
+            scale = q.abs() if name != "y" else q.abs() + b.H_cache[:T].float().abs().amax() if b.H_cache is not None else q.abs() + b.h_packed.float().abs().amax()
+            assert ((p - q).abs() <= 2.0 ** -7 * scale[:len(p)] + F / 16 * 2.0 ** -24 * 0.04 * F).all(), (name, what)
+            assert (p == q).float().mean() > 0.9, (name, what)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", range(len(CASES) + len(ONLY_HERE)))
 @pytest.mark.parametrize("kind", range(len(HALF)))
@@ -104,13 +117,47 @@ def test_combine_adds_the_shares(case, kind):
             B.moe_layer_forward(ctx, a, x, Wg, bg, W1, b1, W2, b2, policy, fuse_gather=fuse, rows_to_cache=to_cache)
             separate_calls(ctx, b, x, Wg, bg, (W1, b1, W2, b2), policy, fuse, to_cache)
             torch.cuda.synchronize()
-            for name in ("y", "H_cache", "S_cache", "h_packed", "x_packed"):
-                p, q = getattr(a, name), getattr(b, name)
-                if case < len(CASES) or name in ("S_cache", "x_packed"):
-                    assert p is None or torch.equal(p, q), (name, to_cache, fuse)
-                elif p is not None:
-                    p, q = p.float(), q.float()
-                    scale = q.abs() if name != "y" else q.abs() + b.H_cache[:T].float().abs().amax() if b.H_cache is not None else q.abs() + b.h_packed.float().abs().amax()
-                    assert ((p - q).abs() <= 2.0 ** -7 * scale[:len(p)] + F / 16 * 2.0 ** -24 * 0.04 * F).all(), (name, to_cache, fuse)
-                    assert (p == q).float().mean() > 0.9, (name, to_cache, fuse)
+            same_outputs(a, b, T, F, case < len(CASES), (to_cache, fuse))
+            assert a.x_packed is None or torch.equal(a.x_packed, b.x_packed), (to_cache, fuse)
             assert torch.isfinite(a.y[:T].float()).all() and a.y[:T].float().abs().sum() > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [0, 1, 3, 5, 6])
+@pytest.mark.parametrize("to_cache", [False, True])
+def test_rows_beyond_the_bound_are_left_alone(case, to_cache):
+    """A bound a few rows short: rows within it are computed as ever, those beyond it are neither read from the shares nor written, and the
+    status call reports them."""
+    T, T_max, d, F, E, k, ns, shares = CASES[case]
+    if to_cache and ns:
+        pytest.skip("rows_to_cache needs a shape without shared experts")
+    short = T * (k + ns) - 5
+    assert P.plan(False, d, F, short, E + ns, sums=True) == P.plan(False, d, F, short + 5, E + ns, sums=True)
+    assert P.plan(False, d, F, short, E + ns, sums=True).endswith(f"/{shares}")
+    print(f"\nbound short, case {case} to_cache={to_cache}", flush=True)
+    x, Wg, bg, *_ = G.small_inputs(91 + case, T, d, E, 64, "bf16")
+    gen = torch.Generator(device=G.DEV).manual_seed(case)
+    normal = lambda *s: torch.randn(s, generator=gen, device=G.DEV) * 0.05
+    w = (normal(E + ns, F, d).bfloat16(), normal(E + ns, F), normal(E + ns, d, F).bfloat16(), normal(E + ns, d))
+    x, Wg, bg = G.to_dev(x, "bf16"), G.to_dev(Wg, "bf16"), G.f32_dev(bg)
+    policy = B.Policy(B.REFRESH_ALL) if to_cache else None
+    ctx = B.Context(T_max, d, F, E, k, "bf16", n_shared=ns)
+    a, b = (B.LayerBuffers(ctx, G.DEV, with_cache=to_cache) for _ in range(2))
+    for buf, rows in ((a, short + 5), (b, short)):
+        buf.h_packed.fill_(0.5)
+        if to_cache:
+            buf.H_cache.fill_(0.5)
+        B.moe_layer_forward(ctx, buf, x, Wg, bg, *w, policy, max_rows=rows)
+    torch.cuda.synchronize()
+    lost = a.perm[short:short + 5].long()                 # pairs of the rows beyond the bound
+    p, q = (buf.H_cache.flatten(0, 1) if to_cache else buf.h_packed for buf in (a, b))
+    rows = lost if to_cache else torch.arange(short, short + 5, device=G.DEV)
+    assert (q[rows] == 0.5).all() and (p[rows] != 0.5).any()
+    q[rows] = p[rows]
+    assert torch.equal(p, q)
+    whole = torch.ones(T, dtype=torch.bool, device=G.DEV)
+    whole[lost // (k + ns)] = False                       # tokens of which no row is missing
+    assert torch.equal(a.y[:T][whole], b.y[:T][whole]) and whole.any()
+    ctx.moe_expert_ffn_status(a.workspace)
+    with pytest.raises(B.MoeError):
+        ctx.moe_expert_ffn_status(b.workspace)

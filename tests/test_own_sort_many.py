@@ -1,5 +1,6 @@
 """Layers whose first GEMM runs on the persistent kernel and sorts up to 4096 pairs itself: every buffer the layer leaves behind has the bits of
-the separate calls (with a dispatch of their own), at the pair counts where the sort takes another number of steps, for workgroups that come
+the separate calls (with a dispatch of their own; outputs where only the layer call splits the second GEMM: within the bound of
+test_layer_sums.py), at the pair counts where the sort takes another group of four steps, for workgroups that come
 back for rows (a piece of a leftover tile) and those that do not, for either width and for the kernel that picks it, with every
 kind of mask."""
 import pytest
@@ -9,13 +10,15 @@ from paper_2411_16786_amd import binding as B
 
 import gpu_util as G
 import plan_util as P
-from test_layer_sums import separate_calls
+from test_layer_sums import same_outputs, separate_calls
 
 CASES = [
     # (T, k, n_shared, d, F, E, hot expert's bias, planned first GEMM, what it runs)
     (700, 3, 0, 384, 1536, 8, 0.0, "stream192", {"halves", "rowless"}),
     (512, 2, 0, 384, 3072, 8, 0.0, "stream192", {"halves"}),                     # 1024 pairs
-    (1025, 2, 0, 384, 3072, 8, 0.0, "stream192", {"leftover"}),                  # 2050: five steps
+    (1024, 2, 0, 512, 2560, 8, 0.0, "stream192", set()),                         # 2048: a group of four steps a wavefront
+    (2049, 1, 0, 512, 2560, 8, 0.0, "stream192", set()),                         # 2049: two
+    (1025, 2, 0, 384, 3072, 8, 0.0, "stream192", {"leftover"}),                  # 2050
     (1365, 2, 1, 512, 2048, 15, 1.0, "stream256", {"leftover"}),                 # 4095, one shared expert
     (1821, 1, 0, 1792, 2048, 8, 0.0, "stream256", {"halves", "rowless"}),
     (2048, 2, 0, 384, 1920, 16, 0.0, "stream192", {"whole"}),                    # 4096, more than one tile a workgroup
@@ -30,7 +33,9 @@ POLICIES = [None, (B.REFRESH_ALL, 0), (B.REFRESH_ALG4, 1), (B.REFRESH_ALG4_RANDO
 def test_the_plan(case):
     T, k, ns, d, F, E, _, planned, _ = case
     assert P.plan(True, F, d, T * (k + ns), E + ns) == planned
-    assert P.plan(False, d, F, T * (k + ns), E + ns) == P.plan(False, d, F, T * (k + ns), E + ns, sums=True) or T in (2048, 512, 1821, 1025)
+    assert P.sorts_pairs("bf16", T, k + ns, E + ns, d, F) == (T * (k + ns) <= 4096)
+    # (the second GEMM of these two is in three shares of one tile in the layer call, of another in the separate ones)
+    assert (P.plan(False, d, F, T * (k + ns), E + ns) != P.plan(False, d, F, T * (k + ns), E + ns, sums=True)) == ((T, F) in ((512, 3072), (1025, 3072)))
 
 
 @pytest.mark.gpu
@@ -61,13 +66,10 @@ def test_own_sort_of_many_pairs(case):
         items = P.stream_items(rows, list(range(E + ns)), F, int(planned[6:]))
         print(entry, rows, items, P.describe(rows, list(range(E + ns)), d, F)[0], flush=True)
         assert entry is not None or runs <= items
-        names = ["scores", "expert_idx", "mask", "n_refresh", "counts", "offsets", "perm", "inv"]
-        # (outputs where the layer call splits the second GEMM as the separate calls do)
-        if P.plan(False, d, F, sum(rows), E + ns) == P.plan(False, d, F, sum(rows), E + ns, sums=True):
-            names += ["y", "h_packed", "H_cache", "S_cache"]
-        for name in names:
+        for name in ("scores", "expert_idx", "mask", "n_refresh", "counts", "offsets", "perm", "inv"):
             p, q = getattr(a, name), getattr(b, name)
             assert p is None or torch.equal(p, q), (entry, name)
+        same_outputs(a, b, T, F, P.plan(False, d, F, sum(rows), E + ns) == P.plan(False, d, F, sum(rows), E + ns, sums=True), entry)
         ctx.moe_expert_ffn_status(a.workspace)
 
 
