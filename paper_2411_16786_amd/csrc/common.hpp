@@ -107,6 +107,17 @@ __device__ __forceinline__ float wave_max(float v) {
     return v;
 }
 
+// inclusive sums over the lanes: lane l ends with the values of lanes 0 .. l
+__device__ __forceinline__ int wave_scan(int v) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int sh = 1; sh < kWave; sh <<= 1) {
+        const int below = __shfl_up(v, sh, kWave);
+        if (lane >= sh) v += below;
+    }
+    return v;
+}
+
 __device__ __forceinline__ uint64_t lanemask_lt() {
     return (1ull << lane_id()) - 1ull;
 }

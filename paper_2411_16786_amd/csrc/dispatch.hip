@@ -80,8 +80,7 @@ __device__ __forceinline__ void load_steps(const int32_t* __restrict__ expert_id
 #pragma unroll
     for (int u = 0; u < S; ++u) {
         const int p = p0 + u * kWave + lane;
-        const bool ok = p < N && mv[u] != 0 && static_cast<unsigned>(ev[u]) < static_cast<unsigned>(E);
-        ev[u] = ok ? ev[u] : -1;
+        ev[u] = has_row(p, N, mv[u], ev[u], E) ? ev[u] : -1;
     }
 }
 
@@ -129,12 +128,7 @@ __global__ __launch_bounds__(1024) void dispatch_scan_kernel(int32_t* __restrict
     for (int e = wave; e < E; e += 1024 / kWave) {
         int run = 0;
         for (int bb = b_lo; bb < b_hi; ++bb) run += block_counts[static_cast<size_t>(bb) * E + e];
-        int incl = run;                           // inclusive scan of the lanes' sums
-#pragma unroll
-        for (int sh = 1; sh < kWave; sh <<= 1) {
-            const int v = __shfl_up(incl, sh, kWave);
-            if (lane >= sh) incl += v;
-        }
+        const int incl = wave_scan(run);
         int prefix = incl - run;
         for (int bb = b_lo; bb < b_hi; ++bb) {
             const int c = block_counts[static_cast<size_t>(bb) * E + e];
@@ -209,40 +203,21 @@ __global__ __launch_bounds__(THREADS) void dispatch_place_kernel(const int32_t* 
     if (p0 < N) {                                           // wave-uniform
         load_steps<S, SOURCE>(expert_idx, mask, p0, lane, N, E, rule, sel_bits, ev);
 #pragma unroll
-        for (int u = 0; u < S; ++u) {
-            const bool live = ev[u] >= 0;
-            const int e = live ? ev[u] : 0;
-            const uint64_t peers = same_expert_peers(live, e, nbits);
-            const int before = __popcll(peers & lanemask_lt());
-            const int run = wave_run[wave][e];             // every peer reads the same running count ...
-            rank[u] = run + before;
-            wave_sync();
-            if (live && before == 0) wave_run[wave][e] = run + __popcll(peers);   // ... then the first updates it
-            wave_sync();
-        }
+        for (int u = 0; u < S; ++u) rank[u] = rank_step(ev[u], nbits, wave_run[wave]);
     } else {
 #pragma unroll
         for (int u = 0; u < S; ++u) { ev[u] = -1; rank[u] = 0; }
     }
     __syncthreads();
     if (tid < E) {
-        int cnt[WAVES], t = 0;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) cnt[w] = wave_run[w][tid];
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) { wave_run[w][tid] = t; t += cnt[w]; }
+        const int t = counts_to_prefixes<WAVES>(wave_run[0], tid);
         if (n_blocks == 1) s_tot[tid] = t;
     }
     __syncthreads();
     // exclusive scan over the experts: lane e of the first wave holds expert e's total
     if (wave == 0) {
         const int mine = lane < E ? s_tot[lane] : 0;
-        int incl = mine;
-#pragma unroll
-        for (int sh = 1; sh < kWave; sh <<= 1) {
-            const int v = __shfl_up(incl, sh, kWave);
-            if (lane >= sh) incl += v;
-        }
+        const int incl = wave_scan(mine);
         if (lane < E) {
             s_off[lane] = incl - mine;
             if (b == 0) { counts[lane] = mine; offsets[lane] = incl - mine; }
@@ -260,15 +235,7 @@ __global__ __launch_bounds__(THREADS) void dispatch_place_kernel(const int32_t* 
         for (int u = 0; u < S; ++u) {
             const int p = p0 + u * kWave + lane;
             const int e = ev[u];
-            int r = -1;
-            if (e >= 0) {
-                r = s_off[e] + s_pre[e] + wave_run[wave][e] + rank[u];
-                perm[r] = p;
-            }
-            if (p < N) {
-                inv[p] = r;
-                if (p >= R) perm[p] = -1;                  // packed rows beyond the refreshed ones
-            }
+            leave_index(p, N, e >= 0, [&] { return s_off[e] + s_pre[e] + wave_run[wave][e] + rank[u]; }, R, perm, inv);
         }
     }
 }
@@ -480,12 +447,7 @@ __global__ void ep_segments_kernel(const int32_t* __restrict__ recv_counts, int 
     for (int g0 = 0; g0 < n_seg; g0 += kWave) {
         const int g = g0 + lane;
         const int mine = g < n_seg ? recv_counts[g] : 0;
-        int incl = mine;
-#pragma unroll
-        for (int sh = 1; sh < kWave; sh <<= 1) {
-            const int v = __shfl_up(incl, sh, kWave);
-            if (lane >= sh) incl += v;
-        }
+        const int incl = wave_scan(mine);
         if (g < n_seg) {
             seg_offsets[g] = run + incl - mine;
             seg_expert[g] = g % E_loc;

@@ -37,12 +37,7 @@ __device__ __forceinline__ bool find_row_tile_by_lanes(const int32_t* __restrict
         const int g = g0 + lane;
         const int begin = g < n_seg ? seg_offsets[g] : 0, end = g < n_seg ? seg_offsets[g + 1] : 0;
         const int nt = (end - begin + BM - 1) / BM;
-        int incl = nt;
-#pragma unroll
-        for (int sh = 1; sh < 64; sh <<= 1) {
-            const int v = __shfl_up(incl, sh, 64);
-            if (lane >= sh) incl += v;
-        }
+        const int incl = wave_scan(nt);
         const uint64_t hit = __ballot(tile < incl);          // the first lane's segment holds the tile
         if (hit != 0) {
             const int l = __builtin_ctzll(hit);

@@ -28,6 +28,55 @@ __device__ __forceinline__ uint64_t same_expert_peers(bool live, int e, int nbit
     return peers;
 }
 
+// ---- one pair of the sort, the same for every kernel that sorts (these two, and the dispatch's own)
+
+// Does pair p, with mask byte m and expert id e, have a row?  Not past the end, not unless refreshed, and not with a bad id.
+__device__ __forceinline__ bool has_row(int p, int N, uint8_t m, int e, int E)
+{
+    return p < N && m != 0 && static_cast<unsigned>(e) < static_cast<unsigned>(E);
+}
+
+// Rank of each lane's pair among this wavefront's pairs of the same expert so far (e < 0: none), in lane order; run: their counts
+__device__ __forceinline__ int rank_step(int e, int nbits, int* run)
+{
+    const bool live = e >= 0;
+    e = live ? e : 0;
+    const uint64_t peers = same_expert_peers(live, e, nbits);
+    const int before = __popcll(peers & lanemask_lt());
+    const int so_far = run[e];                               // every peer reads the same running count ...
+    wave_sync();
+    if (live && before == 0) run[e] = so_far + __popcll(peers);      // ... then the first updates it
+    wave_sync();
+    return so_far + before;
+}
+
+// run[WAVES][kMaxExperts]: the wavefronts' counts of expert e become those of the wavefronts before each; returns the sum
+template <int WAVES>
+__device__ __forceinline__ int counts_to_prefixes(int* run, int e)
+{
+    int cnt[WAVES], total = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) cnt[w] = run[w * kMaxExperts + e];
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) { run[w * kMaxExperts + e] = total; total += cnt[w]; }
+    return total;
+}
+
+// Index entries of pair p (its row(), if it has one) and of packed row p (that there is none, if there are only R)
+template <typename Fn>
+__device__ __forceinline__ void leave_index(int p, int N, bool has, Fn row, int R, int32_t* __restrict__ perm, int32_t* __restrict__ inv)
+{
+    int r = -1;
+    if (has) {
+        r = row();
+        perm[r] = p;
+    }
+    if (p < N) {
+        inv[p] = r;
+        if (p >= R) perm[p] = -1;
+    }
+}
+
 constexpr int own_sort_ints(int waves) { return waves * kMaxExperts + kMaxExperts + 4; }      // scratch beside the row list
 
 // off[0 .. E]: offsets of the experts' rows; row[r]: pair of packed row r.  scratch: own_sort_ints(WAVES) ints of LDS, of which `off` is the
@@ -57,35 +106,17 @@ __device__ __forceinline__ const int* sort_pairs(const PairSort& s, bool writer,
         const int p = p0 + u * kWave;
         rank[u] = 0;
         if (u >= steps) { ev[u] = -1; continue; }           // (uniform)
-        bool ok = p < N && static_cast<unsigned>(ev[u]) < static_cast<unsigned>(E);
+        uint8_t m = 1;
         if (s.rule.mask) {
-            const uint8_t m = simple_mask(s.rule, p);
+            m = simple_mask(s.rule, p);
             if (writer && p < N) s.rule.mask[p] = m;
-            ok = ok && m != 0;
         }
-        if (!ok) ev[u] = -1;
-        const int e = ok ? ev[u] : 0;
-        const uint64_t peers = same_expert_peers(ok, e, nbits);
-        const int before = __popcll(peers & lanemask_lt());
-        const int so_far = run[wave * kMaxExperts + e];      // every peer reads the same running count ...
-        rank[u] = so_far + before;
-        wave_sync();
-        if (ok && before == 0) run[wave * kMaxExperts + e] = so_far + __popcll(peers);      // ... then the first updates it
-        wave_sync();
+        if (!has_row(p, N, m, ev[u], E)) ev[u] = -1;
+        rank[u] = rank_step(ev[u], nbits, run + wave * kMaxExperts);
     }
     __syncthreads();
     if (wave == 0) {                                         // lane e is expert e
-        int cnt[WAVES], total = 0;
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) cnt[w] = run[w * kMaxExperts + lane];
-#pragma unroll
-        for (int w = 0; w < WAVES; ++w) { run[w * kMaxExperts + lane] = total; total += cnt[w]; }
-        int incl = total;
-#pragma unroll
-        for (int sh = 1; sh < kWave; sh <<= 1) {
-            const int v = __shfl_up(incl, sh, kWave);
-            if (lane >= sh) incl += v;
-        }
+        const int total = counts_to_prefixes<WAVES>(run, lane), incl = wave_scan(total);
         if (lane == 0) off[0] = 0;
         off[lane + 1] = incl;                                // (experts from E on have no pairs)
         if (writer) {
@@ -105,11 +136,7 @@ __device__ __forceinline__ const int* sort_pairs(const PairSort& s, bool writer,
             r = off[ev[u]] + run[wave * kMaxExperts + ev[u]] + rank[u];
             row[r] = static_cast<uint16_t>(p);
         }
-        if (writer && p < N) {
-            if (r >= 0) s.perm[r] = p;
-            s.inv[p] = r;
-            if (p >= R) s.perm[p] = -1;                      // packed rows beyond the refreshed ones
-        }
+        if (writer) leave_index(p, N, r >= 0, [&] { return r; }, R, s.perm, s.inv);
     }
     __syncthreads();
     return off;
@@ -156,13 +183,13 @@ struct CountedPairs {
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int p = base + (g * 4 + u) * kWave + lane;
-                bool ok = p < N && static_cast<unsigned>(ev[u]) < static_cast<unsigned>(E);
                 const bool mine = (p >> 6) == static_cast<int>(blockIdx.x) && p < N;
+                uint8_t m = 1;
                 if (s.rule.mask) {
-                    const uint8_t m = simple_mask(s.rule, p);
+                    m = simple_mask(s.rule, p);
                     if (mine) s.rule.mask[p] = m;
-                    ok = ok && m != 0;
                 }
+                const bool ok = has_row(p, N, m, ev[u], E);
                 if (mine && !ok) s.inv[p] = -1;
                 word |= static_cast<uint32_t>(ok ? ev[u] : 255) << (8 * u);
                 if (ok) __hip_atomic_fetch_add(&run[wave * kMaxExperts + ev[u]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -181,12 +208,7 @@ struct CountedPairs {
             before += w < wave ? c : 0;
             total += c;
         }
-        int incl = total;
-#pragma unroll
-        for (int sh = 1; sh < kWave; sh <<= 1) {
-            const int v = __shfl_up(incl, sh, kWave);
-            if (lane >= sh) incl += v;
-        }
+        const int incl = wave_scan(total);
         begin = incl - total;
         end = incl;
         first = begin + before;
