@@ -13,8 +13,7 @@
 // Both GEMMs, graph of ten calls, against 64 x 64 tiles on the vector units: DiT-MoE-S widths, 500 tokens top-2: 137 -> 56 us; 100
 // tokens 127 -> 28; 64 x 256, 4 experts, 64 tokens 28 -> 10, all on 32 x 32 tiles.  On those alone many rows lose what few
 // gain: 16384 rows of the DiT-MoE-S widths 577 us on the vector units, 595 on 32 x 32 tiles, 493 on 64 x 64; 8192 of DiT-MoE-XL 2422, 2604
-// and 1769.  What bounds the small tiles now was not separated: 33 us and 28 us at 500 tokens (kernel trace) move 185 MB each
-// into the compute units, 38 MB of them cold weights; the matrix pipes need 8 us each.
+// and 1769.  Which of these sizes the ring kernel below has taken over since: f32_tile.
 #pragma once
 #include "ffn_mfma.hpp"
 #include "ffn_plan.hpp"
@@ -227,7 +226,7 @@ static hipError_t launch_gemm_f32_tile(const float* A, const float* W, const flo
 //     rows come through LDS as well, so that no load into a register makes the wavefront wait for the loads behind it.
 // 32 x 32 tiles, two stages, two workgroups per compute unit (one multiplies while the other one's sums meet): three or four stages and one
 // workgroup are slower, also with 32 x 64 tiles (500 tokens of DiT-MoE-S, both GEMMs: 66.6 us above; 55.1; 66.5 four stages; 57.2
-// 32 x 64 in three).  64 x 64 tiles, two stages, one workgroup, move half the bytes per flop and are better once they fill the chip.
+// 32 x 64 in three).  64 x 64 tiles, two stages, one workgroup, move half the bytes per flop: ring_wide says where that is better.
 // What bounds it now is the way into LDS: 10 TB/s of stage loads where L2 misses keep 64 to 128 KB per compute unit in flight for
 // about 2 us, as in the bf16 kernels.  Both GEMMs, us, above / here: DiT-MoE-S, 18 tokens top-3 30.5 / 26.8, 2000 tokens 179 / 139, 8192: 508 / 480;
 // DiT-MoE-XL, 100 tokens 157 / 103, 2000: 984 / 880; 2048 x 8192, 4 experts, 200 tokens 458 / 309.

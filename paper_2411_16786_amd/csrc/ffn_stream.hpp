@@ -547,9 +547,10 @@ __device__ __forceinline__ void stream_tiles(const StreamArgs& g, char* smem, in
 }
 
 // All items of a workgroup on tiles of 256 x 64 TN
-// OWN: the row index comes from `pairs`, before anything is loaded: into LDS for the first two items, and for those that a workgroup comes to
-// after its LDS has been taken by stages, where the kernels behind read it.  Workgroups with an item's first columns leave it there in any
-// case (who writes the same place writes the same).
+// OWN: the row index comes from `pairs`, before anything is loaded: into LDS for the first two items, and where the kernels behind read it for
+// what a workgroup comes to after its LDS has been taken by stages.  That is the piece behind whole tiles: ffn_sorts_pairs lets in as many tiles as
+// compute units by its estimate, of which there are half as many again at most, so that nobody has a third whole one.  Workgroups with
+// an item's first columns leave its rows there in any case (who writes the same place writes the same).
 template <int TN, bool GELU, bool GATHER, bool OWN>
 __device__ __forceinline__ void stream_items(const StreamArgs& g, char* smem, XcdTiles& tiles, const StreamPairs* pairs = nullptr, const PairSort* sort = nullptr)
 {
