@@ -80,7 +80,7 @@ __device__ __forceinline__ void load_steps(const int32_t* __restrict__ expert_id
 #pragma unroll
     for (int u = 0; u < S; ++u) {
         const int p = p0 + u * kWave + lane;
-        ev[u] = has_row(p, N, mv[u], ev[u], E) ? ev[u] : -1;
+        ev[u] = has_row(p, N, ev[u], E) && mv[u] != 0 ? ev[u] : -1;
     }
 }
 

@@ -30,10 +30,10 @@ __device__ __forceinline__ uint64_t same_expert_peers(bool live, int e, int nbit
 
 // ---- one pair of the sort, the same for every kernel that sorts (these two, and the dispatch's own)
 
-// Does pair p, with mask byte m and expert id e, have a row?  Not past the end, not unless refreshed, and not with a bad id.
-__device__ __forceinline__ bool has_row(int p, int N, uint8_t m, int e, int E)
+// Does pair p with expert id e have a row, if it is refreshed?  Not past the end, and not with a bad id.
+__device__ __forceinline__ bool has_row(int p, int N, int e, int E)
 {
-    return p < N && m != 0 && static_cast<unsigned>(e) < static_cast<unsigned>(E);
+    return p < N && static_cast<unsigned>(e) < static_cast<unsigned>(E);
 }
 
 // Rank of each lane's pair among this wavefront's pairs of the same expert so far (e < 0: none), in lane order; run: their counts
@@ -106,12 +106,13 @@ __device__ __forceinline__ const int* sort_pairs(const PairSort& s, bool writer,
         const int p = p0 + u * kWave;
         rank[u] = 0;
         if (u >= steps) { ev[u] = -1; continue; }           // (uniform)
-        uint8_t m = 1;
+        bool ok = has_row(p, N, ev[u], E);
         if (s.rule.mask) {
-            m = simple_mask(s.rule, p);
+            const uint8_t m = simple_mask(s.rule, p);
             if (writer && p < N) s.rule.mask[p] = m;
+            ok = ok && m != 0;
         }
-        if (!has_row(p, N, m, ev[u], E)) ev[u] = -1;
+        if (!ok) ev[u] = -1;
         rank[u] = rank_step(ev[u], nbits, run + wave * kMaxExperts);
     }
     __syncthreads();
@@ -184,12 +185,12 @@ struct CountedPairs {
             for (int u = 0; u < 4; ++u) {
                 const int p = base + (g * 4 + u) * kWave + lane;
                 const bool mine = (p >> 6) == static_cast<int>(blockIdx.x) && p < N;
-                uint8_t m = 1;
+                bool ok = has_row(p, N, ev[u], E);
                 if (s.rule.mask) {
-                    m = simple_mask(s.rule, p);
+                    const uint8_t m = simple_mask(s.rule, p);
                     if (mine) s.rule.mask[p] = m;
+                    ok = ok && m != 0;
                 }
-                const bool ok = has_row(p, N, m, ev[u], E);
                 if (mine && !ok) s.inv[p] = -1;
                 word |= static_cast<uint32_t>(ok ? ev[u] : 255) << (8 * u);
                 if (ok) __hip_atomic_fetch_add(&run[wave * kMaxExperts + ev[u]], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
