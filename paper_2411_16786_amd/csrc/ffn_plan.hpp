@@ -91,7 +91,7 @@ constexpr bool stream_fits_192(int N) { return (N + 191) / 192 * 192 * 8 <= N * 
 // unless the other width is expected to be faster by more than the model is off (8 us) on the real ones.  Weights from memory make a step of
 // 192 columns 1.11 us where the host's 1.06 were measured warm.  Whole layer, us, with the planned width / with this rule: second GEMM of
 // DiT-MoE-G, 4096 tokens, 504 / 483 (192 -> 256); first of DiT-MoE-XL, 3000 tokens, 174 / 167 (192 -> 256), 5000 tokens 243 / 230; expert-parallel widths,
-// 4000 tokens, 592 / 568 (192 -> 256); DiT-MoE-XL with two shared experts, 4096 tokens: nothing beyond the noise (298 / 296).
+// 4000 tokens, 592 / 568 (192 -> 256); DiT-MoE-XL with two shared experts, 4096 tokens, 298 / 291 to 296.
 constexpr int stream_columns(int planned, const StreamCost& c192, const StreamCost& c256, int bands)
 {
     const float t192 = stream_cost_of_bands(c192, bands), t256 = stream_cost_of_bands(c256, bands);
