@@ -5,6 +5,7 @@ import itertools
 import pytest
 
 import plan_util as P
+import test_gpu_f32_ring as ring
 import test_gpu_ffn_stream as stream
 import test_gpu_parity as parity
 import test_gpu_small_tiles as small
@@ -103,3 +104,11 @@ def test_lines_between_the_small_tiles(gelu, N, K, rows, n_seg, n_experts, tile)
 ])
 def test_float_tiles(rows, segs, d, F, tiles):
     assert P.f32_plans(rows, segs, d, F) == tiles
+
+
+def test_float_cases_run_what_they_are_named_for():
+    plans = {name: P.f32_plans(sum(seg), len(seg), d, F) for name, seg, d, F in ring.CASES}
+    assert plans["two-stages-on-the-ring"][0] == plans["many-tiles-two-stages"][0] == plans["64-segments"][0] == "ring32"        # K = 256
+    assert plans["ragged-columns-on-the-ring"][0] == plans["three-and-five"][0] == plans["one-expert-of-nine"][0] == "ring32"   # K = 384
+    assert plans["wide-first"][0] == plans["wide-second"][1] == "ring64"
+    assert plans["two-stages"] == ("direct32", "direct32") and plans["very-many-rows"][0] == "direct64"
