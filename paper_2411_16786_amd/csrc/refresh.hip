@@ -3,8 +3,8 @@
 //
 // ALL / NONE / ALG4 are elementwise.  The fraction policies need an exact top-m selection of
 // tokens by a float score with ties going to the lower token index; one workgroup does it with a
-// most-significant-digit radix select on the score's bit pattern (4 passes of 8 bits, LDS
-// histograms), then resolves ties at the threshold by a block-wide prefix count in index order.
+// most-significant-digit radix select on the score's bit pattern (up to 16384 tokens as select_tokens in refresh_rule.hpp does it,
+// beyond that four passes of 8 bits over memory), then resolves ties at the threshold by a block-wide prefix count in index order.
 // Everything is integer work on the bit patterns, so the mask is reproducible bit for bit.
 #include "refresh_rule.hpp"
 
